@@ -269,6 +269,45 @@ __device__ __forceinline__ void pull(const T* __restrict__ src, int x, int y, co
     pull_complete<T, OPEN>(src, x, y, g, Fx, s);
 }
 
+// One axis of an MLS fit (Eq. 9) at p on the nodes c - 1, c, c + 1: with the
+// weights w_i = exp(-(X_i / 0.78)^2), X_i = c + i - 1 - p (0.78 = r_w alpha)
+// and their moments S_q = sum w X^q, D = S_0 S_2 - S_1^2,
+//   a = w / S_0                  the weighted mean,
+//   b = w (S_2 - S_1 X) / D      the value at p of the weighted straight line,
+//   s = w (S_0 X - S_1) / D      its slope.
+// Offsets and weights in the population type, the fit in FP64.
+struct AxisFit {
+    double a[3], b[3], s[3];
+};
+
+template <typename T>
+__device__ __forceinline__ AxisFit axis_fit(T p, int c)
+{
+    const T inv2 = T(1.0 / (2.6 * 0.3 * 2.6 * 0.3));
+    double W[3], X[3];
+#pragma unroll
+    for (int i = 0; i < 3; i++) {
+        const T x = (T)(c + i - 1) - p;
+        X[i] = (double)x;
+        W[i] = (double)(T)exp(-(x * x) * inv2);
+    }
+    const double S0 = W[0] + W[1] + W[2];
+    const double V0 = W[0] * X[0], V1 = W[1] * X[1], V2 = W[2] * X[2];
+    const double S1 = V0 + V1 + V2;
+    const double S2 = V0 * X[0] + V1 * X[1] + V2 * X[2];
+    const double D = S0 * S2 - S1 * S1;
+    const double r = 1.0 / (S0 * D), i0 = r * D, iD = r * S0;
+    AxisFit f;
+#pragma unroll
+    for (int i = 0; i < 3; i++) {
+        const double w = W[i] * iD;
+        f.a[i] = W[i] * i0;
+        f.b[i] = w * (S2 - S1 * X[i]);
+        f.s[i] = w * (S0 * X[i] - S1);
+    }
+    return f;
+}
+
 // Moments of the capsule's fluid patch, staged in LDS: density deviation
 // rho - 1 and the force-corrected velocity.  Cells on a wall row hold NaN
 // and raise ST_WALL if a support touches them.
@@ -407,8 +446,7 @@ __device__ __forceinline__ void stage_cells(const IBArgs<T>& a, const GridArgs& 
             add_pull_offsets(g, row[k], s[k]);
             stage_store(P, i, s[k], fx[k], fy[k], gxf, uref_at<T>(g, row[k]));
         } else if (state[k] == 1) {
-            P.drho[i] = T(NAN);
-            P.ux[i] = P.uy[i] = T(0);
+            P.drho[i] = P.ux[i] = P.uy[i] = T(NAN);
         }
     }
 }

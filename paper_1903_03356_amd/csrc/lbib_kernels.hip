@@ -597,50 +597,68 @@ __device__ __forceinline__ void comp_add(T& hi, T& lo, T d)
 // MLS shape functions of Eq. 9 at p = (px, py), given relative to an integer
 // origin.  Support: the 3x3 nodes around floor(p + 1/2).  Weight
 // exp(-(|x_k - p| / (r_w alpha))^2) with r_w = 2.6, alpha = 0.3.  Linear basis
-// centred on p.  The 3x3 moment matrix is accumulated and inverted (cofactors)
-// in FP64.  Outputs: centre (cx, cy), phi (value) and, if G, the slope rows
-// (dphi/dx, dphi/dy) of the local fit.
+// centred on p.  The weight is a product w(x) w(y) on a 3 x 3 product support,
+// so the weighted x and y offsets are uncorrelated and the 3x3 moment system
+// of the fit splits into one straight-line fit per axis (AxisFit); the rows
+// are products of the axes' values:
+//   phi = b_x a_y + a_x (b_y - a_y),  dphi/dx = s_x a_y,  dphi/dy = a_x s_y.
+// Six exponentials and two divisions where the inverse of the 3x3 system took
+// nine and one, and about a third of its FP64 operations; the IB launch is
+// bound by this chain (one or two waves per SIMD), so it shortens with it.
+// Outputs: centre (cx, cy), phi (value) and, if G, the slope rows of the local
+// fit.
 template <typename T, bool G>
 __device__ __forceinline__ void mls(T px, T py, int& cx, int& cy, T* phi, T* gx, T* gy)
 {
     cx = (int)floor(px + T(0.5));
     cy = (int)floor(py + T(0.5));
-    const T inv2 = T(1.0 / (2.6 * 0.3 * 2.6 * 0.3));
-    T w[9], rx[9], ry[9];
-    double a00 = 0, a01 = 0, a02 = 0, a11 = 0, a12 = 0, a22 = 0;
+    const AxisFit X = axis_fit(px, cx), Y = axis_fit(py, cy);
 #pragma unroll
     for (int k = 0; k < 9; k++) {
-        rx[k] = (T)(cx + k % 3 - 1) - px;
-        ry[k] = (T)(cy + k / 3 - 1) - py;
-        w[k] = exp(-(rx[k] * rx[k] + ry[k] * ry[k]) * inv2);
-        const double W = w[k], X = rx[k], Y = ry[k];
-        a00 += W;
-        a01 += W * X;
-        a02 += W * Y;
-        a11 += W * X * X;
-        a12 += W * X * Y;
-        a22 += W * Y * Y;
-    }
-    const double c00 = a11 * a22 - a12 * a12;
-    const double c01 = a02 * a12 - a01 * a22;
-    const double c02 = a01 * a12 - a02 * a11;
-    const double det = a00 * c00 + a01 * c01 + a02 * c02;
-    const double id = 1.0 / det;
-    const double i00 = c00 * id, i01 = c01 * id, i02 = c02 * id;
-    double i11 = 0, i12 = 0, i22 = 0;
-    if (G) {
-        i11 = (a00 * a22 - a02 * a02) * id;
-        i12 = (a01 * a02 - a00 * a12) * id;
-        i22 = (a00 * a11 - a01 * a01) * id;
-    }
-#pragma unroll
-    for (int k = 0; k < 9; k++) {
-        const double W = w[k], X = rx[k], Y = ry[k];
-        phi[k] = (T)(W * (i00 + i01 * X + i02 * Y));
+        const int i = k % 3, j = k / 3;
+        phi[k] = (T)(X.b[i] * Y.a[j] + X.a[i] * (Y.b[j] - Y.a[j]));
         if (G) {
-            gx[k] = (T)(W * (i01 + i11 * X + i12 * Y));
-            gy[k] = (T)(W * (i02 + i12 * X + i22 * Y));
+            gx[k] = (T)(X.s[i] * Y.a[j]);
+            gy[k] = (T)(X.a[i] * Y.s[j]);
         }
+    }
+}
+
+// Patch index of the first support node if the whole 3x3 support lies in the
+// staged box, else -1.
+template <typename T>
+__device__ __forceinline__ int support_index(const Patch<T>& P, int cx, int cy)
+{
+    const int lx = cx - 1 - P.ox, ly = cy - 1 - P.oy;
+    return lx >= 0 && lx + 2 < P.W && ly >= 0 && ly + 2 < P.H ? ly * P.W + lx : -1;
+}
+
+// Eq. 8 sum of the velocity over the support with the weights phi.  A support
+// inside the box is summed without a test per cell: a cell off the lattice
+// holds NaN, so its sum is NaN, and only then (or beside the box) the cells are
+// taken one by one, leaving out and flagging those that cannot be used.
+template <typename T>
+__device__ __forceinline__ void interp_sum(const Patch<T>& P, int cx, int cy, const T* phi, T& Ux,
+                                           T& Uy, int& st)
+{
+    Ux = Uy = T(0);
+    const int i0 = support_index(P, cx, cy);
+    if (i0 >= 0) {
+#pragma unroll
+        for (int k = 0; k < 9; k++) {
+            const int idx = i0 + (k / 3) * P.W + k % 3;
+            Ux += phi[k] * P.ux[idx];
+            Uy += phi[k] * P.uy[idx];
+        }
+        if (!isnan(Ux + Uy)) return;
+    }
+    Ux = Uy = T(0);
+    for (int k = 0; k < 9; k++) {
+        int idx;
+        if (!patch_index(P, cx, cy, k, idx)) { st |= ST_PATCH; continue; }
+        if (isnan(P.drho[idx])) { st |= ST_WALL; continue; }
+        Ux += phi[k] * P.ux[idx];
+        Uy += phi[k] * P.uy[idx];
     }
 }
 
@@ -651,19 +669,12 @@ __device__ __forceinline__ void interp_u(const Patch<T>& P, T px, T py, T& Ux, T
     int cx, cy;
     T phi[9];
     mls<T, false>(px, py, cx, cy, phi, nullptr, nullptr);
-    Ux = Uy = T(0);
-#pragma unroll
-    for (int k = 0; k < 9; k++) {
-        int idx;
-        if (!patch_index(P, cx, cy, k, idx)) { st |= ST_PATCH; continue; }
-        if (isnan(P.drho[idx])) { st |= ST_WALL; continue; }
-        Ux += phi[k] * P.ux[idx];
-        Uy += phi[k] * P.uy[idx];
-    }
+    interp_sum(P, cx, cy, phi, Ux, Uy, st);
 }
 
 // Probe state for Eqs. 15-16: pressure deviation c_s^2 (rho - 1) and the
 // velocity gradient G[a][b] = d u_a / d x_b from the slope rows of the fit.
+// Cells are tested as in interp_sum.
 template <typename T>
 __device__ __forceinline__ void probe(const Patch<T>& P, T px, T py, T& dp, T (&Gr)[2][2], int& st)
 {
@@ -671,18 +682,28 @@ __device__ __forceinline__ void probe(const Patch<T>& P, T px, T py, T& dp, T (&
     T phi[9], gx[9], gy[9];
     mls<T, true>(px, py, cx, cy, phi, gx, gy);
     T r = 0, g00 = 0, g01 = 0, g10 = 0, g11 = 0;
-#pragma unroll
-    for (int k = 0; k < 9; k++) {
-        int idx;
-        if (!patch_index(P, cx, cy, k, idx)) { st |= ST_PATCH; continue; }
-        const T d = P.drho[idx];
-        if (isnan(d)) { st |= ST_WALL; continue; }
+    auto add = [&](int k, int idx) {
         const T u = P.ux[idx], v = P.uy[idx];
-        r += phi[k] * d;
+        r += phi[k] * P.drho[idx];
         g00 += gx[k] * u;
         g01 += gy[k] * u;
         g10 += gx[k] * v;
         g11 += gy[k] * v;
+    };
+    const int i0 = support_index(P, cx, cy);
+    if (i0 >= 0) {
+#pragma unroll
+        for (int k = 0; k < 9; k++) add(k, i0 + (k / 3) * P.W + k % 3);
+    }
+    if (i0 < 0 || isnan(r)) {
+        r = g00 = g01 = g10 = g11 = T(0);
+#pragma unroll
+        for (int k = 0; k < 9; k++) {
+            int idx;
+            if (!patch_index(P, cx, cy, k, idx)) { st |= ST_PATCH; continue; }
+            if (isnan(P.drho[idx])) { st |= ST_WALL; continue; }
+            add(k, idx);
+        }
     }
     dp = r * T(1.0 / 3.0);
     Gr[0][0] = g00;
@@ -1612,15 +1633,8 @@ __device__ __forceinline__ void ib_block(const IBArgs<T>& a0, unsigned char* sme
                 int cx, cy;
                 T phi[9];
                 mls<T, false>(S.px[v], S.py[v], cx, cy, phi, nullptr, nullptr);
-                T Ux = T(0), Uy = T(0);  // Eq. 8
-#pragma unroll
-                for (int k = 0; k < 9; k++) {
-                    int idx;
-                    if (!patch_index(P, cx, cy, k, idx)) { st |= ST_PATCH; continue; }
-                    if (isnan(P.drho[idx])) { st |= ST_WALL; continue; }
-                    Ux += phi[k] * P.ux[idx];
-                    Uy += phi[k] * P.uy[idx];
-                }
+                T Ux, Uy;  // Eq. 8
+                interp_sum(P, cx, cy, phi, Ux, Uy, st);
                 const T Fx = S.ux[v] - Ux;  // (U_b - U) / dt, step 1
                 const T Fy = S.uy[v] - Uy;
                 T ax, ay, bx, by;
