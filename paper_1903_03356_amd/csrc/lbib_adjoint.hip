@@ -121,72 +121,87 @@ __device__ __forceinline__ Dual<N> dsqrt(const Dual<N>& a)
 }
 
 // ----------------------------------------------------------- MLS with slopes
+// One axis of the fit (AxisFit of lbib_device.h) at p in FP64 with the
+// derivatives of its values with respect to p (dX/dp = -1, dw/dp = 2 X w /
+// (r_w alpha)^2).
+struct AxisFitD {
+    double a[3], b[3], s[3];
+    double da[3], db[3], ds[3];
+};
+
+__device__ __forceinline__ AxisFitD axis_fit_d(double p, int c)
+{
+    const double inv2 = 1.0 / (2.6 * 0.3 * 2.6 * 0.3);
+    double X[3], W[3], dW[3];
+    double S0 = 0, S1 = 0, S2 = 0, dS0 = 0, dS1 = 0, dS2 = 0;
+#pragma unroll
+    for (int i = 0; i < 3; i++) {
+        X[i] = (double)(c + i - 1) - p;
+        W[i] = exp(-(X[i] * X[i]) * inv2);
+        dW[i] = 2.0 * inv2 * X[i] * W[i];
+        S0 += W[i];
+        S1 += W[i] * X[i];
+        S2 += W[i] * X[i] * X[i];
+        dS0 += dW[i];
+        dS1 += dW[i] * X[i] - W[i];
+        dS2 += X[i] * (dW[i] * X[i] - 2.0 * W[i]);
+    }
+    const double D = S0 * S2 - S1 * S1;
+    const double dD = dS0 * S2 + S0 * dS2 - 2.0 * S1 * dS1;
+    const double r = 1.0 / (S0 * D), i0 = r * D, iD = r * S0;
+    AxisFitD f;
+#pragma unroll
+    for (int i = 0; i < 3; i++) {
+        const double tb = S2 - S1 * X[i], ts = S0 * X[i] - S1;
+        f.a[i] = W[i] * i0;
+        f.b[i] = W[i] * tb * iD;
+        f.s[i] = W[i] * ts * iD;
+        f.da[i] = (dW[i] - f.a[i] * dS0) * i0;
+        f.db[i] = (dW[i] * tb + W[i] * (dS2 - dS1 * X[i] + S1) - f.b[i] * dD) * iD;
+        f.ds[i] = (dW[i] * ts + W[i] * (dS0 * X[i] - S0 - dS1) - f.s[i] * dD) * iD;
+    }
+    return f;
+}
+
 // Shape functions of Eq. 9 at p = (px, py) (FP64, patch frame) on the 3x3
 // support centred at (cx, cy), together with their partial derivatives with
-// respect to p.  Weight, basis and moment matrix follow the forward kernel
-// (marker-centred linear basis, W = exp(-(r / (2.6 * 0.3))^2)).  For every
-// support node k, f(k, phi, gx, gy) receives the value row and, if G, the two
-// slope rows (diffuse derivatives), each as a dual over (px, py).
-template <bool G, typename F>
-__device__ __forceinline__ void mls_dual(double px, double py, int cx, int cy, F&& f)
+// respect to p: products of the two axes' fits, as in the forward kernel.  For
+// every support node k, mls_rows calls f(k, phi, gx, gy) with the value row
+// and, if G, the two slope rows (diffuse derivatives), each as a dual over (px, py).
+// (As duals through the inverse of the 3x3 system, this took nine exponentials
+// twice and filled the register file; k_ib_adj at 512x128 went from 39.7 to
+// 29.8 us (Dynamic) and from 22.6 to 20.9 us (Kinematic) per launch.)
+struct MlsFitD {
+    AxisFitD x, y;
+};
+
+__device__ __forceinline__ MlsFitD mls_fit_d(double px, double py, int cx, int cy)
 {
-    using D = Dual<2>;
-    const double inv2 = 1.0 / (2.6 * 0.3 * 2.6 * 0.3);
-    D a00 = dconst<2>(0), a01 = a00, a02 = a00, a11 = a00, a12 = a00, a22 = a00;
+    MlsFitD m;
+    m.x = axis_fit_d(px, cx);
+    m.y = axis_fit_d(py, cy);
+    return m;
+}
+
+template <bool G, typename F>
+__device__ __forceinline__ void mls_rows(const MlsFitD& m, F&& f)
+{
 #pragma unroll
     for (int k = 0; k < 9; k++) {
-        const double X = (double)(cx + k % 3 - 1) - px, Y = (double)(cy + k / 3 - 1) - py;
-        const double e = exp(-(X * X + Y * Y) * inv2);
-        D w;
-        w.v = e;
-        w.d[0] = 2.0 * X * inv2 * e;  // dX/dpx = -1
-        w.d[1] = 2.0 * Y * inv2 * e;
-        D Xd, Yd;
-        Xd.v = X;
-        Xd.d[0] = -1.0;
-        Xd.d[1] = 0.0;
-        Yd.v = Y;
-        Yd.d[0] = 0.0;
-        Yd.d[1] = -1.0;
-        const D wX = w * Xd, wY = w * Yd;
-        a00 = a00 + w;
-        a01 = a01 + wX;
-        a02 = a02 + wY;
-        a11 = a11 + wX * Xd;
-        a12 = a12 + wX * Yd;
-        a22 = a22 + wY * Yd;
-    }
-    const D c00 = a11 * a22 - a12 * a12;
-    const D c01 = a02 * a12 - a01 * a22;
-    const D c02 = a01 * a12 - a02 * a11;
-    const D id = dinv(a00 * c00 + a01 * c01 + a02 * c02);
-    const D i00 = c00 * id, i01 = c01 * id, i02 = c02 * id;
-    D i11 = dconst<2>(0), i12 = i11, i22 = i11;
-    if (G) {
-        i11 = (a00 * a22 - a02 * a02) * id;
-        i12 = (a01 * a02 - a00 * a12) * id;
-        i22 = (a00 * a11 - a01 * a01) * id;
-    }
-#pragma unroll
-    for (int k = 0; k < 9; k++) {
-        const double X = (double)(cx + k % 3 - 1) - px, Y = (double)(cy + k / 3 - 1) - py;
-        const double e = exp(-(X * X + Y * Y) * inv2);
-        D w;
-        w.v = e;
-        w.d[0] = 2.0 * X * inv2 * e;
-        w.d[1] = 2.0 * Y * inv2 * e;
-        D Xd, Yd;
-        Xd.v = X;
-        Xd.d[0] = -1.0;
-        Xd.d[1] = 0.0;
-        Yd.v = Y;
-        Yd.d[0] = 0.0;
-        Yd.d[1] = -1.0;
-        const D phi = w * (i00 + i01 * Xd + i02 * Yd);
-        D gx = dconst<2>(0), gy = gx;
+        const int i = k % 3, j = k / 3;
+        const double ax = m.x.a[i], bx = m.x.b[i], ay = m.y.a[j];
+        const double cy = m.y.b[j] - ay, dcy = m.y.db[j] - m.y.da[j];
+        Dual<2> phi, gx = dconst<2>(0), gy = gx;
+        phi.v = bx * ay + ax * cy;
+        phi.d[0] = m.x.db[i] * ay + m.x.da[i] * cy;
+        phi.d[1] = bx * m.y.da[j] + ax * dcy;
         if (G) {
-            gx = w * (i01 + i11 * Xd + i12 * Yd);
-            gy = w * (i02 + i12 * Xd + i22 * Yd);
+            gx.v = m.x.s[i] * ay;
+            gx.d[0] = m.x.ds[i] * ay;
+            gx.d[1] = m.x.s[i] * m.y.da[j];
+            gy.v = ax * m.y.s[j];
+            gy.d[0] = m.x.da[i] * m.y.s[j];
+            gy.d[1] = ax * m.y.ds[j];
         }
         f(k, phi, gx, gy);
     }
@@ -321,23 +336,29 @@ __global__ __launch_bounds__(kSegW * 4) void k_grid_adj(GridAdjArgs<T> a, GridAr
                 Fx += fix_to_real<T>(a.fib[2 * cell]);
                 Fy += fix_to_real<T>(a.fib[2 * cell + 1]);
             }
-            T s[9], lo[9], sb[9];
-            pull<T, false>(a.pops, x, y, g, Fx, s);  // the adjoint needs periodic x
+            T sT[9];
+            pull<T, false>(a.pops, x, y, g, Fx, sT);  // the adjoint needs periodic x
+            // in FP64 for both types: the rounding of an FP32 product acts alike on
+            // every cell of a smooth adjoint field and adds up over the steps, and the
+            // pass is bound by memory latency (6.3 us in FP32, 6.5 us so at 512x128)
+            double s[9], lo[9], sb[9];
+#pragma unroll
+            for (int i = 0; i < 9; i++) s[i] = sT[i];
 #pragma unroll
             for (int i = 0; i < 9; i++) lo[i] = a.lam_in[i * plane + cell];
-            T Fbx, Fby;
-            collide_vjp(s, Fx, Fy, uref_at<T>(g, y), (T)g.omega, lo, sb, Fbx, Fby);
+            double Fbx, Fby;
+            collide_vjp<double>(s, Fx, Fy, uref_at<T>(g, y), (T)g.omega, lo, sb, Fbx, Fby);
             const bool bot = !g.periodic_y && y == 0, top = !g.periodic_y && y == g.ny - 1;
-            if (bot) zou_he_vjp(sb, Fbx, (T)g.u_bot, false);
-            if (top) zou_he_vjp(sb, Fbx, (T)g.u_top, true);
+            if (bot) zou_he_vjp<double>(sb, Fbx, (T)g.u_bot, false);
+            if (top) zou_he_vjp<double>(sb, Fbx, (T)g.u_top, true);
             if (mflag) {
                 Fbx += a.lfm[2 * cell];
                 Fby += a.lfm[2 * cell + 1];
             }
-            gsum = (double)Fbx;
+            gsum = Fbx;
             if (act) {
-                a.lft[2 * cell] = Fbx;
-                a.lft[2 * cell + 1] = Fby;
+                a.lft[2 * cell] = (T)Fbx;
+                a.lft[2 * cell + 1] = (T)Fby;
             }
             const int xm = x == 0 ? g.nx - 1 : x - 1;
             const int xp = x == g.nx - 1 ? 0 : x + 1;
@@ -347,7 +368,7 @@ __global__ __launch_bounds__(kSegW * 4) void k_grid_adj(GridAdjArgs<T> a, GridAr
                 int ys = y - kEy[i];
                 if (g.periodic_y) ys = ys < 0 ? g.ny - 1 : (ys >= g.ny ? 0 : ys);
                 else if (ys < 0 || ys >= g.ny) continue;
-                a.lam_out[i * plane + (size_t)ys * g.nxp + xs] = sb[i];
+                a.lam_out[i * plane + (size_t)ys * g.nxp + xs] = (T)sb[i];
             }
             // slots that no node pulls from (they point out of the walls)
             if (bot) {
@@ -516,7 +537,9 @@ __global__ __launch_bounds__(kIBThreads) void k_adj_seed(const T* nodes, const d
 template <typename T>
 struct AdjScratch {
     T *pd, *pu, *pv;  // staged rho - 1, ux, uy
-    T *Ld, *Lu, *Lv;  // their adjoints
+    T *Ld, *Lu, *Lv;           // their adjoints, or
+    double *Wd, *Wu, *Wv;      // the same in FP64 where the patch leaves room (wide)
+    bool wide;
     T *hxn, *hyn;     // x^n high parts (frame n)
     T *hxp, *hyp, *lxp, *lyp;  // x^{n-1} high and low parts (frame n-1)
     double *Xn, *Yn, *Xp, *Yp;  // positions in the patch frame (FP64)
@@ -554,6 +577,39 @@ __device__ __forceinline__ int adj_patch_index(const Patch<T>& P, int cx, int cy
     return isnan(P.drho[idx]) ? -1 : idx;
 }
 
+// Adds to the patch adjoints of cell idx.  An FP32 patch of at most half the
+// capacity sums in FP64 (in the space of the FP32 arrays): a cell's sum then
+// does not depend on the order of the atomics beyond 1e-16, so the gradient
+// repeats, and its error is that of the grid's adjoint alone (dJ/dg of 200
+// Dynamic steps at 512x128, five seeds: 1.6e-7 to 2.4e-6 of its value with FP32
+// sums and an FP32 reverse grid step, 2e-9 to 1.6e-7 with both in FP64).
+template <typename T>
+__device__ __forceinline__ void add_adj_u(const AdjScratch<T>& S, int idx, double lu, double lv)
+{
+    if (sizeof(T) == 4 && S.wide) {
+        atomicAdd(&S.Wu[idx], lu);
+        atomicAdd(&S.Wv[idx], lv);
+    } else {
+        atomicAdd(&S.Lu[idx], (T)lu);
+        atomicAdd(&S.Lv[idx], (T)lv);
+    }
+}
+
+template <typename T>
+__device__ __forceinline__ void add_adj(const AdjScratch<T>& S, int idx, double ld, double lu,
+                                        double lv)
+{
+    if (sizeof(T) == 4 && S.wide) {
+        atomicAdd(&S.Wd[idx], ld);
+        atomicAdd(&S.Wu[idx], lu);
+        atomicAdd(&S.Wv[idx], lv);
+    } else {
+        atomicAdd(&S.Ld[idx], (T)ld);
+        atomicAdd(&S.Lu[idx], (T)lu);
+        atomicAdd(&S.Lv[idx], (T)lv);
+    }
+}
+
 // Transpose of the interpolation v = sum_k phi_k(p) u_k (Eq. 8) for a given
 // adjoint lv of v: adds phi_k lv to the velocity adjoints of the support and
 // returns d(lv . v)/dp.
@@ -563,15 +619,15 @@ __device__ __forceinline__ void interp_vjp(const AdjScratch<T>& S, const Patch<T
                                            double& gpx, double& gpy, int& st)
 {
     gpx = gpy = 0.0;
-    mls_dual<false>(px, py, cx, cy, [&](int k, const Dual<2>& phi, const Dual<2>&, const Dual<2>&) {
+    const MlsFitD fit = mls_fit_d(px, py, cx, cy);
+    mls_rows<false>(fit, [&](int k, const Dual<2>& phi, const Dual<2>&, const Dual<2>&) {
         const int idx = adj_patch_index(P, cx, cy, k);
         if (idx < 0) { st |= ST_PATCH; return; }
         const double u = (double)S.pu[idx], v = (double)S.pv[idx];
         const double c = u * lvx + v * lvy;
         gpx += c * phi.d[0];
         gpy += c * phi.d[1];
-        atomicAdd(&S.Lu[idx], (T)(phi.v * lvx));
-        atomicAdd(&S.Lv[idx], (T)(phi.v * lvy));
+        add_adj_u(S, idx, phi.v * lvx, phi.v * lvy);
     });
 }
 
@@ -774,17 +830,17 @@ __device__ void external_vjp(const AdjScratch<T>& S, const Patch<T>& P, int nv, 
         const double px = xc + sg * nx, py = yc + sg * ny;
         // forward value of this lane's probe
         double r = 0, g00 = 0, g01 = 0, g10 = 0, g11 = 0;
-        mls_dual<true>(px, py, cx, cy,
-                       [&](int k, const Dual<2>& phi, const Dual<2>& gx, const Dual<2>& gy) {
-                           const int idx = adj_patch_index(P, cx, cy, k);
-                           if (idx < 0) { st |= ST_PATCH; return; }
-                           const double u = S.pu[idx], v = S.pv[idx];
-                           r += phi.v * (double)S.pd[idx];
-                           g00 += gx.v * u;
-                           g01 += gy.v * u;
-                           g10 += gx.v * v;
-                           g11 += gy.v * v;
-                       });
+        const MlsFitD fit = mls_fit_d(px, py, cx, cy);
+        mls_rows<true>(fit, [&](int k, const Dual<2>& phi, const Dual<2>& gx, const Dual<2>& gy) {
+            const int idx = adj_patch_index(P, cx, cy, k);
+            if (idx < 0) { st |= ST_PATCH; return; }
+            const double u = S.pu[idx], v = S.pv[idx];
+            r += phi.v * (double)S.pd[idx];
+            g00 += gx.v * u;
+            g01 += gy.v * u;
+            g10 += gx.v * v;
+            g11 += gy.v * v;
+        });
         // both probes of the element: side 0 (outer) and side 1 (inner)
         const double own[5] = {r / 3.0, g00, g01, g10, g11};
         double pr[2][5];
@@ -810,20 +866,17 @@ __device__ void external_vjp(const AdjScratch<T>& S, const Patch<T>& P, int nv, 
         const double lP = sgn * ldpr / 3.0;  // lambda of sum phi rho (p = rho / 3)
         const double l00 = 2.0 * sgn * ld00, l11 = 2.0 * sgn * ld11, l01 = sgn * ld01;
         double gpx = 0.0, gpy = 0.0;
-        mls_dual<true>(px, py, cx, cy,
-                       [&](int k, const Dual<2>& phi, const Dual<2>& gx, const Dual<2>& gy) {
-                           const int idx = adj_patch_index(P, cx, cy, k);
-                           if (idx < 0) return;
-                           const double d = S.pd[idx], u = S.pu[idx], v = S.pv[idx];
-                           // G00 = sum gx u, G01 = sum gy u, G10 = sum gx v, G11 = sum gy v
-                           const double cgx = l00 * u + l01 * v;
-                           const double cgy = l01 * u + l11 * v;
-                           gpx += lP * d * phi.d[0] + cgx * gx.d[0] + cgy * gy.d[0];
-                           gpy += lP * d * phi.d[1] + cgx * gx.d[1] + cgy * gy.d[1];
-                           atomicAdd(&S.Ld[idx], (T)(lP * phi.v));
-                           atomicAdd(&S.Lu[idx], (T)(l00 * gx.v + l01 * gy.v));
-                           atomicAdd(&S.Lv[idx], (T)(l01 * gx.v + l11 * gy.v));
-                       });
+        mls_rows<true>(fit, [&](int k, const Dual<2>& phi, const Dual<2>& gx, const Dual<2>& gy) {
+            const int idx = adj_patch_index(P, cx, cy, k);
+            if (idx < 0) return;
+            const double d = S.pd[idx], u = S.pu[idx], v = S.pv[idx];
+            // G00 = sum gx u, G01 = sum gy u, G10 = sum gx v, G11 = sum gy v
+            const double cgx = l00 * u + l01 * v;
+            const double cgy = l01 * u + l11 * v;
+            gpx += lP * d * phi.d[0] + cgx * gx.d[0] + cgy * gy.d[0];
+            gpy += lP * d * phi.d[1] + cgx * gx.d[1] + cgy * gy.d[1];
+            add_adj(S, idx, lP * phi.v, l00 * gx.v + l01 * gy.v, l01 * gx.v + l11 * gy.v);
+        });
         // sums over the two probes (side 0 first)
         const double ox = __shfl_xor(gpx, 1), oy = __shfl_xor(gpy, 1);
         if (side) continue;
@@ -888,6 +941,10 @@ __global__ __launch_bounds__(kAdjThreads) void k_ib_adj(IBAdjArgs<T> a)
         const int pc = a.patch_cap, M = a.max_nv;
         S.pd = p; S.pu = p + pc; S.pv = p + 2 * pc;
         S.Ld = p + 3 * pc; S.Lu = p + 4 * pc; S.Lv = p + 5 * pc;
+        const size_t w = (3 * sizeof(T) * (size_t)pc + 7) & ~(size_t)7;
+        S.Wd = reinterpret_cast<double*>(smem + w);
+        S.Wu = S.Wd + pc / 2;
+        S.Wv = S.Wu + pc / 2;
         T* q = p + 6 * pc;
         S.hxn = q; S.hyn = q + M; S.hxp = q + 2 * M; S.hyp = q + 3 * M;
         S.lxp = q + 4 * M; S.lyp = q + 5 * M;
@@ -969,7 +1026,11 @@ __global__ __launch_bounds__(kAdjThreads) void k_ib_adj(IBAdjArgs<T> a)
         const int ncell = P.W * P.H;
         // four cells per thread with all their loads in flight together
         for (int i = tid; i < ncell; i += 4 * nt) stage_cells<T, 4>(ia, g, P, refx, refy, gxf, i, nt);
-        for (int i = tid; i < ncell; i += nt) S.Ld[i] = S.Lu[i] = S.Lv[i] = T(0);
+        S.wide = sizeof(T) == 4 && ncell <= a.patch_cap / 2;
+        for (int i = tid; i < ncell; i += nt) {
+            if (S.wide) S.Wd[i] = S.Wu[i] = S.Wv[i] = 0.0;
+            else S.Ld[i] = S.Lu[i] = S.Lv[i] = T(0);
+        }
     }
     __syncthreads();
     int st = 0;
@@ -984,17 +1045,17 @@ __global__ __launch_bounds__(kAdjThreads) void k_ib_adj(IBAdjArgs<T> a)
                 double ph[9], phx[9], phy[9];
                 int id9[9];
                 double Ux = 0, Uy = 0;
-                mls_dual<false>(S.Xn[v], S.Yn[v], cx, cy,
-                                [&](int k, const Dual<2>& phi, const Dual<2>&, const Dual<2>&) {
-                                    ph[k] = phi.v;
-                                    phx[k] = phi.d[0];
-                                    phy[k] = phi.d[1];
-                                    id9[k] = adj_patch_index(P, cx, cy, k);
-                                    if (id9[k] >= 0) {
-                                        Ux += phi.v * (double)S.pu[id9[k]];
-                                        Uy += phi.v * (double)S.pv[id9[k]];
-                                    }
-                                });
+                const MlsFitD fit = mls_fit_d(S.Xn[v], S.Yn[v], cx, cy);
+                mls_rows<false>(fit, [&](int k, const Dual<2>& phi, const Dual<2>&, const Dual<2>&) {
+                    ph[k] = phi.v;
+                    phx[k] = phi.d[0];
+                    phy[k] = phi.d[1];
+                    id9[k] = adj_patch_index(P, cx, cy, k);
+                    if (id9[k] >= 0) {
+                        Ux += phi.v * (double)S.pu[id9[k]];
+                        Uy += phi.v * (double)S.pv[id9[k]];
+                    }
+                });
                 const double Fx = S.uvx[v] - Ux, Fy = S.uvy[v] - Uy;
                 const double ax = S.Xn[v] - S.Xn[vl], ay = S.Yn[v] - S.Yn[vl];
                 const double bx = S.Xn[vr] - S.Xn[v], by = S.Yn[vr] - S.Yn[v];
@@ -1029,8 +1090,7 @@ __global__ __launch_bounds__(kAdjThreads) void k_ib_adj(IBAdjArgs<T> a)
                     gpx += lph * phx[k];
                     gpy += lph * phy[k];
                     if (idx >= 0) {
-                        atomicAdd(&S.Lu[idx], (T)(-ph[k] * lFvx));
-                        atomicAdd(&S.Lv[idx], (T)(-ph[k] * lFvy));
+                        add_adj_u(S, idx, -ph[k] * lFvx, -ph[k] * lFvy);
                     } else {
                         st |= ST_PATCH;
                     }
@@ -1061,26 +1121,26 @@ __global__ __launch_bounds__(kAdjThreads) void k_ib_adj(IBAdjArgs<T> a)
                 const int cx = (int)floor(S.hxn[v] + T(0.5)), cy = (int)floor(S.hyn[v] + T(0.5));
                 double lFvx = 0, lFvy = 0, gpx = 0, gpy = 0;
                 const double Fx = S.Fvx[v], Fy = S.Fvy[v];
-                mls_dual<false>(S.Xn[v], S.Yn[v], cx, cy,
-                                [&](int k, const Dual<2>& phi, const Dual<2>&, const Dual<2>&) {
-                                    int gy;
-                                    if (g.periodic_y) {
-                                        gy = wrap_add(wry, cy + k / 3 - 1, g.ny);
-                                    } else {
-                                        const long long yv = refy + cy + k / 3 - 1;
-                                        if (yv < 1 || yv > g.ny - 2) return;
-                                        gy = (int)yv;
-                                    }
-                                    const int gxx = wrap_add(wrx, cx + k % 3 - 1, g.nx);
-                                    const size_t cell = (size_t)gy * g.nxp + (size_t)gxx;
-                                    const double lx_ = (double)lft[2 * cell];
-                                    const double ly_ = (double)lft[2 * cell + 1];
-                                    lFvx += phi.v * lx_;
-                                    lFvy += phi.v * ly_;
-                                    const double lph = Fx * lx_ + Fy * ly_;
-                                    gpx += lph * phi.d[0];
-                                    gpy += lph * phi.d[1];
-                                });
+                const MlsFitD fit = mls_fit_d(S.Xn[v], S.Yn[v], cx, cy);
+                mls_rows<false>(fit, [&](int k, const Dual<2>& phi, const Dual<2>&, const Dual<2>&) {
+                    int gy;
+                    if (g.periodic_y) {
+                        gy = wrap_add(wry, cy + k / 3 - 1, g.ny);
+                    } else {
+                        const long long yv = refy + cy + k / 3 - 1;
+                        if (yv < 1 || yv > g.ny - 2) return;
+                        gy = (int)yv;
+                    }
+                    const int gxx = wrap_add(wrx, cx + k % 3 - 1, g.nx);
+                    const size_t cell = (size_t)gy * g.nxp + (size_t)gxx;
+                    const double lx_ = (double)lft[2 * cell];
+                    const double ly_ = (double)lft[2 * cell + 1];
+                    lFvx += phi.v * lx_;
+                    lFvy += phi.v * ly_;
+                    const double lph = Fx * lx_ + Fy * ly_;
+                    gpx += lph * phi.d[0];
+                    gpy += lph * phi.d[1];
+                });
                 S.lx[v] += gpx;
                 S.ly[v] += gpy;
                 S.lFx[v] = lFvx;
@@ -1178,7 +1238,9 @@ __global__ __launch_bounds__(kAdjThreads) void k_ib_adj(IBAdjArgs<T> a)
         const int pbx = wrap_ref(refx + P.ox, g.nx);
         const int pby = g.periodic_y ? wrap_ref(refy + P.oy, g.ny) : 0;
         for (int i = tid; i < ncell; i += nt) {
-            const T Ld = S.Ld[i], Lu = S.Lu[i], Lv = S.Lv[i];
+            const T Ld = S.wide ? (T)S.Wd[i] : S.Ld[i];
+            const T Lu = S.wide ? (T)S.Wu[i] : S.Lu[i];
+            const T Lv = S.wide ? (T)S.Wv[i] : S.Lv[i];
             if (Ld == T(0) && Lu == T(0) && Lv == T(0)) continue;
             if (isnan(S.pd[i])) continue;
             const int lxi = i % P.W, lyi = i / P.W;
