@@ -28,8 +28,15 @@ NO_PACKED_FP32 = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 PACKED_FP32_OPCODE = re.compile(r"\bv_pk_(?:add|mul|fma)_f32\b")
 
 
+# Multiply-adds are fused within one source expression only, so that every
+# kernel that runs a shared device function computes the same bits (with the
+# default, fast, the compiler also fuses across statements, as each kernel's
+# registers and uses happen to fall).
+FP_CONTRACT = ["-ffp-contract=on"]
+
+
 def common_flags() -> list:
-    return [f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC"] + NO_PACKED_FP32 + [
+    return [f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC"] + FP_CONTRACT + NO_PACKED_FP32 + [
         "-Wall", "-Wno-unused-result", "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
 

@@ -48,32 +48,12 @@ template <typename T, bool NT = true>
 __device__ __forceinline__ void collide_pulled(const T (&s)[9], T* __restrict__ dst,
                                                const GridArgs& g, int x, int y, T Fx, T Fy)
 {
-    const size_t cell = (size_t)y * g.nxp + x;
-    const T drho = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7])) + s[8];
-    const T rho = T(1) + drho;
-    const T jx = (s[1] - s[3]) + (s[5] - s[6]) + (s[8] - s[7]);
-    const T jy = (s[2] - s[4]) + (s[5] + s[6]) - (s[7] + s[8]);
-    const T irho = T(1) / rho;
-    // rho u (Eq. 7): mx = rho u_x - u_ref(y) is the momentum the stored values carry
-    const T mx = jx + T(0.5) * Fx, my = jy + T(0.5) * Fy;
-    const T ux = (uref_at<T>(g, y) + mx) * irho, uy = my * irho;
-    const T om = (T)g.omega;
-    const T pre = T(1) - T(0.5) * om;
-    const T usq15 = T(1.5) * (ux * ux + uy * uy);
-    const T uF = ux * Fx + uy * Fy;
-    const T wa = T(1.0 / 9.0), wd = T(1.0 / 36.0);
-    const T w3a = FirstOrderW<T>::axis, w3d = FirstOrderW<T>::diag;
+    T o[9];
+    collide(s, uref_at<T>(g, y), (T)g.omega, Fx, Fy, o);
     const size_t plane = (size_t)g.ny * g.nxp;
-    T* o = dst + cell;
-    put_pop<T, NT>(&o[0], relax(s[0], T(4.0 / 9.0), T(0), T(0), T(0), T(0), drho, rho, usq15, uF, om, pre));
-    put_pop<T, NT>(&o[plane], relax(s[1], wa, w3a, ux, mx, Fx, drho, rho, usq15, uF, om, pre));
-    put_pop<T, NT>(&o[2 * plane], relax(s[2], wa, w3a, uy, my, Fy, drho, rho, usq15, uF, om, pre));
-    put_pop<T, NT>(&o[3 * plane], relax(s[3], wa, w3a, -ux, -mx, -Fx, drho, rho, usq15, uF, om, pre));
-    put_pop<T, NT>(&o[4 * plane], relax(s[4], wa, w3a, -uy, -my, -Fy, drho, rho, usq15, uF, om, pre));
-    put_pop<T, NT>(&o[5 * plane], relax(s[5], wd, w3d, ux + uy, mx + my, Fx + Fy, drho, rho, usq15, uF, om, pre));
-    put_pop<T, NT>(&o[6 * plane], relax(s[6], wd, w3d, uy - ux, my - mx, Fy - Fx, drho, rho, usq15, uF, om, pre));
-    put_pop<T, NT>(&o[7 * plane], relax(s[7], wd, w3d, -ux - uy, -mx - my, -Fx - Fy, drho, rho, usq15, uF, om, pre));
-    put_pop<T, NT>(&o[8 * plane], relax(s[8], wd, w3d, ux - uy, mx - my, Fx - Fy, drho, rho, usq15, uF, om, pre));
+    T* out = dst + (size_t)y * g.nxp + x;
+#pragma unroll
+    for (int i = 0; i < 9; i++) put_pop<T, NT>(&out[i * plane], o[i]);
 }
 
 // One lattice node with the IB force of this step.  A wave holds one 64-cell
