@@ -102,6 +102,7 @@ struct lbib_ctx {
     int graph = -1;
     hipStream_t s_cap = nullptr;
     hipGraphExec_t gexec[2] = {nullptr, nullptr};
+    const void* g_pops = nullptr;
     int g_ncap = -1, g_mode = -1, g_patch = -1, g_tile = -1;
     double g_contact = -1.0;
     long long graph_replays = 0;
@@ -936,6 +937,16 @@ static hipError_t do_grid(lbib_ctx* c, void* p)
                                  c->stream);
 }
 
+// Steps n and n + 1 of a lattice without capsules, into the buffer of the other
+// parity (the caller swaps the two).
+template <typename T>
+static hipError_t do_grid_two(lbib_ctx* c, void* p)
+{
+    const long long n = *static_cast<const long long*>(p);
+    return launch_grid_two<T>(static_cast<const T*>(pops(c, n)), static_cast<T*>(pops(c, n + 1)),
+                              grid_args(c->L.inst[0]), c->num_cu, c->stream);
+}
+
 template <typename T>
 static lbib_status launch_contact_t(lbib_ctx* c)
 {
@@ -1138,6 +1149,13 @@ static lbib_status capture_steps(lbib_ctx* c, long long n0, bool contact, bool d
     return LBIB_OK;
 }
 
+// Whether the caller is recording the stream into a graph of its own.
+static bool capturing(hipStream_t st)
+{
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(st, &s) != hipSuccess || s != hipStreamCaptureStatusNone;
+}
+
 template <typename T>
 static lbib_status step_t(lbib_ctx* c, int nsteps)
 {
@@ -1160,17 +1178,31 @@ static lbib_status step_t(lbib_ctx* c, int nsteps)
     // replays of captured blocks for the inner steps; timed runs launch directly
     const bool graphs = c->graph == 1 && !c->timing;
     const int tile = c->tile_shape * 256 + c->tile_resident;
-    if (graphs && (c->g_ncap != c->ncap || c->g_mode != c->mode || c->g_patch != c->patch_use ||
+    if (graphs && (c->g_pops != c->buf[LBIB_BUF_POPS_A] || c->g_ncap != c->ncap || c->g_mode != c->mode || c->g_patch != c->patch_use ||
                    c->g_contact != c->contact_cutoff || c->g_tile != tile)) {
         drop_graphs(c);
+        c->g_pops = c->buf[LBIB_BUF_POPS_A];
         c->g_ncap = c->ncap;
         c->g_mode = c->mode;
         c->g_patch = c->patch_use;
         c->g_contact = c->contact_cutoff;
         c->g_tile = tile;
     }
+    // without capsules two steps go in one pass; the state then stands in the other
+    // population buffer, which takes the first one's place (graphs, the library's and
+    // the caller's, hold the buffers' addresses and keep single passes)
+    const bool two = c->ncap == 0 && c->graph != 1 && c->L.inst.size() == 1 &&
+                     grid_two_pays<T>(grid_args(c->L.inst[0])) && !capturing(c->stream);
     for (int k = 0; k < nsteps;) {
         const long long n = c->steps + k;
+        if (two && nsteps - k >= 2) {
+            long long nn = n;
+            lbib_status s = launch_timed<T>(c, 0, do_grid_two<T>, &nn);
+            if (s != LBIB_OK) return s;
+            std::swap(c->buf[LBIB_BUF_POPS_A], c->buf[LBIB_BUF_POPS_B]);
+            k += 2;
+            continue;
+        }
         if (graphs && k >= 1 && nsteps - k >= kGraphSteps) {
             hipGraphExec_t& ge = c->gexec[n & 1];
             if (!ge) {

@@ -9,6 +9,7 @@ namespace lbib {
 // Force field: one 64-cell row segment per wavefront of the grid kernel.
 constexpr int kSegW = 64;
 constexpr double kPlainStoreMaxBytes = 384.0 * (1 << 20);  // single pass: plain stores up to here
+constexpr double kTwoMinBytes = 16.0 * (1 << 20);  // two steps in one pass: populations from here
 constexpr int kGridRowsPerThread = 1;  // grid kernel: nodes per thread, 4 rows apart
 constexpr int kNumXcd = 8;       // MI355X: workgroups are dealt round-robin to 8 XCDs
 constexpr int kIBThreads = 512;  // IB kernel block (one block per capsule)
@@ -187,6 +188,11 @@ hipError_t launch_init(T* pops, const GridArgs& g, int profile, double ux0, doub
 template <typename T>
 hipError_t launch_grid_step(const T* src, T* dst, const long long* fib_now, const int* flags_now,
                             long long* fib_old, int* flags_old, const GridArgs& g, hipStream_t s);
+// Two steps of a lattice without IB force in one pass, where that pays.
+template <typename T>
+bool grid_two_pays(const GridArgs& g);
+template <typename T>
+hipError_t launch_grid_two(const T* src, T* dst, const GridArgs& g, int num_cu, hipStream_t s);
 template <typename T>
 hipError_t launch_grid_step_batch(const T* src, T* dst, const long long* fib_now,
                                   const int* flags_now, long long* fib_old, int* flags_old,

@@ -292,6 +292,253 @@ __global__ __launch_bounds__(kSegW * 4) void k_grid_step(
     }
 }
 
+// ---- two steps in one pass
+// Value of the lane before (x - 1) / behind (x + 1); lanes 0 / 63 get 0.
+template <int CTRL>
+__device__ __forceinline__ float lane_shift(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+
+template <int CTRL>
+__device__ __forceinline__ double lane_shift(double v)
+{
+    return dpp_move_f64<CTRL, 0xf>(v);
+}
+
+constexpr int kWaveShr1 = 0x138, kWaveShl1 = 0x130;
+constexpr int kTwoMaxThreads = 576;
+
+// Block barrier that orders LDS accesses only: global loads in flight stay in
+// flight across it.
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Raw buffer access: a scalar base and offset per row and plane, one 32-bit
+// offset per lane; an offset past the end reads 0 and stores nothing, so a lane
+// without a cell needs no branch (kNoCell).  Streaming loads and stores as
+// ld_stream, st_stream (aux 2: non-temporal).
+constexpr unsigned kNoCell = 0xffffffffu;
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, unsigned bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00027000);
+}
+
+template <int AUX, typename T>
+__device__ __forceinline__ void buf_load(__amdgpu_buffer_rsrc_t r, unsigned v, unsigned s, T& out)
+{
+    if constexpr (sizeof(T) == 4) {
+        out = __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, (int)v, (int)s, AUX));
+    } else {
+        out = __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, (int)v, (int)s, AUX));
+    }
+}
+
+template <int AUX, typename T>
+__device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t r, unsigned v, unsigned s, T x)
+{
+    if constexpr (sizeof(T) == 4) {
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, x), r, (int)v, (int)s, AUX);
+    } else {
+        typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, x), r, (int)v, (int)s, AUX);
+    }
+}
+
+// Two time steps of a lattice without an IB force (periodic in x) in one pass:
+// P^n is read and P^{n+2} written, 36 bytes a cell and step in FP32 where two
+// single passes move 72.  A block takes `cols` columns (a multiple of a cache
+// line, so that its stores fill whole lines: strips of 62 columns, two lanes
+// of each wave short, ran at half the speed) and one line of halo before
+// them and one lane behind, one column per lane, and walks `rows` rows up: it
+// collides row r of step n in registers, moves the populations that leave the
+// column to their neighbour (a lane shift; across waves through LDS, one
+// barrier per row), and with the rows r - 2 and r - 1 it holds from before it
+// collides row r - 1 of step n + 1 and stores it.  The rows two ahead are in
+// flight meanwhile (buffer loads and stores without a branch, so that the wait
+// for a row leaves the later loads and the stores outstanding).  Each node's
+// arithmetic is that of two single steps, bit for bit.  Bound by memory: 4096 x
+// 4096 FP32 205 -> 119 us per step (10.2 TB/s counted as 72 bytes a cell and step,
+// 5.2 TB/s moved, the rate of a plain copy); VALU about 45 % busy.
+template <typename T, bool NT>
+__global__ __launch_bounds__(kTwoMaxThreads) void k_grid_two(const T* __restrict__ src,
+                                                             T* __restrict__ dst, GridArgs g,
+                                                             unsigned bytes, int rows, int cols,
+                                                             int nblkx)
+{
+    constexpr int kHalo = 128 / (int)sizeof(T);
+    // populations that leave a wave through its first ([0]: 3, 6, 7) and last
+    // ([1]: 1, 5, 8) lane; a spare wave at either end
+    __shared__ T edge[2][kTwoMaxThreads / 64 + 2][2][3];
+    // each XCD takes a run of consecutive tiles, x fastest (4096^2: 119 us; the
+    // rows of tiles dealt to the XCDs in turn 124 us)
+    const int per = (int)gridDim.x / kNumXcd;
+    const int t = ((int)blockIdx.x % kNumXcd) * per + (int)blockIdx.x / kNumXcd;
+    const int chunk = t / nblkx, xblk = t - chunk * nblkx;
+    const int ya = chunk * rows;
+    if (ya >= g.ny) return;
+    const int yb = min(ya + rows, g.ny);
+    const int tid = threadIdx.x, lane = tid & 63, wave = (tid >> 6) + 1;
+    const int xo = xblk * cols - kHalo + tid;
+    int x = xo % g.nx;
+    x = x < 0 ? x + g.nx : x;
+    const unsigned vm = (unsigned)(x == 0 ? g.nx - 1 : x - 1) * sizeof(T);
+    const unsigned v0 = (unsigned)x * sizeof(T);
+    const unsigned vp = (unsigned)(x == g.nx - 1 ? 0 : x + 1) * sizeof(T);
+    const unsigned vout = tid >= kHalo && tid < kHalo + cols && xo < g.nx ? v0 : kNoCell;
+    const T om = (T)g.omega, Fx = (T)g.gx, Fy = T(0);
+    const T uc = (T)g.uref_c, c3 = (T)((double)FirstOrderW<T>::diag * g.uref_c);
+    auto offsets = [&](int y, T (&s)[9]) {  // add_pull_offsets
+        const T dm = c3 * (T)(2 * y - g.ny), dp = c3 * (T)(g.ny - 2 - 2 * y);
+        s[5] += dm;
+        s[6] -= dm;
+        s[7] -= dp;
+        s[8] += dp;
+    };
+    auto uref = [&](int y) { return uc * (T)(y * (g.ny - 1 - y)); };
+    const unsigned row = (unsigned)g.nxp * sizeof(T), plane = (unsigned)g.ny * row;
+    const bool py = g.periodic_y;
+    const int top = g.ny - 1;
+    auto wrap = [&](int y) { return y < 0 ? y + g.ny : (y > top ? y - g.ny : y); };
+    auto load = [&](int r, T (&s)[9]) {
+        const __amdgpu_buffer_rsrc_t in = buffer_of(src, r <= yb ? bytes : 0u);
+        int y, ym, yp;
+        if (py) {
+            y = wrap(r);
+            ym = wrap(y - 1);
+            yp = wrap(y + 1);
+        } else {  // rows past a wall are not used, nor is what a wall row would read there
+            y = max(0, min(top, r));
+            ym = max(0, y - 1);
+            yp = min(top, y + 1);
+        }
+        const unsigned o = (unsigned)y * row, om_ = (unsigned)ym * row, op = (unsigned)yp * row;
+        buf_load<2>(in, v0, o, s[0]);
+        buf_load<0>(in, vm, o + plane, s[1]);
+        buf_load<2>(in, v0, om_ + 2 * plane, s[2]);
+        buf_load<0>(in, vp, o + 3 * plane, s[3]);
+        buf_load<2>(in, v0, op + 4 * plane, s[4]);
+        buf_load<0>(in, vm, om_ + 5 * plane, s[5]);
+        buf_load<0>(in, vp, om_ + 6 * plane, s[6]);
+        buf_load<0>(in, vp, op + 7 * plane, s[7]);
+        buf_load<0>(in, vm, op + 8 * plane, s[8]);
+    };
+    // post-collision values of the rows before, moved to this column: 2, 5, 6
+    // of row r - 2 (A), 0, 1, 3 and 2, 5, 6 of row r - 1 (B)
+    T A2 = 0, A5 = 0, A6 = 0, B0 = 0, B1 = 0, B2 = 0, B3 = 0, B5 = 0, B6 = 0;
+    auto step = [&](int r, T (&ahead)[9]) {
+        T s[9], p[9];
+#pragma unroll
+        for (int i = 0; i < 9; i++) s[i] = ahead[i];
+        load(r + 2, ahead);
+        const int rw = py ? wrap(r) : r;
+        offsets(rw, s);
+        if (!py && (rw == 0 || rw == top)) pull_complete<T, false>(src, 1, rw, g, Fx, s);
+        collide(s, uref(rw), om, Fx, Fy, p);
+        const int par = r & 1;
+        if (lane == 0 || lane == 63) {
+            T* e = edge[par][wave][lane != 0];
+            e[0] = lane ? p[1] : p[3];
+            e[1] = lane ? p[5] : p[6];
+            e[2] = lane ? p[8] : p[7];
+        }
+        lds_barrier();
+        const T* e = lane ? edge[par][wave + 1][0] : edge[par][wave - 1][1];
+        const T e0 = e[0], e1 = e[1], e2 = e[2];
+        p[1] = lane_shift<kWaveShr1>(p[1]);
+        p[5] = lane_shift<kWaveShr1>(p[5]);
+        p[8] = lane_shift<kWaveShr1>(p[8]);
+        p[3] = lane_shift<kWaveShl1>(p[3]);
+        p[6] = lane_shift<kWaveShl1>(p[6]);
+        p[7] = lane_shift<kWaveShl1>(p[7]);
+        p[1] = lane == 0 ? e0 : p[1];
+        p[5] = lane == 0 ? e1 : p[5];
+        p[8] = lane == 0 ? e2 : p[8];
+        p[3] = lane == 63 ? e0 : p[3];
+        p[6] = lane == 63 ? e1 : p[6];
+        p[7] = lane == 63 ? e2 : p[7];
+        const int yo = r - 1;
+        T q[9] = {B0, B1, A2, B3, p[4], A5, A6, p[7], p[8]}, o[9];
+        offsets(yo, q);
+        if (!py && (yo == 0 || yo == top)) pull_complete<T, false>(src, 1, yo, g, Fx, q);
+        collide(q, uref(yo), om, Fx, Fy, o);
+        const __amdgpu_buffer_rsrc_t to = buffer_of(dst, yo >= ya ? bytes : 0u);
+        const unsigned so = (unsigned)max(yo, 0) * row;
+#pragma unroll
+        for (int i = 0; i < 9; i++) buf_store<NT ? 2 : 0>(to, vout, so + i * plane, o[i]);
+        A2 = B2;
+        A5 = B5;
+        A6 = B6;
+        B0 = p[0];
+        B1 = p[1];
+        B2 = p[2];
+        B3 = p[3];
+        B5 = p[5];
+        B6 = p[6];
+    };
+    // rows ya - 1 .. yb; past a wall there is none (its values are replaced), and
+    // the row is computed from clamped loads and not used
+    const int r0 = (!py && ya == 0) ? 0 : ya - 1;
+    T even[9], odd[9];
+    load(r0, even);
+    load(r0 + 1, odd);
+    for (int r = r0; r <= yb; r += 2) {
+        step(r, even);
+        if (r + 1 <= yb) step(r + 1, odd);
+    }
+}
+
+// Whether two steps of a lattice go in one pass: its populations must be past
+// the size where a single pass is bound by its launch (us per step in single /
+// double passes, FP32: 512^2, 9 MiB, 4.8 / 5.0-6.2; 768^2, 20 MiB, 7.7 / 6.5; 1024^2
+// 12.7 / 9.6; 2048^2 52.9 / 32.4; 8192^2 839 / 501; FP64: 550^2 8.8 / 7.5, 1777 x 1003
+// 40.1 / 27.2, 4096^2 408 / 249) and within the 32-bit buffer offsets.
+template <typename T>
+bool grid_two_pays(const GridArgs& g)
+{
+    const double bytes = 9.0 * g.ny * g.nxp * sizeof(T);
+    return g.periodic_x && bytes >= kTwoMinBytes && bytes < 4.0 * (1u << 30) - 4096.0;
+}
+
+// Column blocks of at most kTwoThreads lanes, and as many rows per block as
+// put two blocks on every compute unit in one round: all blocks then start and
+// end together (4096^2 FP32: 64 rows 119 us, 32 rows and two rounds 134, 60 rows
+// and a second round of a few blocks 157); one block where that would leave fewer
+// than six rows to set against the two extra rows of step n (1024^2: 8 rows 9.8 us,
+// 4 rows 10.0).
+template <typename T>
+hipError_t launch_grid_two(const T* src, T* dst, const GridArgs& g, int num_cu, hipStream_t s)
+{
+    constexpr int kHalo = 128 / (int)sizeof(T);
+    constexpr int max_threads = sizeof(T) == 4 ? 576 : 512;
+    constexpr int max_cols = (max_threads - kHalo - 1) / kHalo * kHalo;
+    const int nblkx = (g.nx + max_cols - 1) / max_cols;
+    const int cols = ((g.nx + nblkx - 1) / nblkx + kHalo - 1) / kHalo * kHalo;
+    const int threads = (kHalo + cols + 1 + 63) / 64 * 64;
+    auto rows_for = [&](int per_cu) {
+        const int chunks = max(1, per_cu * num_cu / nblkx);
+        return (g.ny + chunks - 1) / chunks;
+    };
+    int rows = rows_for(2);
+    if (rows < 6) rows = rows_for(1);
+    rows = max(rows, 4);
+    const int tiles = (g.ny + rows - 1) / rows * nblkx;
+    const dim3 grid((unsigned)((tiles + kNumXcd - 1) / kNumXcd * kNumXcd));
+    const unsigned bytes = (unsigned)(9ull * g.ny * g.nxp * sizeof(T));
+    if (2.0 * bytes > kPlainStoreMaxBytes)
+        hipLaunchKernelGGL((k_grid_two<T, true>), grid, dim3(threads), 0, s, src, dst, g, bytes,
+                           rows, cols, nblkx);
+    else
+        hipLaunchKernelGGL((k_grid_two<T, false>), grid, dim3(threads), 0, s, src, dst, g, bytes,
+                           rows, cols, nblkx);
+    return hipGetLastError();
+}
+
 int grid_blocks(int ny, int nseg)
 {
     constexpr int R = kGridRowsPerThread;
@@ -2159,6 +2406,8 @@ hipError_t launch_set_nodes(T* nodes, CapsuleDev* caps, int cap, int nv, int nod
                                        hipStream_t);                                              \
     template hipError_t launch_grid_step<T>(const T*, T*, const long long*, const int*,           \
                                             long long*, int*, const GridArgs&, hipStream_t);      \
+    template bool grid_two_pays<T>(const GridArgs&);                                              \
+    template hipError_t launch_grid_two<T>(const T*, T*, const GridArgs&, int, hipStream_t);      \
     template hipError_t launch_grid_step_batch<T>(const T*, T*, const long long*, const int*,     \
                                                   long long*, int*, const InstDev*, const int2*,  \
                                                   int, int, int, int, bool, const int*, int,      \
