@@ -1550,19 +1550,24 @@ static lbib_status adjoint_t(lbib_ctx* c, int N, int mode, int objective, int ca
     // takes the IB launches and tapes the nodes; a recomputed segment spreads
     // the taped node forces instead (the same force levels, no node state)
     auto run_segment = [&](int c0, int e0, bool again) -> lbib_status {
+        if (again) {
+            SpreadTapeArgs<T> sa;
+            sa.fib = gF(1);
+            sa.flags = gFl(1);
+            sa.tape = sN(c0);
+            sa.ref = sR(c0);
+            sa.fib_stride = A.gslot / sizeof(long long);
+            sa.flags_stride = A.gslot / sizeof(int);
+            sa.tape_stride = A.nslot / sizeof(T);
+            sa.ref_stride = A.nslot / sizeof(double);
+            sa.caps = reinterpret_cast<const CapsuleDev*>(bufp(c, LBIB_BUF_CAPS));
+            sa.status = status_word(c);
+            sa.node_stride = c->L.max_nodes;
+            HIPCHK(c, launch_spread_tape<T>(sa, c->ncap, e0 - c0, st));
+        }
         for (int n = c0; n < e0; n++) {
             const int r = n - c0;
-            if (again) {
-                SpreadTapeArgs<T> sa;
-                sa.fib = gF(r + 1);
-                sa.flags = gFl(r + 1);
-                sa.tape = sN(n);
-                sa.ref = sR(n);
-                sa.caps = reinterpret_cast<const CapsuleDev*>(bufp(c, LBIB_BUF_CAPS));
-                sa.status = status_word(c);
-                sa.node_stride = c->L.max_nodes;
-                HIPCHK(c, launch_spread_tape<T>(sa, c->ncap, st));
-            } else {
+            if (!again) {
                 IBArgs<T> a = ib_args<T>(c, n, n == 0 ? (PH_PRIME | PH_A) : (PH_B | PH_A));
                 a.pops = gP(r);
                 a.fib_prev = gF(r);

@@ -159,13 +159,15 @@ struct IBArgs {
 constexpr int kTapeFX = 8, kTapeFY = 9;
 constexpr int kTapeFields = 10;
 
-// Spreading of a taped step (recomputed segments of the gradient runs).
+// Spreading of taped steps (recomputed segments of the gradient runs): step i
+// of the launch is i strides behind the first.
 template <typename T>
 struct SpreadTapeArgs {
-    long long* fib;         // force level of the step (accumulated), [ny][nxp][2] per lattice
+    long long* fib;         // force level of a step (accumulated), [ny][nxp][2] per lattice
     int* flags;             // its segment flags
-    const T* tape;          // node tape of the step, [kTapeFields][node_stride]
-    const double* ref;      // reference points of the step, [max_capsules][2]
+    const T* tape;          // node tape of a step, [kTapeFields][node_stride]
+    const double* ref;      // reference points of a step, [max_capsules][2]
+    size_t fib_stride, flags_stride, tape_stride, ref_stride;  // elements from step to step
     const CapsuleDev* caps;
     int* status;
     int node_stride;
@@ -212,7 +214,7 @@ hipError_t launch_grid_near(const T* src, T* dst, const long long* fib_now, cons
 template <typename T>
 hipError_t launch_contact(const ContactArgs<T>& a, hipStream_t s);
 template <typename T>
-hipError_t launch_spread_tape(const SpreadTapeArgs<T>& a, int ncap, hipStream_t s);
+hipError_t launch_spread_tape(const SpreadTapeArgs<T>& a, int ncap, int nsteps, hipStream_t s);
 template <typename T>
 hipError_t contact_set_lds_limit(int max_nv);
 // Blocks of the grid kernel for one lattice (a multiple of kNumXcd).
