@@ -347,7 +347,9 @@ __global__ __launch_bounds__(kSegW * 4) void k_grid_adj(GridAdjArgs<T> a, GridAr
 #pragma unroll
             for (int i = 0; i < 9; i++) lo[i] = a.lam_in[i * plane + cell];
             double Fbx, Fby;
-            collide_vjp<double>(s, Fx, Fy, uref_at<T>(g, y), (T)g.omega, lo, sb, Fbx, Fby);
+            const Uref<T> ur = uref_at<T>(g, y);
+            collide_vjp<double>(s, Fx, Fy, (double)ur.c * (double)ur.yy, (T)g.omega, lo, sb, Fbx,
+                                Fby);
             const bool bot = !g.periodic_y && y == 0, top = !g.periodic_y && y == g.ny - 1;
             if (bot) zou_he_vjp<double>(sb, Fbx, (T)g.u_bot, false);
             if (top) zou_he_vjp<double>(sb, Fbx, (T)g.u_top, true);
@@ -1019,13 +1021,13 @@ __global__ __launch_bounds__(kAdjThreads) void k_ib_adj(IBAdjArgs<T> a)
     // the reference point on the periodic axes (x always periodic here)
     const int wrx = wrap_ref(refx, g.nx), wry = g.periodic_y ? wrap_ref(refy, g.ny) : 0;
     {
-        IBArgs<T> ia;
-        ia.pops = a.pops + cap.pop_off;
-        ia.fib_prev = a.fib_prev + cap.fib_off;
-        const T gxf = (T)cap.gx;
+        PatchGeo<T> Q;
+        set_geo(Q, P, g, a.pops + cap.pop_off, a.fib_prev + cap.fib_off, wrx,
+                g.periodic_y ? wry : (int)refy);
         const int ncell = P.W * P.H;
         // four cells per thread with all their loads in flight together
-        for (int i = tid; i < ncell; i += 4 * nt) stage_cells<T, 4>(ia, g, P, refx, refy, gxf, i, nt);
+        for (int i = tid; i < ncell; i += 4 * nt) stage_cells<T, 4>(Q, g, P, i, nt, ncell);
+        stage_other_cells(Q, g, P);
         S.wide = sizeof(T) == 4 && ncell <= a.patch_cap / 2;
         for (int i = tid; i < ncell; i += nt) {
             if (S.wide) S.Wd[i] = S.Wu[i] = S.Wv[i] = 0.0;

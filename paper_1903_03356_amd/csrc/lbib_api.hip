@@ -103,6 +103,7 @@ struct lbib_ctx {
     hipStream_t s_cap = nullptr;
     hipGraphExec_t gexec[2] = {nullptr, nullptr};
     const void* g_pops = nullptr;
+    int g_levels[2] = {-1, -1};  // force levels each was captured with (prev, next)
     int g_ncap = -1, g_mode = -1, g_patch = -1, g_tile = -1;
     double g_contact = -1.0;
     long long graph_replays = 0;
@@ -123,6 +124,13 @@ struct lbib_ctx {
     // there phase A writes no node state), so the next call starts with the
     // grid pass.  set_state drops it (the state it was computed from changes).
     bool a_ready = false;
+    // of a forcing spread ahead: the step's near map is stamped too (overlapped
+    // schedule only)
+    bool a_stamped = false;
+    // force levels by what they hold at time `steps` (as the step calls go on):
+    // F^{n-1}, F^n (zero until spread), and a spare one (zero).  A serial step
+    // swaps the first two, a fused one rotates all three.
+    int lv_prev = 1, lv_next = 0, lv_spare = 2;
     // membrane checks (lbib_set_limits), 0 = off
     float max_edge = 0.0f, max_dA = 0.0f;
 };
@@ -266,8 +274,8 @@ static size_t layout_bytes(const Layout& L, int id)
     switch (id) {
     case LBIB_BUF_POPS_A:
     case LBIB_BUF_POPS_B: return round256(L.pop_elems * L.rb);
-    case LBIB_BUF_FORCE: return round256(2 * L.fib_level * sizeof(long long));
-    case LBIB_BUF_FLAGS: return round256(2 * L.flag_level * sizeof(int));
+    case LBIB_BUF_FORCE: return round256(kForceLevels * L.fib_level * sizeof(long long));
+    case LBIB_BUF_FLAGS: return round256(kForceLevels * L.flag_level * sizeof(int));
     case LBIB_BUF_NODES: return round256((size_t)NF_COUNT * L.max_nodes * L.rb);
     case LBIB_BUF_CAPS:
         return L.hints + round256((size_t)L.max_caps * sizeof(int4));
@@ -329,14 +337,15 @@ static T* pops_of(const lbib_ctx* c, long long parity, const Inst& I)
     return static_cast<T*>(pops(c, parity)) + I.pop_off;
 }
 
-static long long* fib(const lbib_ctx* c, long long parity)
+// A force level (lbib_ctx::lv_*) and its segment flags.
+static long long* fib(const lbib_ctx* c, int level)
 {
-    return reinterpret_cast<long long*>(bufp(c, LBIB_BUF_FORCE)) + (parity & 1) * c->L.fib_level;
+    return reinterpret_cast<long long*>(bufp(c, LBIB_BUF_FORCE)) + level * c->L.fib_level;
 }
 
-static int* flags(const lbib_ctx* c, long long parity)
+static int* flags(const lbib_ctx* c, int level)
 {
-    return reinterpret_cast<int*>(bufp(c, LBIB_BUF_FLAGS)) + (parity & 1) * c->L.flag_level;
+    return reinterpret_cast<int*>(bufp(c, LBIB_BUF_FLAGS)) + level * c->L.flag_level;
 }
 
 static int* status_word(const lbib_ctx* c)
@@ -353,6 +362,13 @@ static bool any_open(const lbib_ctx* c)
 {
     for (const Inst& I : c->L.inst)
         if (!I.walls.periodic_x) return true;
+    return false;
+}
+
+static bool any_rigid(const lbib_ctx* c)
+{
+    for (int r : c->cap_rigid)
+        if (r) return true;
     return false;
 }
 
@@ -390,11 +406,11 @@ static unsigned long long* ib_done_counter(const lbib_ctx* c)
 static lbib_status drop_pending_forcing(lbib_ctx* c)
 {
     if (!c->a_ready) return LBIB_OK;
-    const long long n = c->steps;
-    HIPCHK(c, hipMemsetAsync(fib(c, n), 0, c->L.fib_level * sizeof(long long), c->stream));
-    HIPCHK(c, hipMemsetAsync(flags(c, n), 0, c->L.flag_level * sizeof(int), c->stream));
-    HIPCHK(c, hipMemsetAsync(near_map(c, n), 0, c->L.flag_level * sizeof(int), c->stream));
-    c->a_ready = false;
+    HIPCHK(c, hipMemsetAsync(fib(c, c->lv_next), 0, c->L.fib_level * sizeof(long long), c->stream));
+    HIPCHK(c, hipMemsetAsync(flags(c, c->lv_next), 0, c->L.flag_level * sizeof(int), c->stream));
+    if (c->a_stamped)
+        HIPCHK(c, hipMemsetAsync(near_map(c, c->steps), 0, c->L.flag_level * sizeof(int), c->stream));
+    c->a_ready = c->a_stamped = false;
     return LBIB_OK;
 }
 
@@ -694,6 +710,16 @@ static lbib_status add_capsule_t(lbib_ctx* c, int inst, const double* xy, int n,
     cd.gx = g.gx;
     cd.nu = I.nu;
     cd.uref_c = g.uref_c;
+    auto wrapped = [](double ref, int n, int periodic) {
+        return (int)(periodic ? ref - n * std::floor(ref / n) : ref);
+    };
+    cd.wx = wrapped(refx, g.nx, g.periodic_x);
+    cd.wy = wrapped(refy, g.ny, g.periodic_y);
+    cd.omega = g.omega;
+    cd.u_bot = g.u_bot;
+    cd.u_top = g.u_top;
+    cd.u_in = g.u_in;
+    cd.rho_out = g.rho_out;
     if (rigid) {
         cd.rigid = 1;
         cd.rX = rcx;
@@ -816,12 +842,12 @@ static void size_patches(lbib_ctx* c)
 template <typename T>
 static IBArgs<T> ib_args(const lbib_ctx* c, long long n, int phase)
 {
-    // state n: populations f*^{n-1} in buffer n%2, force F^{n-1} in level (n-1)%2
+    // state n: populations f*^{n-1} in buffer n%2, force F^{n-1} in its level
     IBArgs<T> a;
     a.pops = static_cast<const T*>(pops(c, n));
-    a.fib_prev = fib(c, n + 1);
-    a.fib_next = fib(c, n);
-    a.flags_next = flags(c, n);
+    a.fib_prev = fib(c, c->lv_prev);
+    a.fib_next = fib(c, c->lv_next);
+    a.flags_next = flags(c, c->lv_next);
     a.nodes = reinterpret_cast<T*>(bufp(c, LBIB_BUF_NODES));
     a.caps = reinterpret_cast<CapsuleDev*>(bufp(c, LBIB_BUF_CAPS));
     a.diag = reinterpret_cast<double*>(bufp(c, LBIB_BUF_DIAG));
@@ -928,14 +954,18 @@ static hipError_t do_grid(lbib_ctx* c, void* p)
     if (c->L.inst.size() == 1) {
         const GridArgs g = grid_args(c->L.inst[0]);
         return launch_grid_step<T>(static_cast<const T*>(pops(c, n)),
-                                   static_cast<T*>(pops(c, n + 1)), fib(c, n), flags(c, n),
-                                   fib(c, n + 1), flags(c, n + 1), g, c->stream);
+                                   static_cast<T*>(pops(c, n + 1)), fib(c, c->lv_next),
+                                   flags(c, c->lv_next), fib(c, c->lv_prev), flags(c, c->lv_prev),
+                                   g, c->stream);
     }
     return launch_batch_shape<T>(c, static_cast<const T*>(pops(c, n)),
-                                 static_cast<T*>(pops(c, n + 1)), fib(c, n), flags(c, n),
-                                 fib(c, n + 1), flags(c, n + 1), c->tile_shape, c->tile_resident,
-                                 c->stream);
+                                 static_cast<T*>(pops(c, n + 1)), fib(c, c->lv_next),
+                                 flags(c, c->lv_next), fib(c, c->lv_prev), flags(c, c->lv_prev),
+                                 c->tile_shape, c->tile_resident, c->stream);
 }
+
+// The force levels after a grid step that cleared F^{n-1}.
+static void levels_after_step(lbib_ctx* c) { std::swap(c->lv_prev, c->lv_next); }
 
 // Steps n and n + 1 of a lattice without capsules, into the buffer of the other
 // parity (the caller swaps the two).
@@ -971,13 +1001,15 @@ static hipError_t do_far(lbib_ctx* c, void* p)
     const bool own_event = c->L.inst.size() == 1 && !c->timing;
     if (c->L.inst.size() > 1)
         return launch_batch_shape<T>(c, static_cast<const T*>(pops(c, n)),
-                                     static_cast<T*>(pops(c, n + 1)), fib(c, n), flags(c, n),
-                                     fib(c, n + 1), flags(c, n + 1), c->tile_shape,
-                                     c->tile_resident, c->s_far, near_map(c, n), step_stamp(n));
+                                     static_cast<T*>(pops(c, n + 1)), fib(c, c->lv_next),
+                                     flags(c, c->lv_next), fib(c, c->lv_prev),
+                                     flags(c, c->lv_prev), c->tile_shape, c->tile_resident,
+                                     c->s_far, near_map(c, n), step_stamp(n));
     const GridArgs g = grid_args(c->L.inst[0]);
     return launch_grid_far<T>(static_cast<const T*>(pops(c, n)), static_cast<T*>(pops(c, n + 1)),
-                              fib(c, n), flags(c, n), fib(c, n + 1), flags(c, n + 1),
-                              near_map(c, n), step_stamp(n), status_word(c), g, c->s_far,
+                              fib(c, c->lv_next), flags(c, c->lv_next), fib(c, c->lv_prev),
+                              flags(c, c->lv_prev), near_map(c, n), step_stamp(n),
+                              status_word(c), g, c->s_far,
                               own_event ? c->e_far[n & 1] : nullptr,
                               c->far_waits_inside ? ib_done_counter(c) : nullptr,
                               c->ib_blocks_issued);
@@ -988,8 +1020,8 @@ static hipError_t do_near(lbib_ctx* c, void* p)
 {
     const long long n = *static_cast<const long long*>(p);
     return launch_grid_near<T>(static_cast<const T*>(pops(c, n)), static_cast<T*>(pops(c, n + 1)),
-                               fib(c, n), flags(c, n), fib(c, n + 1), flags(c, n + 1),
-                               rect_table(c, n),
+                               fib(c, c->lv_next), flags(c, c->lv_next), fib(c, c->lv_prev),
+                               flags(c, c->lv_prev), rect_table(c, n),
                                reinterpret_cast<const CapsuleDev*>(bufp(c, LBIB_BUF_CAPS)),
                                inst_table(c), c->ncap, c->stream);
 }
@@ -1019,6 +1051,10 @@ static lbib_status step_overlap_t(lbib_ctx* c, int nsteps)
     }
     // the forcing of the first step, unless the last call spread it ahead;
     // the event orders the first far launch after all work on the main stream
+    if (c->a_ready && !c->a_stamped) {  // spread by a fused call, without the near map
+        lbib_status s = drop_pending_forcing(c);
+        if (s != LBIB_OK) return s;
+    }
     if (!c->a_ready) {
         const long long n = c->steps;
         IBLaunch<T> q{n, n == 0 ? (PH_PRIME | PH_A) : PH_A, true};
@@ -1053,13 +1089,14 @@ static lbib_status step_overlap_t(lbib_ctx* c, int nsteps)
             HIPCHK(c, hipEventRecord(c->e_far[n & 1], c->s_far));
         s = launch_timed<T>(c, 2, do_near<T>, &nn);
         if (s != LBIB_OK) return s;
+        levels_after_step(c);
         const bool more = k + 1 < nsteps || ahead;
         IBLaunch<T> q{n + 1, more ? (PH_B | PH_A) : PH_B, more};
         s = launch_timed<T>(c, 1, do_ib<T>, &q);
         if (s != LBIB_OK) return s;
         HIPCHK(c, hipEventRecord(c->e_ib, c->stream));
     }
-    c->a_ready = ahead;
+    c->a_ready = c->a_stamped = ahead;
     HIPCHK(c, hipStreamWaitEvent(c->stream, c->e_far[(c->steps + nsteps - 1) & 1], 0));
     c->steps += nsteps;
     return LBIB_OK;
@@ -1100,7 +1137,49 @@ static lbib_status step_body(lbib_ctx* c, long long n, int pb, int pa, bool cont
         if (s != LBIB_OK) return s;
     }
     long long nn = n;
-    return launch_timed<T>(c, 0, do_grid<T>, &nn);
+    const lbib_status s = launch_timed<T>(c, 0, do_grid<T>, &nn);
+    levels_after_step(c);
+    return s;
+}
+
+// Fused schedule of one lattice: one launch per step (k_step) after a first one
+// that spreads the forcing of the call's first step.  With the Dynamic scheme
+// the last launch also spreads the forcing of the step after it (phase A writes
+// no node state there), so that the next call goes without.
+template <typename T>
+static lbib_status step_fused_t(lbib_ctx* c, int nsteps, bool contact)
+{
+    const GridArgs g = grid_args(c->L.inst[0]);
+    const bool ahead = c->mode == LBIB_DYNAMIC && !contact;
+    if (!c->a_ready) {
+        IBLaunch<T> q{c->steps, c->steps == 0 ? (PH_PRIME | PH_A) : PH_A, false};
+        HIPCHK(c, do_ib<T>(c, &q));
+    }
+    for (int k = 0; k < nsteps; k++) {
+        const long long n = c->steps + k;
+        const bool more = k + 1 < nsteps || ahead;
+        if (contact) {
+            lbib_status s = launch_contact_t<T>(c);
+            if (s != LBIB_OK) return s;
+        }
+        // IB of step n + 1 from P^n and F^n, its forcing into the spare level
+        IBArgs<T> a = ib_args<T>(c, n, more ? (PH_B | PH_A) : PH_B);
+        a.fib_prev = fib(c, c->lv_next);
+        a.fib_next = fib(c, c->lv_spare);
+        a.flags_next = flags(c, c->lv_spare);
+        HIPCHK(c, launch_step<T>(a, c->ncap, any_rigid(c), c->lds_use, static_cast<const T*>(pops(c, n)),
+                                 static_cast<T*>(pops(c, n + 1)), fib(c, c->lv_next),
+                                 flags(c, c->lv_next), fib(c, c->lv_prev), flags(c, c->lv_prev), g,
+                                 c->stream));
+        const int cleared = c->lv_prev;
+        c->lv_prev = c->lv_next;
+        c->lv_next = c->lv_spare;
+        c->lv_spare = cleared;
+    }
+    c->a_ready = ahead;
+    c->a_stamped = false;
+    c->steps += nsteps;
+    return LBIB_OK;
 }
 
 // Steps per replay of a captured block (even: a replay leaves the buffer
@@ -1175,6 +1254,11 @@ static lbib_status step_t(lbib_ctx* c, int nsteps)
     const bool want = c->overlap >= 1 || (c->overlap < 0 && c->L.inst.size() == 1 &&
                                           cells >= kOverlapMinCells);
     if (can_overlap && want) return step_overlap_t<T>(c, nsteps);
+    // one launch per step (the contact force of the Kinematic scheme sits between
+    // the node update and the forcing, so it keeps separate launches)
+    if (c->overlap < 0 && c->ncap > 0 && c->L.inst.size() == 1 && !(contact && !dyn) &&
+        !c->timing && c->graph != 1 && !capturing(c->stream))
+        return step_fused_t<T>(c, nsteps, contact);
     // replays of captured blocks for the inner steps; timed runs launch directly
     const bool graphs = c->graph == 1 && !c->timing;
     const int tile = c->tile_shape * 256 + c->tile_resident;
@@ -1205,6 +1289,12 @@ static lbib_status step_t(lbib_ctx* c, int nsteps)
         }
         if (graphs && k >= 1 && nsteps - k >= kGraphSteps) {
             hipGraphExec_t& ge = c->gexec[n & 1];
+            const int levels = c->lv_prev * kForceLevels + c->lv_next;
+            if (ge && c->g_levels[n & 1] != levels) {
+                (void)hipGraphExecDestroy(ge);
+                ge = nullptr;
+            }
+            c->g_levels[n & 1] = levels;
             if (!ge) {
                 lbib_status s = capture_steps<T>(c, n, contact, dyn, &ge);
                 if (s != LBIB_OK) return s;
@@ -1229,7 +1319,7 @@ static lbib_status step_t(lbib_ctx* c, int nsteps)
         lbib_status s = launch_timed<T>(c, 1, do_ib<T>, &q);
         if (s != LBIB_OK) return s;
     }
-    c->a_ready = false;
+    c->a_ready = c->a_stamped = false;
     c->steps += nsteps;
     return LBIB_OK;
 }
@@ -1262,7 +1352,7 @@ static lbib_status get_t(lbib_ctx* c, int what, int cap, void* dst, size_t bytes
     const Inst& I = c->L.inst[field ? cap : 0];
     const GridArgs g = grid_args(I);
     const size_t plane = (size_t)I.grid.nx * I.grid.ny;
-    const long long* fib_last = fib(c, c->steps + 1) + I.fib_off;
+    const long long* fib_last = fib(c, c->lv_prev) + I.fib_off;
     double* stage = reinterpret_cast<double*>(bufp(c, LBIB_BUF_STAGE));
     const hipMemcpyKind d2h = hipMemcpyDeviceToHost;
     auto finish = [&](const double* src, size_t n) -> lbib_status {
@@ -1620,9 +1710,9 @@ static lbib_status adjoint_t(lbib_ctx* c, int N, int mode, int objective, int ca
     }
     // the context now stands at step N
     HIPCHK(c, hipMemcpyAsync(pops(c, N), gP(rN), pop_bytes, d2d, st));
-    HIPCHK(c, hipMemcpyAsync(fib(c, N + 1), gF(rN), 2 * (size_t)I.nxp * I.grid.ny * sizeof(long long),
+    HIPCHK(c, hipMemcpyAsync(fib(c, c->lv_prev), gF(rN), 2 * (size_t)I.nxp * I.grid.ny * sizeof(long long),
                              d2d, st));
-    HIPCHK(c, hipMemcpyAsync(flags(c, N + 1), gFl(rN), (size_t)I.grid.ny * I.nseg * sizeof(int),
+    HIPCHK(c, hipMemcpyAsync(flags(c, c->lv_prev), gFl(rN), (size_t)I.grid.ny * I.nseg * sizeof(int),
                              d2d, st));
     c->steps = N;
     c->a_ready = false;
@@ -1878,8 +1968,8 @@ static lbib_status autotune_t(lbib_ctx* c, int launches, double* us)
     const long long n = c->steps;
     const T* src = static_cast<const T*>(pops(c, n));
     T* dst = static_cast<T*>(pops(c, n + 1));
-    long long* f = fib(c, n);
-    int* fl = flags(c, n);
+    long long* f = fib(c, c->lv_next);
+    int* fl = flags(c, c->lv_next);
     hipEvent_t e0 = nullptr, e1 = nullptr;  // timing only, as take_event's
     HIPCHK(c, hipEventCreateWithFlags(&e0, hipEventDisableSystemFence));
     if (hipEventCreateWithFlags(&e1, hipEventDisableSystemFence) != hipSuccess) {

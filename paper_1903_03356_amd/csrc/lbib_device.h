@@ -49,10 +49,19 @@ struct FirstOrderW {
 // every step, and at the coarser scale those roundings add up to a drift of
 // 1e-5 of the velocity over 2e4 steps.  (3 w_i) are the first-order weights
 // above, whose moments give u_ref back exactly.
+// u_ref as its two factors: it is added with one rounding (FMA).  Rounded by
+// itself it would put a fixed error of 1e-9 on the velocity of every row, 2e-6 of
+// the shear between rows, and twice the error on dJ/dk_s (2.6e-6 instead of 1.4e-6).
 template <typename T>
-__device__ __forceinline__ T uref_at(const GridArgs& g, int y)
+struct Uref {
+    T c, yy;
+    __device__ __forceinline__ T plus(T x) const { return fma(c, yy, x); }
+};
+
+template <typename T>
+__device__ __forceinline__ Uref<T> uref_at(const GridArgs& g, int y)
 {
-    return (T)g.uref_c * (T)(y * (g.ny - 1 - y));
+    return {(T)g.uref_c, (T)(y * (g.ny - 1 - y))};
 }
 
 // A population pulled from row y - e_iy to row y changes reference:
@@ -95,47 +104,53 @@ __device__ __forceinline__ double recip(double x)
 //   m = sum s e + F / 2 = rho u - u_ref  (Eq. 7; taken as is in the first-order
 //       term, so that rho * (m / rho) rounding does not leak into the momentum)
 //   M = u_ref + m = rho u,  u = M / rho,  p F = (1 - om/2) F,
-//   G = om/2 M + p F,  H = om m + p F,  C = om (rho - 1) - 3 u.G,
+//   G = om/2 M + p F,  C = om (rho - 1) - 3 u.G,
 // the populations after the collision are
-//   s - om s + w (C + 9 (e.u)(e.G)) + 3 w e.H:
-// the even part (first bracket) and the odd part are shared by opposite
-// directions, and (e.u)(e.G) by t_x = u_x G_x, t_y = u_y G_y and
-// X = u_x G_y + u_y G_x.  About 85 operations instead of 180 with every
-// direction on its own: one step is bound by memory either way, two steps in
-// one pass (k_grid_two) would not be.  The rest population takes C less the
-// other eight shares, so that mass is conserved whatever 1/9 rounds to, and
-// s - om s is one FMA with the exact om for the same reason.
+//   s + [w (C + 9 (e.u)(e.G)) - om s_even] + [om (3 w e.m - s_odd) + 3 w e.pF]:
+// the even bracket (s_even = half the sum with the opposite direction's) and the
+// odd one (s_odd = half the difference) are shared by opposite directions, and
+// (e.u)(e.G) by t_x = u_x G_x, t_y = u_y G_y and X = u_x G_y + u_y G_x.  Both
+// brackets are small near equilibrium and are added to s last, so that a value
+// as large as the flow's first-order term (where there is no reference flow) is
+// rounded once.  About 90 operations instead of 180 with every direction on its
+// own: one step is bound by memory either way, two steps in one pass
+// (k_grid_two) would not be.  The rest population takes C less the other eight
+// shares, so that mass is conserved whatever 1/9 rounds to.
 template <typename T>
-__device__ __forceinline__ void collide(const T (&s)[9], T ur, T om, T Fx, T Fy, T (&o)[9])
+__device__ __forceinline__ void collide(const T (&s)[9], Uref<T> ur, T om, T Fx, T Fy, T (&o)[9])
 {
     const T d13 = s[1] - s[3], d24 = s[2] - s[4], d57 = s[5] - s[7], d68 = s[6] - s[8];
-    const T drho = ((s[0] + (s[1] + s[3])) + (s[2] + s[4])) + ((s[5] + s[7]) + (s[6] + s[8]));
+    const T p13 = s[1] + s[3], p24 = s[2] + s[4], p57 = s[5] + s[7], p68 = s[6] + s[8];
+    const T drho = ((s[0] + p13) + p24) + (p57 + p68);
     const T jx = d13 + (d57 - d68), jy = d24 + (d57 + d68);
     const T mx = fma(T(0.5), Fx, jx), my = fma(T(0.5), Fy, jy);
-    const T Mx = ur + mx;
+    const T Mx = ur.plus(mx);
     const T irho = recip(T(1) + drho);
     const T ux = Mx * irho, uy = my * irho;
     const T hom = T(0.5) * om, pre = T(1) - hom;
     const T pFx = pre * Fx, pFy = pre * Fy;
     const T Gx = fma(hom, Mx, pFx), Gy = fma(hom, my, pFy);
-    const T Hx = fma(om, mx, pFx), Hy = fma(om, my, pFy);
     const T tx = ux * Gx, ty = uy * Gy, S = tx + ty;
     const T X = fma(ux, Gy, uy * Gx);
     const T C = fma(T(-3), S, om * drho);
     const T c9 = C * T(1.0 / 9.0);
-    const T Ex = tx + c9, Ey = ty + c9;
-    const T q = c9 + S, Ep = T(0.25) * (q + X), Em = T(0.25) * (q - X);
-    const T Ox = FirstOrderW<T>::axis * Hx, Oy = FirstOrderW<T>::axis * Hy;
-    const T Op = FirstOrderW<T>::diag * (Hx + Hy), Om = FirstOrderW<T>::diag * (Hy - Hx);
-    o[0] = fma(-om, s[0], s[0]) + fma(T(-5), c9, C);
-    o[1] = fma(-om, s[1], s[1]) + (Ex + Ox);
-    o[2] = fma(-om, s[2], s[2]) + (Ey + Oy);
-    o[3] = fma(-om, s[3], s[3]) + (Ex - Ox);
-    o[4] = fma(-om, s[4], s[4]) + (Ey - Oy);
-    o[5] = fma(-om, s[5], s[5]) + (Ep + Op);
-    o[6] = fma(-om, s[6], s[6]) + (Em + Om);
-    o[7] = fma(-om, s[7], s[7]) + (Ep - Op);
-    o[8] = fma(-om, s[8], s[8]) + (Em - Om);
+    const T q = c9 + S;
+    const T w3a = FirstOrderW<T>::axis, w3d = FirstOrderW<T>::diag;
+    const T Ex = fma(-hom, p13, tx + c9), Ey = fma(-hom, p24, ty + c9);
+    const T Ep = fma(-hom, p57, T(0.25) * (q + X)), Em = fma(-hom, p68, T(0.25) * (q - X));
+    const T Ox = fma(om, fma(w3a, mx, T(-0.5) * d13), w3a * pFx);
+    const T Oy = fma(om, fma(w3a, my, T(-0.5) * d24), w3a * pFy);
+    const T Op = fma(om, fma(w3d, mx + my, T(-0.5) * d57), w3d * (pFx + pFy));
+    const T Om = fma(om, fma(w3d, my - mx, T(-0.5) * d68), w3d * (pFy - pFx));
+    o[0] = s[0] + fma(-om, s[0], fma(T(-5), c9, C));
+    o[1] = s[1] + (Ex + Ox);
+    o[2] = s[2] + (Ey + Oy);
+    o[3] = s[3] + (Ex - Ox);
+    o[4] = s[4] + (Ey - Oy);
+    o[5] = s[5] + (Ep + Op);
+    o[6] = s[6] + (Em + Om);
+    o[7] = s[7] + (Ep - Op);
+    o[8] = s[8] + (Em - Om);
 }
 
 // Population loads of the pull.  The lines of the three directions with
@@ -148,6 +163,12 @@ template <typename T>
 __device__ __forceinline__ T ld_stream(const T* p)
 {
     return __builtin_nontemporal_load(p);
+}
+
+template <bool STREAM, typename T>
+__device__ __forceinline__ T ld_pop(const T* p)
+{
+    return STREAM ? __builtin_nontemporal_load(p) : *p;
 }
 
 // Raw pull of the nine populations arriving at an interior node.
@@ -247,7 +268,7 @@ __device__ __forceinline__ void open_boundary(const T* __restrict__ src, int x, 
 // (the hot path, and callers that never reach the end columns of an open
 // channel).  The split lets the grid pass issue the nine loads before it reads
 // the segment's flags, whose value the completion (F_x) depends on.
-template <typename T, bool OPEN = true>
+template <typename T, bool OPEN = true, bool STREAM = true>
 __device__ __forceinline__ void pull_loads(const T* __restrict__ src, int x, int y,
                                            const GridArgs& g, T s[9])
 {
@@ -267,11 +288,11 @@ __device__ __forceinline__ void pull_loads(const T* __restrict__ src, int x, int
         yp = y == g.ny - 1 ? y : y + 1;
     }
     const size_t r0 = (size_t)y * g.nxp, rm = (size_t)ym * g.nxp, rp = (size_t)yp * g.nxp;
-    s[0] = ld_stream(&src[r0 + x]);
+    s[0] = ld_pop<STREAM>(&src[r0 + x]);
     s[1] = src[plane + r0 + xm];
-    s[2] = ld_stream(&src[2 * plane + rm + x]);
+    s[2] = ld_pop<STREAM>(&src[2 * plane + rm + x]);
     s[3] = src[3 * plane + r0 + xp];
-    s[4] = ld_stream(&src[4 * plane + rp + x]);
+    s[4] = ld_pop<STREAM>(&src[4 * plane + rp + x]);
     s[5] = src[5 * plane + rm + xm];
     s[6] = src[6 * plane + rm + xp];
     s[7] = src[7 * plane + rp + xp];
@@ -328,6 +349,20 @@ struct AxisFit {
     double a[3], b[3], s[3];
 };
 
+// exp(-x), 0 <= x <= 8: FP32 by the hardware's 2^t (1 ulp) with the rounding of
+// t = -x log2(e) put back to first order.  
+__device__ __forceinline__ float gauss(float x)
+{
+    const float c = -1.44269504088896341f;                          // -log2(e), rounded
+    const float cl = (float)(-1.44269504088896341 - (double)c);     // and the rest
+    const float t = x * c;
+    const float r = fma(x, c, -t) + x * cl;
+    const float e = __builtin_amdgcn_exp2f(t);
+    return fma(e, r * 0.693147180559945309f, e);
+}
+
+__device__ __forceinline__ double gauss(double x) { return exp(-x); }
+
 template <typename T>
 __device__ __forceinline__ AxisFit axis_fit(T p, int c)
 {
@@ -337,14 +372,14 @@ __device__ __forceinline__ AxisFit axis_fit(T p, int c)
     for (int i = 0; i < 3; i++) {
         const T x = (T)(c + i - 1) - p;
         X[i] = (double)x;
-        W[i] = (double)(T)exp(-(x * x) * inv2);
+        W[i] = (double)gauss(x * x * inv2);
     }
     const double S0 = W[0] + W[1] + W[2];
     const double V0 = W[0] * X[0], V1 = W[1] * X[1], V2 = W[2] * X[2];
     const double S1 = V0 + V1 + V2;
     const double S2 = V0 * X[0] + V1 * X[1] + V2 * X[2];
     const double D = S0 * S2 - S1 * S1;
-    const double r = 1.0 / (S0 * D), i0 = r * D, iD = r * S0;
+    const double r = recip(S0 * D), i0 = r * D, iD = r * S0;
     AxisFit f;
 #pragma unroll
     for (int i = 0; i < 3; i++) {
@@ -379,123 +414,420 @@ __device__ __forceinline__ bool patch_index(const Patch<T>& P, int cx, int cy, i
 // F^{n-1} of the last collision (Eqs. 6-7, fixed-point force, g added):
 // rho - 1 and the force-corrected velocity.
 template <typename T>
-__device__ __forceinline__ void stage_store(const Patch<T>& P, int i, const T (&s)[9],
-                                            long long fx, long long fy, T gxf, T ur)
+__device__ __forceinline__ void stage_moments(const Patch<T>& P, int i, const T (&s)[9], T Fx,
+                                              T Fy, Uref<T> ur)
 {
-    const T Fx = gxf + fix_to_real<T>(fx);
-    const T Fy = fix_to_real<T>(fy);
     const T drho = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7])) + s[8];
     const T jx = (s[1] - s[3]) + (s[5] - s[6]) + (s[8] - s[7]);
     const T jy = (s[2] - s[4]) + (s[5] + s[6]) - (s[7] + s[8]);
     const T irho = T(1) / (T(1) + drho);
     P.drho[i] = drho;
-    P.ux[i] = (ur + (jx + T(0.5) * Fx)) * irho;
+    P.ux[i] = ur.plus(jx + T(0.5) * Fx) * irho;
     P.uy[i] = (jy + T(0.5) * Fy) * irho;
 }
 
 // Lattice coordinate ref + off on a periodic axis of n nodes.  The reference
 // point (64-bit, unwrapped) is reduced once per call site with wrap_ref; each
 // coordinate then takes an add and at most one correction while |off| < n, and
-// the remainder only beyond that.  (A 64-bit remainder is a long software
-// sequence on the GPU.)
+// the remainder only beyond that.
 __device__ __forceinline__ int wrap_ref(long long ref, int n)
 {
-    const long long r = ref % n;
-    return (int)(r < 0 ? r + n : r);
+    // the quotient in FP64 (off by one at most for |ref| < 2^50), the remainder exact
+    const long long r = ref - (long long)floor((double)ref * (1.0 / n)) * n;
+    return (int)(r < 0 ? r + n : (r >= n ? r - n : r));
 }
 
 __device__ __forceinline__ int wrap_add(int base, int off, int n)
 {
     int v = base + off;
-    if (v < 0) v += n;
-    else if (v >= n) v -= n;
-    if ((unsigned)v >= (unsigned)n) v = wrap_ref(v, n);
+#pragma unroll 1
+    while ((unsigned)v >= (unsigned)n) v += v < 0 ? n : -n;
     return v;
 }
 
-// K patch cells first, first + stride, ..., with the loads of all of them
-// issued before any is used (one memory latency for K cells).  A cell on a
-// wall row or an open end column is marked NaN; cells past the patch store
-// nothing (both load lattice cell (1, 1) instead).  A staged cell is never on
-// a wall row or an end column, so its pull (the nine source addresses of the
-// grid kernel's pull) needs no boundary rule.
-template <typename T, int K>
-__device__ __forceinline__ void stage_cells(const IBArgs<T>& a, const GridArgs& g,
-                                            const Patch<T>& P, long long refx, long long refy,
-                                            T gxf, int first, int stride)
+// Raw buffer access: a scalar base and offset per row and plane, one 32-bit
+// offset per lane; an offset past the end reads 0 and stores nothing, so a lane
+// without a cell needs no branch (kNoCell).  Streaming loads and stores as
+// ld_stream, st_stream (aux 2: non-temporal).
+constexpr unsigned kNoCell = 0xffffffffu;
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, unsigned bytes)
 {
-    const int ncell = P.W * P.H;
-    const size_t plane = (size_t)g.ny * g.nxp;
-    const int bx = g.periodic_x ? wrap_ref(refx + P.ox, g.nx) : 0;
-    const int by = g.periodic_y ? wrap_ref(refy + P.oy, g.ny) : 0;
-    // patch column and row of cell `first`, advanced by `stride` per k
-    int lx = first % P.W, ly = first / P.W;
-    const int sx = stride % P.W, sy = stride / P.W;
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00027000);
+}
+
+template <int AUX, typename T>
+__device__ __forceinline__ void buf_load(__amdgpu_buffer_rsrc_t r, unsigned v, unsigned s, T& out)
+{
+    if constexpr (sizeof(T) == 4) {
+        out = __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, (int)v, (int)s, AUX));
+    } else {
+        out = __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, (int)v, (int)s, AUX));
+    }
+}
+
+template <int AUX, typename T>
+__device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t r, unsigned v, unsigned s, T x)
+{
+    if constexpr (sizeof(T) == 4) {
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, x), r, (int)v, (int)s, AUX);
+    } else {
+        typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, x), r, (int)v, (int)s, AUX);
+    }
+}
+
+// ---- staging of a capsule's patch
+// Where a patch lies and what its cells are read from.  Staging is the
+// instruction stream of one or two waves per SIMD (each issues at most one
+// instruction in four cycles), so it is written for few instructions: one 32-bit
+// offset addresses the nine loads of a cell (raw buffers, the neighbour and
+// plane offsets in scalars), no integer division, and the force is converted only
+// where it is not zero.  Cells that need another rule than "load the nine
+// neighbours" (beside a periodic wrap, on a wall or an end column) are left to a
+// second loop that most patches skip.
+template <typename T>
+struct PatchGeo {
+    const T* src;          // populations of the lattice
+    const long long* fib;  // its force level
+    T* post;               // k_step: post-collision values, [9][cells of a band with its ring]
+    int W, H, RW;          // patch size, ring width
+    int by0, rows;         // k_step: first patch row and rows of the band
+    int bx, by;            // lattice coordinates of the patch origin, wrapped on periodic axes
+    float inv_rw, inv_w;
+    T gx, om, uc, c3;      // body force, 1 / tau, storage reference (uref_at, add_pull_offsets)
+    bool plain;            // every cell of the patch and its ring takes the nine plain loads
+    bool far_offsets;      // the lattice is past the 32-bit offsets: no plain loads
+};
+
+// (wx, wy): lattice coordinates of the reference point (CapsuleDev).
+template <typename T>
+__device__ __forceinline__ void set_geo(PatchGeo<T>& Q, const Patch<T>& P, const GridArgs& g,
+                                        const T* src, const long long* fib, int wx, int wy)
+{
+    Q.src = src;
+    Q.fib = fib;
+    Q.W = P.W;
+    Q.H = P.H;
+    Q.RW = P.W + 2;
+    Q.inv_w = 1.0f / (float)P.W;
+    Q.inv_rw = 1.0f / (float)Q.RW;
+    Q.by0 = 0;
+    Q.rows = P.H;
+    Q.bx = g.periodic_x ? wrap_add(wx, P.ox, g.nx) : wx + P.ox;
+    Q.by = g.periodic_y ? wrap_add(wy, P.oy, g.ny) : wy + P.oy;
+    Q.gx = (T)g.gx;
+    Q.om = (T)g.omega;
+    Q.uc = (T)g.uref_c;
+    Q.c3 = (T)((double)FirstOrderW<T>::diag * g.uref_c);
+    Q.far_offsets = (unsigned long long)g.ny * (unsigned)g.nxp >= 0xfffff000u / (9 * sizeof(T)) ||
+                    (unsigned long long)g.ny * (unsigned)g.nxp >= 0xfffff000u / 16;
+    Q.plain = !Q.far_offsets && Q.bx >= 2 && Q.bx + P.W <= g.nx - 2 && Q.by >= 2 &&
+              Q.by + P.H <= g.ny - 2;
+}
+
+// Row i / width of item i (width = 1 / inv): exact, as (i + 1/2) / width is at
+// least 1 / (2 width) from the next integer and a patch has under 2^14 cells.
+__device__ __forceinline__ int row_of(int i, float inv)
+{
+    return (int)(((float)i + 0.5f) * inv);
+}
+
+// Lattice coordinates of patch column lx (-1 .. W) and row ly (-1 .. H); false
+// if off the lattice.
+template <typename T>
+__device__ __forceinline__ bool patch_cell(const PatchGeo<T>& Q, const GridArgs& g, int lx, int ly,
+                                           int& x, int& y)
+{
+    bool on = true;
+    if (g.periodic_y) {
+        y = wrap_add(Q.by, ly, g.ny);
+    } else {
+        y = Q.by + ly;
+        on = y >= 0 && y < g.ny;
+    }
+    if (g.periodic_x) {
+        x = wrap_add(Q.bx, lx, g.nx);
+    } else {
+        x = Q.bx + lx;
+        on = on && x >= 0 && x < g.nx;
+    }
+    return on;
+}
+
+template <typename T>
+__device__ __forceinline__ Uref<T> ref_at(const PatchGeo<T>& Q, const GridArgs& g, int y)
+{
+    return {Q.uc, (T)(y * (g.ny - 1 - y))};
+}
+
+template <typename T>
+__device__ __forceinline__ void ref_offsets(const PatchGeo<T>& Q, const GridArgs& g, int y,
+                                            T (&s)[9])
+{
+    const T dm = Q.c3 * (T)(2 * y - g.ny);
+    const T dp = Q.c3 * (T)(g.ny - 2 - 2 * y);
+    s[5] += dm;
+    s[6] -= dm;
+    s[7] -= dp;
+    s[8] += dp;
+}
+
+// Collides ring cell i (ring column lx, band row ly) at lattice row y from its
+// pulled populations and keeps the result; a patch cell's force is left in its
+// (ux, uy) slots for the moments.
+template <typename T>
+__device__ __forceinline__ void collide_ring_cell(const PatchGeo<T>& Q, const GridArgs& g,
+                                                  const Patch<T>& P, int i, int lx, int ly, int y,
+                                                  const T (&s)[9], T Fx, T Fy)
+{
+    T o[9];
+    collide(s, ref_at(Q, g, y), Q.om, Fx, Fy, o);
+    const int nring = Q.RW * (Q.rows + 2);
+    T* p = Q.post + i;
+#pragma unroll
+    for (int q = 0; q < 9; q++) p[q * nring] = o[q];
+    if (lx >= 1 && lx <= Q.W && ly >= 1 && ly <= Q.rows) {
+        const int pi = (Q.by0 + ly - 1) * Q.W + lx - 1;
+        P.ux[pi] = Fx;
+        P.uy[pi] = Fy;
+    }
+}
+
+// Whether the nine sources of a cell are its plain neighbours.
+__device__ __forceinline__ bool plain_cell(const GridArgs& g, int x, int y)
+{
+    return (unsigned)(x - 1) < (unsigned)(g.nx - 2) && (unsigned)(y - 1) < (unsigned)(g.ny - 2);
+}
+
+// The nine plain loads of lattice cell `cell` (kNoCell: none) and its force.
+template <typename T>
+struct PlainLoads {
+    __amdgpu_buffer_rsrc_t in, ff;
+    unsigned row, plane;
+    __device__ __forceinline__ PlainLoads(const PatchGeo<T>& Q, const GridArgs& g)
+    {
+        row = (unsigned)g.nxp * sizeof(T);
+        plane = (unsigned)g.ny * row;
+        in = buffer_of(Q.src, 9 * plane);
+        ff = buffer_of(Q.fib, 16u * (unsigned)g.ny * (unsigned)g.nxp);
+    }
+    __device__ __forceinline__ void operator()(unsigned cell, bool on, T (&s)[9], long long& fx,
+                                               long long& fy) const
+    {
+        const unsigned v = on ? cell * (unsigned)sizeof(T) : kNoCell;
+        buf_load<0>(in, v, 0, s[0]);
+        buf_load<0>(in, v, plane - sizeof(T), s[1]);
+        buf_load<0>(in, v, 2 * plane - row, s[2]);
+        buf_load<0>(in, v, 3 * plane + sizeof(T), s[3]);
+        buf_load<0>(in, v, 4 * plane + row, s[4]);
+        buf_load<0>(in, v, 5 * plane - row - sizeof(T), s[5]);
+        buf_load<0>(in, v, 6 * plane - row + sizeof(T), s[6]);
+        buf_load<0>(in, v, 7 * plane + row + sizeof(T), s[7]);
+        buf_load<0>(in, v, 8 * plane + row - sizeof(T), s[8]);
+        const unsigned vf = on ? cell * 16u : kNoCell;
+        buf_load<0>(ff, vf, 0, fx);
+        buf_load<0>(ff, vf, 8, fy);
+    }
+};
+
+// Whether the patch cell (x, y) carries moments (not on a wall or an end column).
+__device__ __forceinline__ bool has_moments(const GridArgs& g, int x, int y)
+{
+    return (g.periodic_y || (unsigned)(y - 1) < (unsigned)(g.ny - 2)) &&
+           (g.periodic_x || (unsigned)(x - 1) < (unsigned)(g.nx - 2));
+}
+
+// Total force of a cell from its level's values.
+template <typename T>
+__device__ __forceinline__ void cell_force(T gx, long long fx, long long fy, T& Fx, T& Fy)
+{
+    Fx = gx;
+    Fy = T(0);
+    if ((fx | fy) != 0) {
+        Fx += fix_to_real<T>(fx);
+        Fy += fix_to_real<T>(fy);
+    }
+}
+
+// The plain patch cells among first, first + stride, ... (K of them, below
+// `end`): loads of all in flight together, then their moments.
+template <typename T, int K>
+__device__ __forceinline__ void stage_cells(const PatchGeo<T>& Q, const GridArgs& g,
+                                            const Patch<T>& P, int first, int stride, int end)
+{
+    const PlainLoads<T> load(Q, g);
     T s[K][9];
     long long fx[K], fy[K];
-    int state[K];  // 0: past the patch, 1: off the lattice, 2: staged
-    int row[K];
+    int ys[K];
+    bool on[K];
 #pragma unroll
     for (int k = 0; k < K; k++) {
         const int i = first + k * stride;
-        int x = 1, y = 1;
-        state[k] = 0;
-        if (i < ncell) {
-            bool on = true;
-            int wy, wx;
-            if (g.periodic_y) {
-                wy = wrap_add(by, ly, g.ny);
-            } else {
-                const long long v = refy + P.oy + ly;
-                on = v >= 1 && v <= g.ny - 2;
-                wy = (int)v;
-            }
-            if (g.periodic_x) {
-                wx = wrap_add(bx, lx, g.nx);
-            } else {
-                const long long v = refx + P.ox + lx;
-                on = on && v >= 1 && v <= g.nx - 2;
-                wx = (int)v;
-            }
-            state[k] = on ? 2 : 1;
-            if (on) {
-                x = wx;
-                y = wy;
-            }
-        }
-        lx += sx;
-        ly += sy;
-        if (lx >= P.W) {
-            lx -= P.W;
-            ly++;
-        }
-        const int xm = x == 0 ? g.nx - 1 : x - 1, xp = x == g.nx - 1 ? 0 : x + 1;
-        const int ym = y == 0 ? g.ny - 1 : y - 1, yp = y == g.ny - 1 ? 0 : y + 1;
-        const size_t r0 = (size_t)y * g.nxp, rm = (size_t)ym * g.nxp, rp = (size_t)yp * g.nxp;
-        const T* src = a.pops;
-        s[k][0] = src[r0 + x];
-        s[k][1] = src[plane + r0 + xm];
-        s[k][2] = src[2 * plane + rm + x];
-        s[k][3] = src[3 * plane + r0 + xp];
-        s[k][4] = src[4 * plane + rp + x];
-        s[k][5] = src[5 * plane + rm + xm];
-        s[k][6] = src[6 * plane + rm + xp];
-        s[k][7] = src[7 * plane + rp + xp];
-        s[k][8] = src[8 * plane + rp + xm];
-        row[k] = y;
-        const longlong2 f = *reinterpret_cast<const longlong2*>(a.fib_prev + 2 * (r0 + x));
-        fx[k] = f.x;
-        fy[k] = f.y;
+        const int ly = row_of(i, Q.inv_w), lx = i - ly * Q.W;
+        int x, y;
+        on[k] = patch_cell(Q, g, lx, ly, x, y) && i < end && plain_cell(g, x, y) && !Q.far_offsets;
+        ys[k] = y;
+        load((unsigned)y * (unsigned)g.nxp + (unsigned)x, on[k], s[k], fx[k], fy[k]);
     }
 #pragma unroll
     for (int k = 0; k < K; k++) {
-        const int i = first + k * stride;
-        if (state[k] == 2) {
-            add_pull_offsets(g, row[k], s[k]);
-            stage_store(P, i, s[k], fx[k], fy[k], gxf, uref_at<T>(g, row[k]));
-        } else if (state[k] == 1) {
+        if (!on[k]) continue;
+        T Fx, Fy;
+        cell_force(Q.gx, fx[k], fy[k], Fx, Fy);
+        ref_offsets(Q, g, ys[k], s[k]);
+        stage_moments(P, first + k * stride, s[k], Fx, Fy, ref_at(Q, g, ys[k]));
+    }
+}
+
+// The other patch cells: NaN on a wall row or an end column, else pulled with
+// the wrap.
+template <typename T>
+__device__ void stage_other_cells(const PatchGeo<T>& Q, const GridArgs& g, const Patch<T>& P)
+{
+    if (Q.plain) return;
+    for (int i = threadIdx.x; i < Q.W * Q.H; i += blockDim.x) {
+        const int ly = row_of(i, Q.inv_w), lx = i - ly * Q.W;
+        int x, y;
+        if (!patch_cell(Q, g, lx, ly, x, y) || !has_moments(g, x, y)) {
             P.drho[i] = P.ux[i] = P.uy[i] = T(NAN);
+            continue;
         }
+        if (plain_cell(g, x, y) && !Q.far_offsets) continue;
+        T s[9], Fx, Fy;
+        pull_loads<T, true, false>(Q.src, x, y, g, s);
+        const longlong2 f = *reinterpret_cast<const longlong2*>(Q.fib + 2 * ((size_t)y * g.nxp + x));
+        cell_force(Q.gx, f.x, f.y, Fx, Fy);
+        stage_moments(P, i, s, Fx, Fy, ref_at(Q, g, y));
+    }
+}
+
+// ---- the patch's own grid step (k_step)
+// The patch moments of time n + 1 from the populations P^n and the force F^n of
+// the collision in between: the post-collision values of the patch and a ring
+// of one cell, computed here as the grid pass of the same launch computes them
+// (the same functions, so the same bits), go to LDS, and the patch cells pull
+// from there.  Patch rows are taken in bands that fit the LDS left.
+
+// The plain ring cells among first, first + stride, ... (K of them, below `end`)
+// of the band: loads of all in flight together, then collide.
+template <typename T, int K>
+__device__ __forceinline__ void step_cells(const PatchGeo<T>& Q, const GridArgs& g,
+                                           const Patch<T>& P, int first, int stride, int end)
+{
+    const PlainLoads<T> load(Q, g);
+    T s[K][9];
+    long long fx[K], fy[K];
+    int lxs[K], lys[K], ys[K];
+    bool on[K];
+#pragma unroll
+    for (int k = 0; k < K; k++) {
+        const int i = first + k * stride;
+        lys[k] = row_of(i, Q.inv_rw);
+        lxs[k] = i - lys[k] * Q.RW;
+        int x, y;
+        on[k] = patch_cell(Q, g, lxs[k] - 1, Q.by0 + lys[k] - 1, x, y) && i < end &&
+                plain_cell(g, x, y);
+        ys[k] = y;
+        load((unsigned)y * (unsigned)g.nxp + (unsigned)x, on[k], s[k], fx[k], fy[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < K; k++) {
+        if (!on[k]) continue;
+        T Fx, Fy;
+        cell_force(Q.gx, fx[k], fy[k], Fx, Fy);
+        ref_offsets(Q, g, ys[k], s[k]);
+        collide_ring_cell(Q, g, P, first + k * stride, lxs[k], lys[k], ys[k], s[k], Fx, Fy);
+    }
+}
+
+// The band's other ring cells.
+template <typename T>
+__device__ void step_other_cells(const PatchGeo<T>& Q, const GridArgs& g, const Patch<T>& P)
+{
+    if (Q.plain) return;
+    for (int i = threadIdx.x; i < Q.RW * (Q.rows + 2); i += blockDim.x) {
+        const int ly = row_of(i, Q.inv_rw), lx = i - ly * Q.RW;
+        int x, y;
+        if (!patch_cell(Q, g, lx - 1, Q.by0 + ly - 1, x, y) || plain_cell(g, x, y)) continue;
+        const longlong2 f = *reinterpret_cast<const longlong2*>(Q.fib + 2 * ((size_t)y * g.nxp + x));
+        T s[9], Fx, Fy;
+        cell_force(Q.gx, f.x, f.y, Fx, Fy);
+        pull<T, true>(Q.src, x, y, g, Fx, s);
+        collide_ring_cell(Q, g, P, i, lx, ly, y, s, Fx, Fy);
+    }
+}
+
+// Moments of the band's patch cells from their neighbours' post-collision
+// values in LDS.
+template <typename T>
+__device__ __forceinline__ void step_moments(const PatchGeo<T>& Q, const GridArgs& g,
+                                             const Patch<T>& P)
+{
+    constexpr int K = 2;
+    const int nring = Q.RW * (Q.rows + 2), n = Q.W * Q.rows, nt = blockDim.x;
+    for (int i0 = threadIdx.x; i0 < n; i0 += K * nt) {
+        T s[K][9], Fx[K], Fy[K];
+        int ys[K], state[K];  // 0: past the band, 1: no moments, 2: moments
+#pragma unroll
+        for (int k = 0; k < K; k++) {
+            const int i = i0 + k * nt < n ? i0 + k * nt : i0;
+            const int ly = row_of(i, Q.inv_w), lx = i - ly * Q.W;
+            int x, y;
+            const bool on = patch_cell(Q, g, lx, Q.by0 + ly, x, y) && has_moments(g, x, y);
+            state[k] = i0 + k * nt < n ? (on ? 2 : 1) : 0;
+            ys[k] = y;
+            const T* c = Q.post + (ly + 1) * Q.RW + lx + 1;
+#pragma unroll
+            for (int q = 0; q < 9; q++) s[k][q] = c[q * nring - kEy[q] * Q.RW - kEx[q]];
+            Fx[k] = P.ux[Q.by0 * Q.W + i];
+            Fy[k] = P.uy[Q.by0 * Q.W + i];
+        }
+#pragma unroll
+        for (int k = 0; k < K; k++) {
+            const int pi = Q.by0 * Q.W + i0 + k * nt;
+            if (state[k] == 2) {
+                ref_offsets(Q, g, ys[k], s[k]);
+                stage_moments(P, pi, s[k], Fx[k], Fy[k], ref_at(Q, g, ys[k]));
+            } else if (state[k] == 1) {
+                P.drho[pi] = P.ux[pi] = P.uy[pi] = T(NAN);
+            }
+        }
+    }
+}
+
+// A patch so wide that no row of it fits beside its moments (or a lattice past
+// the 32-bit offsets): every cell computes its nine neighbours' collisions.
+template <typename T>
+__device__ void step_cells_direct(const PatchGeo<T>& Q, const GridArgs& g, const Patch<T>& P)
+{
+    for (int pi = threadIdx.x; pi < Q.W * Q.H; pi += blockDim.x) {
+        const int py = row_of(pi, Q.inv_w), px = pi - py * Q.W;
+        int x, y;
+        if (!patch_cell(Q, g, px, py, x, y) || !has_moments(g, x, y)) {
+            P.drho[pi] = P.ux[pi] = P.uy[pi] = T(NAN);
+            continue;
+        }
+        T s[9] = {}, Fx0 = 0, Fy0 = 0;
+#pragma unroll 1
+        for (int q = 0; q < 9; q++) {
+            const int ex = q == 0 ? 0 : (q < 5 ? (q & 1 ? 2 - q : 0) : (q == 5 || q == 8 ? 1 : -1));
+            const int ey = q == 0 ? 0 : (q < 5 ? (q & 1 ? 0 : 3 - q) : (q < 7 ? 1 : -1));
+            int xn, yn;
+            patch_cell(Q, g, px - ex, py - ey, xn, yn);
+            const longlong2 f =
+                *reinterpret_cast<const longlong2*>(Q.fib + 2 * ((size_t)yn * g.nxp + xn));
+            T t[9], o[9], Fx, Fy;
+            cell_force(Q.gx, f.x, f.y, Fx, Fy);
+            pull<T, true>(Q.src, xn, yn, g, Fx, t);
+            collide(t, ref_at(Q, g, yn), Q.om, Fx, Fy, o);
+            Fx0 = q == 0 ? Fx : Fx0;
+            Fy0 = q == 0 ? Fy : Fy0;
+#pragma unroll
+            for (int i = 0; i < 9; i++) s[i] = i == q ? o[i] : s[i];
+        }
+        ref_offsets(Q, g, y, s);
+        stage_moments(P, pi, s, Fx0, Fy0, ref_at(Q, g, y));
     }
 }
 
@@ -562,6 +894,24 @@ __device__ __forceinline__ float wave_extreme(float v)
 // kIBThreads / 64): a DPP reduction within each wave, then the wave partials in
 // order.
 
+// Lane l of every wave holds partial l % 8 of group l / 8 (value k of wave w at
+// l = 8 k + w): the combination within groups of eight lanes.
+template <typename F>
+__device__ __forceinline__ double combine8(double v, F&& op)
+{
+    v = op(v, dpp_move_f64<0xB1, 0xF>(v));   // quad_perm [1, 0, 3, 2]
+    v = op(v, dpp_move_f64<0x4E, 0xF>(v));   // quad_perm [2, 3, 0, 1]
+    return op(v, dpp_move_f64<0x141, 0xF>(v));  // row_half_mirror
+}
+
+__device__ __forceinline__ double lane_value(double v, int lane)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)(unsigned int)(b & 0xffffffffLL), lane);
+    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned int)lo);
+}
+
 template <int N>
 __device__ __forceinline__ void block_sum(double (&v)[N], double (*red)[8])
 {
@@ -572,41 +922,39 @@ __device__ __forceinline__ void block_sum(double (&v)[N], double (*red)[8])
 #pragma unroll
         for (int k = 0; k < N; k++) red[wave][k] = v[k];
     __syncthreads();
-    const int nw = (int)(blockDim.x >> 6);
+    const bool has = (lane & 7) < (int)(blockDim.x >> 6);
+    const double t = combine8(has ? red[lane & 7][lane >> 3] : 0.0,
+                              [](double a, double b) { return a + b; });
 #pragma unroll
-    for (int k = 0; k < N; k++) {
-        double acc = red[0][k];
-        for (int w = 1; w < nw; w++) acc += red[w][k];
-        v[k] = acc;
-    }
+    for (int k = 0; k < N; k++) v[k] = lane_value(t, 8 * k);
     __syncthreads();
 }
 
+// Minima and maxima of two coordinates: the maxima go through as minima of the
+// negated values.
 __device__ __forceinline__ void block_minmax(float (&mn)[2], float (&mx)[2], double (*red)[8],
                                              bool closing_barrier = true)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int k = 0; k < 2; k++) {
-        mn[k] = wave_extreme<false>(mn[k]);
-        mx[k] = wave_extreme<true>(mx[k]);
-    }
+    float* r = reinterpret_cast<float*>(red);  // [wave][16], four used
+    float m[4] = {mn[0], mn[1], -mx[0], -mx[1]};
+#pragma unroll
+    for (int k = 0; k < 4; k++) m[k] = wave_extreme<false>(m[k]);
     if (lane == 0) {
-        red[wave][0] = mn[0];
-        red[wave][1] = mn[1];
-        red[wave][2] = mx[0];
-        red[wave][3] = mx[1];
+#pragma unroll
+        for (int k = 0; k < 4; k++) r[16 * wave + k] = m[k];
     }
     __syncthreads();
-    const int nw = (int)(blockDim.x >> 6);
-    for (int k = 0; k < 2; k++) {
-        float a = (float)red[0][k], b = (float)red[0][2 + k];
-        for (int w = 1; w < nw; w++) {
-            a = fminf(a, (float)red[w][k]);
-            b = fmaxf(b, (float)red[w][2 + k]);
-        }
-        mn[k] = a;
-        mx[k] = b;
-    }
+    const bool has = (lane & 7) < (int)(blockDim.x >> 6);
+    float t = has ? r[16 * (lane & 7) + ((lane >> 3) & 3)] : 3e38f;
+    t = fminf(t, dpp_move_f32<0xB1, 0xF>(t));
+    t = fminf(t, dpp_move_f32<0x4E, 0xF>(t));
+    t = fminf(t, dpp_move_f32<0x141, 0xF>(t));
+    auto at = [&](int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), l)); };
+    mn[0] = at(0);
+    mn[1] = at(8);
+    mx[0] = -at(16);
+    mx[1] = -at(24);
     if (closing_barrier) __syncthreads();
 }
 

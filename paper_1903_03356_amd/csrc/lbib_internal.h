@@ -12,6 +12,7 @@ constexpr double kPlainStoreMaxBytes = 384.0 * (1 << 20);  // single pass: plain
 constexpr double kTwoMinBytes = 16.0 * (1 << 20);  // two steps in one pass: populations from here
 constexpr int kGridRowsPerThread = 1;  // grid kernel: nodes per thread, 4 rows apart
 constexpr int kNumXcd = 8;       // MI355X: workgroups are dealt round-robin to 8 XCDs
+constexpr int kStepRows = 2;     // k_step: rows per wave of its grid blocks
 constexpr int kIBThreads = 512;  // IB kernel block (one block per capsule)
 // per-node arrays in the IB kernel's LDS: positions (4), node state (8) and
 // work arrays (kNodeScratch)
@@ -81,16 +82,23 @@ struct CapsuleDev {
     int64_t pop_off, fib_off, flag_off;
     double gx, nu;
     double uref_c;  // reference profile of the lattice's stored populations (GridArgs)
+    double omega, u_bot, u_top, u_in, rho_out;  // for the patch's own grid step (k_step)
     // rigid particle (Sec. 2.3.1): nodes x_v = X + R(theta) r0_v
-    int32_t rigid, pad2;
+    int32_t rigid;
+    int32_t pad2;
+    int32_t wx, wy;  // lattice coordinates of the reference point, wrapped on periodic axes
     double rX, rY, rth;        // centroid (world coordinates) and angle
     double ru[2], rum1[2];     // velocity at n and n-1 (Eq. 19)
     double rw, rwm1;           // angular velocity at n and n-1 (Eq. 20)
     double rI, rm;             // moment of inertia about the centroid, mass
     double rF[2], rM;          // last hydrodynamic (+ contact) force and torque (Eqs. 17-18)
-    double pad3;
 };
-static_assert(sizeof(CapsuleDev) == 272, "CapsuleDev layout");
+static_assert(sizeof(CapsuleDev) == 312, "CapsuleDev layout");
+
+// Time levels of the force field: that of the last collision, that of the
+// coming one, and a spare one for the schedules that spread the forcing of the
+// next step while the grid still reads this step's (k_step).
+constexpr int kForceLevels = 3;
 
 constexpr int kDiagStride = 16;  // doubles per capsule in BUF_DIAG
 
@@ -231,6 +239,11 @@ int grid_tiles_linear(int ny, int nseg, int rows);
 template <typename T>
 hipError_t launch_ib(const IBArgs<T>& a, int ncap, size_t lds_bytes, hipStream_t s,
                      bool wide);
+// One launch for grid step n and the IB work of step n + 1 (see k_step).
+template <typename T>
+hipError_t launch_step(const IBArgs<T>& a, int ncap, bool rigid, size_t lds_bytes, const T* src, T* dst,
+                       const long long* fib_now, const int* flags_now, long long* fib_old,
+                       int* flags_old, const GridArgs& g, hipStream_t s);
 template <typename T>
 size_t ib_lds_bytes(int patch_cap, int max_nv);
 template <typename T>

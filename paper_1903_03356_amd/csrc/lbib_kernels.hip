@@ -318,38 +318,6 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// Raw buffer access: a scalar base and offset per row and plane, one 32-bit
-// offset per lane; an offset past the end reads 0 and stores nothing, so a lane
-// without a cell needs no branch (kNoCell).  Streaming loads and stores as
-// ld_stream, st_stream (aux 2: non-temporal).
-constexpr unsigned kNoCell = 0xffffffffu;
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, unsigned bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00027000);
-}
-
-template <int AUX, typename T>
-__device__ __forceinline__ void buf_load(__amdgpu_buffer_rsrc_t r, unsigned v, unsigned s, T& out)
-{
-    if constexpr (sizeof(T) == 4) {
-        out = __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, (int)v, (int)s, AUX));
-    } else {
-        out = __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, (int)v, (int)s, AUX));
-    }
-}
-
-template <int AUX, typename T>
-__device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t r, unsigned v, unsigned s, T x)
-{
-    if constexpr (sizeof(T) == 4) {
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, x), r, (int)v, (int)s, AUX);
-    } else {
-        typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, x), r, (int)v, (int)s, AUX);
-    }
-}
-
 // Two time steps of a lattice without an IB force (periodic in x) in one pass:
 // P^n is read and P^{n+2} written, 36 bytes a cell and step in FP32 where two
 // single passes move 72.  A block takes `cols` columns (a multiple of a cache
@@ -400,7 +368,7 @@ __global__ __launch_bounds__(kTwoMaxThreads) void k_grid_two(const T* __restrict
         s[7] -= dp;
         s[8] += dp;
     };
-    auto uref = [&](int y) { return uc * (T)(y * (g.ny - 1 - y)); };
+    auto uref = [&](int y) -> Uref<T> { return {uc, (T)(y * (g.ny - 1 - y))}; };
     const unsigned row = (unsigned)g.nxp * sizeof(T), plane = (unsigned)g.ny * row;
     const bool py = g.periodic_y;
     const int top = g.ny - 1;
@@ -1231,21 +1199,10 @@ __device__ __forceinline__ long long to_fix(T v, int& st)
 // One spreading contribution (Dynamic step 3, Kinematic step iii): the value
 // (vx, vy) = c phi_k F goes to support node k of the 3x3 support centred on
 // (cx, cy), relative to the reference point.
-// (bx, by): the reference point reduced onto periodic axes (wrap_ref).
+// (bx, by): the reference point's lattice coordinates (CapsuleDev wx, wy).
 struct SpreadRef {
-    long long rx, ry;
     int bx, by;
 };
-
-__device__ __forceinline__ SpreadRef spread_ref(const GridArgs& g, long long refx, long long refy)
-{
-    SpreadRef r;
-    r.rx = refx;
-    r.ry = refy;
-    r.bx = g.periodic_x ? wrap_ref(refx, g.nx) : 0;
-    r.by = g.periodic_y ? wrap_ref(refy, g.ny) : 0;
-    return r;
-}
 
 template <typename T>
 __device__ __forceinline__ void spread_one(const IBArgs<T>& a, const GridArgs& g,
@@ -1256,16 +1213,14 @@ __device__ __forceinline__ void spread_one(const IBArgs<T>& a, const GridArgs& g
     if (g.periodic_y) {
         gy = wrap_add(r.by, cy + k / 3 - 1, g.ny);
     } else {
-        const long long v = r.ry + cy + k / 3 - 1;
-        if (v < 1 || v > g.ny - 2) { st |= ST_WALL; return; }
-        gy = (int)v;
+        gy = r.by + cy + k / 3 - 1;
+        if (gy < 1 || gy > g.ny - 2) { st |= ST_WALL; return; }
     }
     if (g.periodic_x) {
         gx = wrap_add(r.bx, cx + k % 3 - 1, g.nx);
     } else {
-        const long long v = r.rx + cx + k % 3 - 1;
-        if (v < 1 || v > g.nx - 2) { st |= ST_WALL; return; }
-        gx = (int)v;
+        gx = r.bx + cx + k % 3 - 1;
+        if (gx < 1 || gx > g.nx - 2) { st |= ST_WALL; return; }
     }
     const long long fx = to_fix(vx, st), fy = to_fix(vy, st);
     const size_t cell = (size_t)gy * g.nxp + (size_t)gx;
@@ -1292,12 +1247,11 @@ __device__ __forceinline__ void cache_weights(const Scratch<T>& S, int v, int cx
 // item per (node, support node).
 template <typename T>
 __device__ __forceinline__ void spread_cached(const IBArgs<T>& a, const GridArgs& g,
-                                              const Scratch<T>& S, int nv, long long refx,
-                                              long long refy, int& st)
+                                              const Scratch<T>& S, int nv, const SpreadRef& r,
+                                              int& st)
 {
     const T* base = S.t[0];
     const size_t stride = S.t[1] - S.t[0];  // the scratch arrays are contiguous
-    const SpreadRef r = spread_ref(g, refx, refy);
     for (int w = threadIdx.x; w < 9 * nv; w += blockDim.x) {
         const int v = w / 9, k = w - 9 * v;
         const T phi = base[(size_t)(k < 8 ? k : 12) * stride + v];
@@ -1313,57 +1267,69 @@ __device__ __forceinline__ void spread_cached(const IBArgs<T>& a, const GridArgs
 // pair of global atomics and raises its segment flag.  The sums take the
 // patch arrays (dead once the forcing has interpolated); the caller checks
 // that 20 bytes per patch cell fit there.  A contribution outside the box
-// goes straight to the level.
+// goes straight to the level.  One work item per (node, row of its support).  A
+// box inside the lattice (Q.plain) needs no test for walls and no wrap.
+// The sums are zero on entry (clear_sums, a barrier ago).
+__device__ __forceinline__ int spread_bytes(int ncell) { return (20 * ncell + 15) & ~15; }
+
+__device__ __forceinline__ void clear_sums(unsigned char* sums, int ncell)
+{
+    uint4* z = reinterpret_cast<uint4*>(sums);
+    for (int i = threadIdx.x; i < spread_bytes(ncell) / 16; i += blockDim.x)
+        z[i] = make_uint4(0, 0, 0, 0);
+}
+
 template <typename T>
 __device__ __forceinline__ void spread_patch(const IBArgs<T>& a, const GridArgs& g,
-                                             const Scratch<T>& S, const Patch<T>& P, int nv,
-                                             long long refx, long long refy, int& st)
+                                             const Scratch<T>& S, const Patch<T>& P,
+                                             const PatchGeo<T>& Q, unsigned char* sums, int nv,
+                                             const SpreadRef& r, int& st)
 {
     const int tid = threadIdx.x, nt = blockDim.x;
     const int ncell = P.W * P.H;
-    unsigned long long* sx = reinterpret_cast<unsigned long long*>(P.drho);
+    unsigned long long* sx = reinterpret_cast<unsigned long long*>(sums);
     unsigned long long* sy = sx + ncell;
     int* touched = reinterpret_cast<int*>(sy + ncell);
-    for (int i = tid; i < ncell; i += nt) {
-        sx[i] = 0;
-        sy[i] = 0;
-        touched[i] = 0;
-    }
-    __syncthreads();
     const T* base = S.t[0];
-    const size_t stride = S.t[1] - S.t[0];  // the scratch arrays are contiguous
-    const SpreadRef r = spread_ref(g, refx, refy);
-    for (int w = tid; w < 9 * nv; w += nt) {
-        const int v = w / 9, k = w - 9 * v;
-        const T phi = base[(size_t)(k < 8 ? k : 12) * stride + v];
+    const int stride = (int)(S.t[1] - S.t[0]);  // the scratch arrays are contiguous
+    for (int w = tid; w < 3 * nv; w += nt) {
+        const int v = (w * 43691) >> 17, row = w - 3 * v;  // w / 3 (w < 2^13)
         const int cx = (int)S.t[10][v], cy = (int)S.t[11][v];
-        const T vx = phi * S.t[8][v], vy = phi * S.t[9][v];
-        int idx;
-        if (!patch_index(P, cx, cy, k, idx)) {
-            spread_one(a, g, r, cx, cy, k, vx, vy, st);
+        const T fx = S.t[8][v], fy = S.t[9][v];
+        const T* phi = base + 3 * row * stride + v;
+        const T p[3] = {phi[0], phi[stride], row == 2 ? base[12 * stride + v] : phi[2 * stride]};
+        const int lx = cx - 1 - P.ox, ly = cy + row - 1 - P.oy;
+        const bool inside = lx >= 0 && lx + 2 < P.W && ly >= 0 && ly < P.H;
+        if (!inside) {
+            for (int i = 0; i < 3; i++)
+                spread_one(a, g, r, cx, cy, 3 * row + i, p[i] * fx, p[i] * fy, st);
             continue;
         }
-        if (!g.periodic_y) {  // walls: as spread_one
-            const long long yv = r.ry + cy + k / 3 - 1;
-            if (yv < 1 || yv > g.ny - 2) { st |= ST_WALL; continue; }
+        if (!Q.plain && !g.periodic_y) {  // walls: as spread_one
+            const int y = r.by + cy + row - 1;
+            if (y < 1 || y > g.ny - 2) { st |= ST_WALL; continue; }
         }
-        if (!g.periodic_x) {
-            const long long xv = r.rx + cx + k % 3 - 1;
-            if (xv < 1 || xv > g.nx - 2) { st |= ST_WALL; continue; }
+        const int i0 = ly * P.W + lx;
+#pragma unroll
+        for (int i = 0; i < 3; i++) {
+            if (!Q.plain && !g.periodic_x) {
+                const int x = r.bx + cx + i - 1;
+                if (x < 1 || x > g.nx - 2) { st |= ST_WALL; continue; }
+            }
+            const long long ix = to_fix(p[i] * fx, st), iy = to_fix(p[i] * fy, st);
+            atomicAdd(&sx[i0 + i], (unsigned long long)ix);
+            atomicAdd(&sy[i0 + i], (unsigned long long)iy);
+            touched[i0 + i] = 1;
         }
-        const long long fx = to_fix(vx, st), fy = to_fix(vy, st);
-        atomicAdd(&sx[idx], (unsigned long long)fx);
-        atomicAdd(&sy[idx], (unsigned long long)fy);
-        touched[idx] = 1;
     }
     __syncthreads();
-    const int bx = g.periodic_x ? wrap_ref(refx + P.ox, g.nx) : 0;
-    const int by = g.periodic_y ? wrap_ref(refy + P.oy, g.ny) : 0;
+    const int bx = g.periodic_x ? wrap_add(r.bx, P.ox, g.nx) : r.bx + P.ox;
+    const int by = g.periodic_y ? wrap_add(r.by, P.oy, g.ny) : r.by + P.oy;
     for (int i = tid; i < ncell; i += nt) {
         if (!touched[i]) continue;
-        const int lx = i % P.W, ly = i / P.W;
-        const int gx = g.periodic_x ? wrap_add(bx, lx, g.nx) : (int)(refx + P.ox + lx);
-        const int gy = g.periodic_y ? wrap_add(by, ly, g.ny) : (int)(refy + P.oy + ly);
+        const int ly = row_of(i, Q.inv_w), lx = i - ly * P.W;
+        const int gx = g.periodic_x ? wrap_add(bx, lx, g.nx) : bx + lx;
+        const int gy = g.periodic_y ? wrap_add(by, ly, g.ny) : by + ly;
         const size_t cell = (size_t)gy * g.nxp + (size_t)gx;
         unsigned long long* dst = reinterpret_cast<unsigned long long*>(a.fib_next + 2 * cell);
         if (sx[i]) atomicAdd(dst, sx[i]);
@@ -1582,7 +1548,13 @@ __device__ void rigid_update(const IBArgs<T>& a, const Scratch<T>& S, const Patc
 //             with c_v = node arc length), Kinematic steps i-iii (internal
 //             forces, c_v = 1)
 //   PH_DIAG   diagnostics of the current shape only
-template <typename T, bool DYN>
+//
+// STEP: the launch also holds grid step n - 1 (k_step): a.pops is P^{n-1}, and
+// the block takes the moments of its patch at time n from its own grid step
+// there (step_cells), not from P^n.
+// Such a launch runs phases B and A of started capsules and no diagnostics,
+// near regions or tape; without rigid particles (RIGID) their code is left out too.
+template <typename T, bool DYN, bool STEP, bool RIGID>
 __device__ __forceinline__ void ib_block(const IBArgs<T>& a0, unsigned char* smem,
                                          double (*red)[8])
 {
@@ -1605,17 +1577,20 @@ __device__ __forceinline__ void ib_block(const IBArgs<T>& a0, unsigned char* sme
     g.nseg = cap.nseg;
     g.periodic_y = cap.periodic_y;
     g.periodic_x = cap.periodic_x;
-    g.omega = 0.0;
+    g.omega = STEP ? cap.omega : 0.0;
     g.gx = cap.gx;
-    g.u_bot = g.u_top = 0.0;  // wall rows and open-channel columns are never staged
-    g.u_in = 0.0;
-    g.rho_out = 1.0;
+    // wall rows and open-channel columns are never staged, but lie in the ring of
+    // the patch's own grid step
+    g.u_bot = STEP ? cap.u_bot : 0.0;
+    g.u_top = STEP ? cap.u_top : 0.0;
+    g.u_in = STEP ? cap.u_in : 0.0;
+    g.rho_out = STEP ? cap.rho_out : 1.0;
     g.uref_c = cap.uref_c;
     const int nv = cap.nv, off = cap.node_offset;
     const size_t NS = a.node_stride;
     T* N = a.nodes;
 
-    if (a.phase == PH_DIAG) {
+    if (!STEP && a.phase == PH_DIAG) {
         diagnostics(a, cap, c, red);
         return;
     }
@@ -1642,48 +1617,73 @@ __device__ __forceinline__ void ib_block(const IBArgs<T>& a0, unsigned char* sme
     for (int k = 0; k < kNodeScratch; k++) S.t[k] = S.th0 + (size_t)(k + 1) * a.max_nv;
 
     int st = 0;
-    const bool prime = (a.phase & PH_PRIME) && !cap.primed;
+    const bool prime = !STEP && (a.phase & PH_PRIME) && !cap.primed;
+    const bool rigid = RIGID && cap.rigid;
     const bool doB = (a.phase & PH_B) && cap.primed;
     const bool doA = (a.phase & PH_A) != 0;
-    long long refx = (long long)cap.ref_x, refy = (long long)cap.ref_y;
+    int wx = cap.wx, wy = cap.wy;
+    const int patch_bytes = 3 * a.patch_cap * (int)sizeof(T);
+    unsigned char* sums = nullptr;
     const bool need_field = prime || doB || (doA && DYN);
-    const T gxf = (T)cap.gx;
 
-    // The patch box of this capsule's last launch: the waves that hold no node
-    // stage it while the node waves load the node state, so that the two
-    // load latencies overlap.  Below, the box the nodes need is checked
-    // against it; the patch is staged again if it does not fit.  (Each cell's
-    // staged values do not depend on the box, so the results do not either.)
-    const int node_threads = (nv + 63) / 64 * 64;
     const int4 hint = need_field ? hint0 : make_int4(0, 0, 0, 0);
-    const bool early = hint.z > 0 && hint.w > 0 && (long long)hint.z * hint.w <= a.patch_cap &&
-                       node_threads < nt;
-    if (early && tid >= node_threads) {
-        P.ox = hint.x;
-        P.oy = hint.y;
-        P.W = hint.z;
-        P.H = hint.w;
-        const int ncell = P.W * P.H, ns = nt - node_threads;
-        for (int i = tid - node_threads; i < ncell; i += 3 * ns)
-            stage_cells<T, 3>(a, g, P, refx, refy, gxf, i, ns);
+    PatchGeo<T> Q;
+    // takes the W x H box at (ox, oy) for the patch; STEP: lays out its moments and
+    // behind them the post-collision values of its own grid step, and returns how
+    // many patch rows fit at a time
+    auto lay_out = [&](int ox, int oy, int W, int H) -> int {
+        P.ox = ox;
+        P.oy = oy;
+        P.W = W;
+        P.H = H;
+        set_geo(Q, P, g, a.pops, a.fib_prev, wx, wy);
+        const int n = W * H;
+        P.ux = P.drho + n;
+        P.uy = P.ux + n;
+        if (STEP) {
+            Q.post = P.uy + n;
+            Q.rows = Q.far_offsets ? 0 : min(H, (3 * a.patch_cap - 3 * n) / (9 * Q.RW) - 2);
+        }
+        return Q.rows;
+    };
+    // The patch box of this capsule's last launch is staged while the node state is
+    // on its way: the node loads go out first, then three cells' loads per thread,
+    // and the wave waits for all of them about once.  Below, the box the nodes need
+    // is checked against it; the patch is staged again if it does not fit.  (Each
+    // cell's staged values do not depend on the box, so the results do not either.)
+    constexpr int NF = 12;
+    const int fields[NF] = {NF_HX, NF_HY, NF_LX, NF_LY, NF_DX, NF_DY,
+                            NF_UX, NF_UY, NF_L0, NF_L0L, NF_KS, NF_TH0};
+    T* const kept[NF] = {S.px, S.py, S.qx, S.qy, S.dx, S.dy, S.ux, S.uy, S.l0, S.l0l, S.ks, S.th0};
+    T nd[NF];
+    if (tid < nv) {
+#pragma unroll
+        for (int f = 0; f < NF; f++) nd[f] = N[fields[f] * NS + off + tid];
+    }
+    bool early = hint.z > 0 && hint.w > 0 && (long long)hint.z * hint.w <= a.patch_cap;
+    if (early) early = lay_out(hint.x, hint.y, hint.z, hint.w) == hint.w;
+    if (early) {
+        // by the waves without nodes where three cells each are enough, else by all
+        const int n = STEP ? Q.RW * (Q.rows + 2) : Q.W * Q.H;
+        const int node_threads = (nv + 63) & ~63;
+        const bool split = n <= 3 * (nt - node_threads);
+        const int stride = split ? nt - node_threads : nt;
+        for (int i = split ? tid - node_threads : tid; i >= 0 && i < n; i += 3 * stride) {
+            if (STEP) step_cells<T, 3>(Q, g, P, i, stride, n);
+            else stage_cells<T, 3>(Q, g, P, i, stride, n);
+        }
     }
 
     float mn[2] = {3e38f, 3e38f}, mxv[2] = {-3e38f, -3e38f};
     bool finite = true;
     for (int v = tid; v < nv; v += nt) {
-        const T x = N[NF_HX * NS + off + v], y = N[NF_HY * NS + off + v];
-        S.px[v] = x;
-        S.py[v] = y;
-        S.qx[v] = N[NF_LX * NS + off + v];
-        S.qy[v] = N[NF_LY * NS + off + v];
-        S.dx[v] = N[NF_DX * NS + off + v];
-        S.dy[v] = N[NF_DY * NS + off + v];
-        S.ux[v] = N[NF_UX * NS + off + v];
-        S.uy[v] = N[NF_UY * NS + off + v];
-        S.l0[v] = N[NF_L0 * NS + off + v];
-        S.l0l[v] = N[NF_L0L * NS + off + v];
-        S.ks[v] = N[NF_KS * NS + off + v];
-        S.th0[v] = N[NF_TH0 * NS + off + v];
+        if (v != tid) {
+#pragma unroll
+            for (int f = 0; f < NF; f++) nd[f] = N[fields[f] * NS + off + v];
+        }
+#pragma unroll
+        for (int f = 0; f < NF; f++) kept[f][v] = nd[f];
+        const T x = nd[0], y = nd[1];
         finite = finite && isfinite(x) && isfinite(y);
         mn[0] = fminf(mn[0], (float)x);
         mn[1] = fminf(mn[1], (float)y);
@@ -1698,7 +1698,7 @@ __device__ __forceinline__ void ib_block(const IBArgs<T>& a0, unsigned char* sme
     // Dynamic node update: the enclosed area of x^n for the membrane forces,
     // as wave partials in red[.][7], summed in wave order (as block_sum) after
     // the staging barrier below
-    const bool dyn_forces = doB && DYN && !cap.rigid;
+    const bool dyn_forces = doB && DYN && !rigid;
     if (dyn_forces) {
         const double acc = wave_sum(area_share(S, nv));
         if ((tid & 63) == 0) red[tid >> 6][7] = acc;
@@ -1720,10 +1720,13 @@ __device__ __forceinline__ void ib_block(const IBArgs<T>& a0, unsigned char* sme
         const int H = (int)floorf(mxv[1]) - (int)floorf(mn[1]) + 7;
         if (early && ox >= hint.x && oy >= hint.y && ox + W <= hint.x + hint.z &&
             oy + H <= hint.y + hint.w) {
-            P.ox = hint.x;
-            P.oy = hint.y;
-            P.W = hint.z;
-            P.H = hint.w;
+            if (STEP) {
+                step_other_cells(Q, g, P);
+                if (!Q.plain) __syncthreads();  // (block_minmax had the barrier for the plain ones)
+                step_moments(Q, g, P);
+            } else {
+                stage_other_cells(Q, g, P);
+            }
         } else {
             if ((long long)W * H > a.patch_cap) {
                 if (tid == 0) atomicOr(a.status, ST_PATCH);
@@ -1732,19 +1735,40 @@ __device__ __forceinline__ void ib_block(const IBArgs<T>& a0, unsigned char* sme
             // one spare cell on every side where it fits, so that the box
             // serves the next launches while the capsule drifts
             const bool spare = (long long)(W + 2) * (H + 2) <= a.patch_cap;
-            P.ox = spare ? ox - 1 : ox;
-            P.oy = spare ? oy - 1 : oy;
-            P.W = spare ? W + 2 : W;
-            P.H = spare ? H + 2 : H;
-            // three cells per thread with all their loads in flight together
-            const int ncell = P.W * P.H;
-            for (int i = tid; i < ncell; i += 3 * nt) stage_cells<T, 3>(a, g, P, refx, refy, gxf, i, nt);
+            const int fit = lay_out(spare ? ox - 1 : ox, spare ? oy - 1 : oy, spare ? W + 2 : W,
+                                    spare ? H + 2 : H);
+            if (!STEP) {
+                // three cells per thread with all their loads in flight together
+                for (int i = tid; i < Q.W * Q.H; i += 3 * nt)
+                    stage_cells<T, 3>(Q, g, P, i, nt, Q.W * Q.H);
+                stage_other_cells(Q, g, P);
+            } else if (fit < 1) {
+                step_cells_direct(Q, g, P);
+            } else {
+                for (; Q.by0 < P.H; Q.by0 += fit) {
+                    Q.rows = min(fit, P.H - Q.by0);
+                    const int nring = Q.RW * (Q.rows + 2);
+                    for (int i = tid; i < nring; i += 3 * nt)
+                        step_cells<T, 3>(Q, g, P, i, nt, nring);
+                    step_other_cells(Q, g, P);
+                    __syncthreads();
+                    step_moments(Q, g, P);
+                    __syncthreads();
+                }
+            }
         }
         __syncthreads();
+        // the spreading's sums behind the moments, where both fit: cleared here, so
+        // that the spreading needs no pass and no barrier of its own for it
+        const int at = (3 * P.W * P.H * (int)sizeof(T) + 15) & ~15;
+        if (doA && at + spread_bytes(P.W * P.H) <= patch_bytes) {
+            sums = smem + at;
+            clear_sums(sums, P.W * P.H);
+        }
     }
 
     // ---- start-up (reading: u_v^0 = U(x^0), x^{-1} = x^0 - U(x^0))
-    if (prime && cap.rigid) {
+    if (prime && rigid) {
         rigid_prime(a, S, P, cap, c, st, red);
     } else if (prime) {
         for (int v = tid; v < nv; v += nt) {
@@ -1764,15 +1788,16 @@ __device__ __forceinline__ void ib_block(const IBArgs<T>& a0, unsigned char* sme
     // ---- node update closing the previous step
     if (doB) {
         double csum[2] = {0.0, 0.0};
-        if (cap.rigid) rigid_update(a, S, P, cap, c, st, red, csum);
+        if (rigid) rigid_update(a, S, P, cap, c, st, red, csum);
         if (dyn_forces) {  // element and probe terms, t12, t13 (Eq. 23); nodal sums below
-            double area = red[0][7];
-            for (int w = 1; w < (int)(nt >> 6); w++) area += red[w][7];
+            const int w = tid & 7;
+            const double area = lane_value(combine8(w < (nt >> 6) ? red[w][7] : 0.0,
+                                                    [](double p, double q) { return p + q; }), 0);
             dynamic_forces(S, P, nv, cap.kb, cap.ka, cap.A0, 0.5 * area, (T)cap.nu, a.max_edge,
                            a.max_dA, st);
         }
         const T half_inv_m = (T)(0.5 / cap.mv);
-        for (int v = cap.rigid ? nv : tid; v < nv; v += nt) {
+        for (int v = rigid ? nv : tid; v < nv; v += nt) {
             T Ux, Uy;  // tentative velocity, Eq. 23 (Dynamic: interpolated beside the probes)
             if (DYN) {
                 Ux = S.t[12][v];
@@ -1849,13 +1874,15 @@ __device__ __forceinline__ void ib_block(const IBArgs<T>& a0, unsigned char* sme
         if (kx != T(0) || ky != T(0)) {
             cap.ref_x += (double)kx;
             cap.ref_y += (double)ky;
-            refx += (long long)kx;
-            refy += (long long)ky;
+            wx = g.periodic_x ? wrap_add(wx, (int)kx, g.nx) : wx + (int)kx;
+            wy = g.periodic_y ? wrap_add(wy, (int)ky, g.ny) : wy + (int)ky;
             P.ox -= (int)kx;
             P.oy -= (int)ky;
             if (tid == 0) {
                 a.caps[c].ref_x = cap.ref_x;
                 a.caps[c].ref_y = cap.ref_y;
+                a.caps[c].wx = wx;
+                a.caps[c].wy = wy;
             }
         }
         __syncthreads();
@@ -1864,7 +1891,7 @@ __device__ __forceinline__ void ib_block(const IBArgs<T>& a0, unsigned char* sme
     // ---- near region of this step's grid update (overlapped schedule): the
     // bounding box of x^n and x^{n-1} = x^n - d^n plus 5 cells covers the
     // supports of F^n and F^{n-1} and the patch the next IB launch stages
-    if (a.rects) {
+    if (!STEP && a.rects) {
         float nmn[2] = {3e38f, 3e38f}, nmx[2] = {-3e38f, -3e38f};
         for (int v = tid; v < nv; v += nt) {
             const float x = (float)S.px[v], y = (float)S.py[v];
@@ -1875,6 +1902,7 @@ __device__ __forceinline__ void ib_block(const IBArgs<T>& a0, unsigned char* sme
             nmx[1] = fmaxf(nmx[1], fmaxf(y, yo));
         }
         block_minmax(nmn, nmx, red);
+        const long long refx = (long long)cap.ref_x, refy = (long long)cap.ref_y;
         NearRect r;
         r.x0 = (int)(refx + (long long)floorf(nmn[0])) - 5;
         r.x1 = (int)(refx + (long long)floorf(nmx[0])) + 5;
@@ -1931,15 +1959,21 @@ __device__ __forceinline__ void ib_block(const IBArgs<T>& a0, unsigned char* sme
         // pre-sum in LDS where the staged patch box holds the sums (fewer
         // global atomics: 388 capsules 42.7 -> 30.0 us per launch, 32 capsules
         // 25.2 -> 24.3 us; a lone capsule pays about 0.3 us for the barriers)
-        if (need_field && (size_t)P.W * P.H * 20 <= (size_t)3 * a.patch_cap * sizeof(T))
-            spread_patch(a, g, S, P, nv, refx, refy, st);
+        const SpreadRef r = {wx, wy};
+        if (need_field && !sums && spread_bytes(P.W * P.H) <= patch_bytes) {
+            sums = smem;  // over the moments, which the forcing no longer needs
+            clear_sums(sums, P.W * P.H);
+            __syncthreads();
+        }
+        if (sums)
+            spread_patch(a, g, S, P, Q, sums, nv, r, st);
         else
-            spread_cached(a, g, S, nv, refx, refy, st);
+            spread_cached(a, g, S, nv, r, st);
     }
     if (prime && tid == 0) a.caps[c].primed = 1;
     if (need_field && a.hints && tid == 0) a.hints[c] = make_int4(P.ox, P.oy, P.W, P.H);
     // trajectory tape (reverse sweeps): the node state of this time level
-    if (a.tape_nodes) {
+    if (!STEP && a.tape_nodes) {
         T* TN = a.tape_nodes;
         for (int v = tid; v < nv; v += nt) {
             TN[NF_HX * NS + off + v] = S.px[v];
@@ -1984,7 +2018,7 @@ __global__ __launch_bounds__(kIBThreads) void k_ib(IBArgs<T> a0)
     if (WIDE) __builtin_amdgcn_s_setprio(0);
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ double red[kIBThreads / 64][8];
-    ib_block<T, DYN>(a0, smem, red);  // every exit of ib_block is block-uniform
+    ib_block<T, DYN, false, DYN>(a0, smem, red);  // every exit of ib_block is block-uniform
     if (a0.done_count) {
         // the block's stores (near map, force level, node state) are made
         // visible device-wide before the count announces them
@@ -1996,6 +2030,68 @@ __global__ __launch_bounds__(kIBThreads) void k_ib(IBArgs<T> a0)
     }
 }
 
+// Grid step n and the IB work of step n + 1 in one launch: the first blocks
+// hold a capsule each, the others the grid.  Both read only P^n and F^n; the
+// grid blocks write P^{n+1} and clear the force level of step n - 1, the
+// capsule blocks compute the collisions of their own patches again (about 1,300
+// cells, the same bits), update their nodes and spread F^{n+1} into a third
+// force level.  Nothing in the launch waits for anything else in it, so the grid
+// pass runs beside the IB chain, and a step is one launch:
+//   two launches -> one, us per step: 2048x512 with 32 capsules 28.7 -> 20.5,
+//   1536x256 open with 16 36.1 -> 33.2, 64x64 FP64 16.0 -> 14.8, 256x101
+//   Kinematic 16.0 -> 15.4; 1024x256 with one (the IB chain alone is as long as
+//   the step) 22.2 -> 22.4
+// Rows per wave: the node arrays and the patch in LDS leave one or two blocks on
+// a compute unit, so a wave takes ROWS rows with their loads in flight together.
+template <typename T, bool DYN, bool RIGID>
+__global__ __launch_bounds__(kIBThreads) void k_step(IBArgs<T> a0, int cap_blocks, int ncap,
+                                                     const T* __restrict__ src,
+                                                     T* __restrict__ dst,
+                                                     const long long* __restrict__ fib_now,
+                                                     const int* __restrict__ flags_now,
+                                                     long long* __restrict__ fib_old,
+                                                     int* __restrict__ flags_old, GridArgs g)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ double red[kIBThreads / 64][8];
+    if ((int)blockIdx.x < cap_blocks) {
+        if ((int)blockIdx.x < ncap) ib_block<T, DYN, true, RIGID>(a0, smem, red);
+        return;
+    }
+    constexpr int ROWS = kStepRows, WAVES = kIBThreads / 64;
+    const int b = blockIdx.x - cap_blocks, per = (gridDim.x - cap_blocks) / kNumXcd;
+    const int t = (b % kNumXcd) * per + b / kNumXcd;
+    const int segs = (g.nx + kSegW - 1) / kSegW;
+    const int band = t / segs, seg = t - band * segs;
+    const int lane = threadIdx.x & (kSegW - 1);
+    const int y0 = band * (WAVES * ROWS) + (threadIdx.x >> 6);
+#pragma unroll
+    for (int r = 0; r < ROWS; r++) {
+        const int y = y0 + WAVES * r;
+        if (y < g.ny)
+            grid_cell<true, false>(src, dst, fib_now, flags_now, fib_old, flags_old, g, y, seg,
+                                   lane);
+    }
+}
+
+template <typename T>
+hipError_t launch_step(const IBArgs<T>& a, int ncap, bool rigid, size_t lds_bytes, const T* src, T* dst,
+                       const long long* fib_now, const int* flags_now, long long* fib_old,
+                       int* flags_old, const GridArgs& g, hipStream_t s)
+{
+    const int cap_blocks = (ncap + kNumXcd - 1) / kNumXcd * kNumXcd;
+    const int segs = (g.nx + kSegW - 1) / kSegW;
+    const int rows = kIBThreads / 64 * kStepRows;
+    const int tiles = (g.ny + rows - 1) / rows * segs;
+    const dim3 grid((unsigned)(cap_blocks + (tiles + kNumXcd - 1) / kNumXcd * kNumXcd));
+    const auto f = !a.dynamic ? &k_step<T, false, false>
+                   : rigid    ? &k_step<T, true, true>
+                              : &k_step<T, true, false>;
+    hipLaunchKernelGGL(f, grid, dim3(kIBThreads), lds_bytes, s, a, cap_blocks, ncap, src, dst,
+                       fib_now, flags_now, fib_old, flags_old, g);
+    return hipGetLastError();
+}
+
 template <typename T>
 size_t ib_lds_bytes(int patch_cap, int max_nv)
 {
@@ -2005,7 +2101,10 @@ size_t ib_lds_bytes(int patch_cap, int max_nv)
 template <typename T>
 hipError_t ib_set_lds_limit(size_t bytes)
 {
-    const void* fns[4] = {reinterpret_cast<const void*>(&k_ib<T, true, false>),
+    const void* fns[7] = {reinterpret_cast<const void*>(&k_step<T, true, true>),
+                          reinterpret_cast<const void*>(&k_step<T, true, false>),
+                          reinterpret_cast<const void*>(&k_step<T, false, false>),
+                          reinterpret_cast<const void*>(&k_ib<T, true, false>),
                           reinterpret_cast<const void*>(&k_ib<T, false, false>),
                           reinterpret_cast<const void*>(&k_ib<T, true, true>),
                           reinterpret_cast<const void*>(&k_ib<T, false, true>)};
@@ -2063,12 +2162,13 @@ __global__ __launch_bounds__(kIBThreads) void k_spread_tape(SpreadTapeArgs<T> a)
     IBArgs<T> ia;
     ia.fib_next = a.fib + cap.fib_off;
     ia.flags_next = a.flags + cap.flag_off;
-    const long long refx = (long long)a.ref[2 * c], refy = (long long)a.ref[2 * c + 1];
+    const double refx = a.ref[2 * c], refy = a.ref[2 * c + 1];
+    const SpreadRef r = {g.periodic_x ? wrap_ref((long long)refx, g.nx) : (int)refx,
+                         g.periodic_y ? wrap_ref((long long)refy, g.ny) : (int)refy};
     const size_t NS = a.node_stride;
     const int off = cap.node_offset;
     const T* TN = a.tape;
     int st = 0;
-    const SpreadRef r = spread_ref(g, refx, refy);
     for (int v = threadIdx.x; v < cap.nv; v += blockDim.x) {
         int cx, cy;
         T phi[9];
@@ -2479,6 +2579,9 @@ hipError_t launch_set_nodes(T* nodes, CapsuleDev* caps, int cap, int nv, int nod
     template hipError_t launch_spread_tape<T>(const SpreadTapeArgs<T>&, int, int, hipStream_t);         \
     template hipError_t contact_set_lds_limit<T>(int);                                            \
     template hipError_t launch_ib<T>(const IBArgs<T>&, int, size_t, hipStream_t, bool);                 \
+    template hipError_t launch_step<T>(const IBArgs<T>&, int, bool, size_t, const T*, T*,          \
+                                       const long long*, const int*, long long*, int*,            \
+                                       const GridArgs&, hipStream_t);                             \
     template size_t ib_lds_bytes<T>(int, int);                                                    \
     template hipError_t ib_set_lds_limit<T>(size_t);                                              \
     template hipError_t launch_get_pop_plane<T>(const T*, double*, int, int, const GridArgs&,     \

@@ -85,3 +85,73 @@ def test_two_steps_under_capture():
         torch.cuda.synchronize()
     b.step(6)
     np.testing.assert_array_equal(a.pops(), b.pops())
+
+
+def _ellipse(cx, cy, a, b, n, angle=0.0):
+    t = 2.0 * np.pi * (np.arange(n) + 0.5) / n
+    x, y = a * np.cos(t), b * np.sin(t)
+    c, s = np.cos(angle), np.sin(angle)
+    return np.stack([cx + c * x - s * y, cy + s * x + c * y], axis=1)
+
+
+def _fused_case(name, real_bytes, mode):
+    """Lattice and capsules of one path of the capsule blocks' own grid step."""
+    u, tau = 0.02, 0.8
+    channel = dict(init_profile=wl.INIT_POISEUILLE)
+    if name == "open":  # an end column and a wall row in the ring
+        cfg = wl.open_channel(96, 64, tau, u, real_bytes=real_bytes, mode=mode,
+                              init_profile=wl.INIT_INLET)
+        shapes = [_ellipse(9.0, 12.0, 5.5, 6.0, 40), _ellipse(86.0, 40.0, 6.0, 6.0, 40)]
+    elif name == "box":  # both axes wrap
+        cfg = wl.periodic_box(70, 45, tau, u0=(u, -u), real_bytes=real_bytes, mode=mode)
+        shapes = [_ellipse(2.0, 43.5, 6.0, 5.0, 40), _ellipse(35.0, 20.0, 8.0, 5.0, 48, 0.5)]
+    elif name == "bands":  # FP64: the ring of a large capsule in several bands of rows
+        cfg = wl._base(name, 160, 128, tau, real_bytes, mode, 0,
+                       body_force_x=wl.poiseuille_body_force(tau, 128, u), **channel)
+        shapes = [_ellipse(80.3, 60.2, 22.0, 21.0, 120)]
+    elif name == "direct":  # FP64: a patch so wide that no row of the ring fits
+        cfg = wl._base(name, 400, 48, tau, real_bytes, mode, 0,
+                       body_force_x=wl.poiseuille_body_force(tau, 48, u), **channel)
+        shapes = [_ellipse(200.0, 22.0, 140.0, 3.0, 120)]
+    else:  # walls: moving walls, one capsule on each, patches over the wall rows and the wrap
+        cfg = wl._base(name, 130, 40, tau, real_bytes, mode, 0, u_bottom=-u, u_top=u,
+                       init_profile=wl.INIT_COUETTE)
+        shapes = [_ellipse(3.0, 9.2, 6.0, 6.0, 40), _ellipse(64.0, 29.9, 9.0, 6.0, 60)]
+    cfg["capsules"] = [wl.capsule(p, 0.05, 0.0, 1.0, 1.2) for p in shapes]
+    return cfg
+
+
+@pytest.mark.parametrize("mode", ["dynamic", "kinematic"])
+@pytest.mark.parametrize("name,real_bytes", [("walls", 4), ("walls", 8), ("box", 4), ("open", 4),
+                                             ("open", 8), ("bands", 8), ("direct", 8)])
+def test_one_launch_per_step(name, real_bytes, mode):
+    """A step as one launch (the automatic schedule of a single lattice): the
+    same bits as a grid and an IB launch per step, also after the nodes were
+    moved by hand (the patch box of the last launch does not fit) and across a
+    change of schedule between calls."""
+    cfg = _fused_case(name, real_bytes, mode)
+    a, b = lbib.Sim(cfg), lbib.Sim(cfg)
+    b.set_overlap(False)
+
+    def same():
+        np.testing.assert_array_equal(a.pops(), b.pops())
+        np.testing.assert_array_equal(a.force(), b.force())
+        for c in range(len(a.nv)):
+            np.testing.assert_array_equal(np.stack(a.capsule(c)), np.stack(b.capsule(c)))
+
+    for n in (1, 6):
+        a.step(n)
+        b.step(n)
+        same()
+    x, xp, uv = a.capsule(0)
+    shift = np.array([0.0, 2.0]) if name != "direct" else np.array([2.0, 0.0])
+    for s in (a, b):
+        s.set_capsule(0, x + shift, xp + shift, uv)
+        s.step(3)
+    same()
+    a.set_overlap(False)
+    b.set_overlap(None)
+    for s in (a, b):
+        s.step(4)
+    same()
+    assert a.check() == b.check()
