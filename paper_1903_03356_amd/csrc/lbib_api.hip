@@ -65,6 +65,11 @@ struct Layout {
     size_t inst_table = 0, round_table = 0, rect_table = 0, near_map = 0, bounds = 0,
            hints = 0;  // in BUF_CAPS
     size_t round_off[kTileShapes] = {};  // the round table of each tile shape
+    int levels = 2;  // force levels
+    int max_flags = 0;  // segment flags of the largest lattice
+    // tiles of the batched pass of two steps (pair_tiles), 0: none
+    int two_tiles = 0, two_rows = 0, two_threads = 0;
+    size_t two_off = 0;
 };
 
 struct lbib_ctx {
@@ -127,10 +132,13 @@ struct lbib_ctx {
     // of a forcing spread ahead: the step's near map is stamped too (overlapped
     // schedule only)
     bool a_stamped = false;
+    bool recorded = false;  // a caller has recorded a step call into a graph
+    bool a_rects = false;  // and the capsules' node boxes are written (step_pair_t only)
     // force levels by what they hold at time `steps` (as the step calls go on):
     // F^{n-1}, F^n (zero until spread), and a spare one (zero).  A serial step
     // swaps the first two, a fused one rotates all three.
     int lv_prev = 1, lv_next = 0, lv_spare = 2;
+    int lv_old = 3;  // may still hold F^{n-2}: step_pair_t clears it before use
     // membrane checks (lbib_set_limits), 0 = off
     float max_edge = 0.0f, max_dA = 0.0f;
 };
@@ -212,6 +220,20 @@ constexpr int kMaxOverlapCapsules = 4096;  // near regions per step (one near-ke
 constexpr long long kFarWaitInsideCells = 1LL << 23;
 constexpr long long kOverlapMinCells = 1LL << 22;  // automatic overlap from 4.2 M cells
 
+constexpr long long kSpareLevelCells = 1LL << 28;
+
+static std::vector<GridArgs> batch_sizes(const Layout& L)
+{
+    std::vector<GridArgs> g(L.inst.size(), GridArgs());
+    for (size_t i = 0; i < g.size(); i++) {
+        g[i].nx = L.inst[i].grid.nx;
+        g[i].ny = L.inst[i].grid.ny;
+        g[i].nxp = L.inst[i].nxp;
+        g[i].nseg = L.inst[i].nseg;
+    }
+    return g;
+}
+
 // Fills L from the lattices' sizes and capacities; false if any is invalid or
 // the totals leave the supported range.
 static bool make_layout(const lbib_grid* grids, int n, Layout& L)
@@ -243,6 +265,7 @@ static bool make_layout(const lbib_grid* grids, int n, Layout& L)
         cells += (long long)g->nx * g->ny;
         L.max_nv = std::max(L.max_nv, g->max_nodes_capsule);
         L.plane_max = std::max(L.plane_max, (size_t)g->nx * g->ny);
+        L.max_flags = std::max(L.max_flags, g->ny * I.nseg);
         L.inst.push_back(I);
     }
     // one-row tiles are the most numerous shape
@@ -261,6 +284,12 @@ static bool make_layout(const lbib_grid* grids, int n, Layout& L)
     L.near_map = L.rect_table + round256((size_t)2 * L.max_caps * sizeof(NearRect));
     L.bounds = L.near_map + round256((size_t)2 * L.flag_level * sizeof(int));
     L.hints = L.bounds + round256((size_t)L.max_caps * sizeof(float4));
+    L.two_off = L.hints + round256((size_t)L.max_caps * sizeof(int4));
+    if (cells <= kSpareLevelCells) L.levels = kForceLevels;
+    if (n > 1 && L.levels == kForceLevels && L.pop_elems * L.rb >= kPairMinBytes) {
+        const std::vector<GridArgs> g = batch_sizes(L);
+        L.two_tiles = pair_tiles(g.data(), n, L.rb, nullptr, L.two_threads, L.two_rows);
+    }
     return true;
 }
 
@@ -274,11 +303,11 @@ static size_t layout_bytes(const Layout& L, int id)
     switch (id) {
     case LBIB_BUF_POPS_A:
     case LBIB_BUF_POPS_B: return round256(L.pop_elems * L.rb);
-    case LBIB_BUF_FORCE: return round256(kForceLevels * L.fib_level * sizeof(long long));
-    case LBIB_BUF_FLAGS: return round256(kForceLevels * L.flag_level * sizeof(int));
+    case LBIB_BUF_FORCE: return round256(L.levels * L.fib_level * sizeof(long long));
+    case LBIB_BUF_FLAGS: return round256(L.levels * L.flag_level * sizeof(int));
     case LBIB_BUF_NODES: return round256((size_t)NF_COUNT * L.max_nodes * L.rb);
     case LBIB_BUF_CAPS:
-        return L.hints + round256((size_t)L.max_caps * sizeof(int4));
+        return L.two_off + round256((size_t)L.two_tiles * sizeof(TwoTile));
     case LBIB_BUF_DIAG: return round256(status_offset(L) + 64);
     case LBIB_BUF_STAGE: {
         size_t n = 3 * L.plane_max;
@@ -406,11 +435,10 @@ static unsigned long long* ib_done_counter(const lbib_ctx* c)
 static lbib_status drop_pending_forcing(lbib_ctx* c)
 {
     if (!c->a_ready) return LBIB_OK;
-    HIPCHK(c, hipMemsetAsync(fib(c, c->lv_next), 0, c->L.fib_level * sizeof(long long), c->stream));
-    HIPCHK(c, hipMemsetAsync(flags(c, c->lv_next), 0, c->L.flag_level * sizeof(int), c->stream));
-    if (c->a_stamped)
-        HIPCHK(c, hipMemsetAsync(near_map(c, c->steps), 0, c->L.flag_level * sizeof(int), c->stream));
-    c->a_ready = c->a_stamped = false;
+    HIPCHK(c, launch_clear_level(fib(c, c->lv_next), flags(c, c->lv_next), inst_table(c),
+                                 (int)c->L.inst.size(), c->L.max_flags, c->stream));
+    if (c->a_stamped) HIPCHK(c, launch_zero(near_map(c, c->steps), c->L.flag_level, c->stream));
+    c->a_ready = c->a_stamped = c->a_rects = false;
     return LBIB_OK;
 }
 
@@ -574,6 +602,14 @@ static lbib_status create_common(const lbib_grid* grids, const double* taus,
         if (!rounds[k].empty())
             e = hipMemcpyAsync(bufp(c, LBIB_BUF_CAPS) + L.round_off[k], rounds[k].data(),
                                rounds[k].size() * sizeof(int2), hipMemcpyHostToDevice, c->stream);
+    std::vector<TwoTile> two(L.two_tiles);
+    if (L.two_tiles > 0 && e == hipSuccess) {
+        const std::vector<GridArgs> g = batch_sizes(L);
+        int threads, rows;
+        pair_tiles(g.data(), n_inst, L.rb, two.data(), threads, rows);
+        e = hipMemcpyAsync(bufp(c, LBIB_BUF_CAPS) + L.two_off, two.data(),
+                           two.size() * sizeof(TwoTile), hipMemcpyHostToDevice, c->stream);
+    }
     if (e != hipSuccess) return bail(LBIB_EDEVICE, std::string("hipMemcpyAsync: ") + hipGetErrorString(e));
     for (int i = 0; i < n_inst && e == hipSuccess; i++) {
         const Inst& I = c->L.inst[i];
@@ -1097,6 +1133,7 @@ static lbib_status step_overlap_t(lbib_ctx* c, int nsteps)
         HIPCHK(c, hipEventRecord(c->e_ib, c->stream));
     }
     c->a_ready = c->a_stamped = ahead;
+    c->a_rects = false;
     HIPCHK(c, hipStreamWaitEvent(c->stream, c->e_far[(c->steps + nsteps - 1) & 1], 0));
     c->steps += nsteps;
     return LBIB_OK;
@@ -1142,6 +1179,80 @@ static lbib_status step_body(lbib_ctx* c, long long n, int pb, int pa, bool cont
     return s;
 }
 
+// Two steps in one pass over the lattices, with capsules.  The pass needs F^n and
+// F^{n+1} before it starts, and the IB work of steps n + 1 and n + 2 reads only
+// the cells near the capsules, so per pair, on one stream:
+//   IB     step n + 1 from P^n (ib_block, STEP): spreads F^{n+1}; beside it f*^n near
+//          the capsules into the buffer of P^{n+2}, and the clearing of two levels
+//   IB     step n + 2 in the same way from there: spreads F^{n+2}
+//   grid   P^n -> P^{n+2}, over the cells the first launch left
+template <typename T>
+static lbib_status step_pair_t(lbib_ctx* c, int nsteps)
+{
+    const bool single = c->L.inst.size() == 1, ahead = c->mode == LBIB_DYNAMIC;
+    if (c->a_ready && !c->a_rects) {
+        lbib_status s = drop_pending_forcing(c);
+        if (s != LBIB_OK) return s;
+    }
+    NearRect* rects = rect_table(c, 0);
+    if (!c->a_ready) {
+        IBArgs<T> a = ib_args<T>(c, c->steps, c->steps == 0 ? (PH_PRIME | PH_A) : PH_A);
+        a.rects = rects;
+        HIPCHK(c, launch_ib<T>(a, c->ncap, c->lds_use, c->stream, c->ncap <= c->num_cu));
+    }
+    const bool rigid = any_rigid(c);
+    const int n_inst = (int)c->L.inst.size();
+    const bool nt = 2.0 * c->L.pop_elems * sizeof(T) > kPlainStoreMaxBytes;
+    for (int k = 0; k < nsteps / 2; k++) {
+        const long long n = c->steps;
+        const T* src = static_cast<const T*>(pops(c, n));
+        T* dst = static_cast<T*>(pops(c, n + 1));
+        IBArgs<T> a = ib_args<T>(c, n, PH_B | PH_A);
+        a.fib_prev = fib(c, c->lv_next);
+        a.fib_next = fib(c, c->lv_spare);
+        a.flags_next = flags(c, c->lv_spare);
+        const PairNear near = {rects, a.caps, inst_table(c),
+                               {fib(c, c->lv_prev), fib(c, c->lv_old)},
+                               {flags(c, c->lv_prev), flags(c, c->lv_old)}, 0, 0, 0};
+        HIPCHK(c, launch_step_near<T>(a, c->ncap, rigid, c->lds_use, src, dst, fib(c, c->lv_next), near,
+                                      n_inst, c->L.max_flags, c->stream));
+        a.pops = dst;
+        a.phase = 2 * k + 2 < nsteps || ahead ? (PH_B | PH_A) : PH_B;
+        a.fib_prev = fib(c, c->lv_spare);
+        a.fib_next = fib(c, c->lv_old);
+        a.flags_next = flags(c, c->lv_old);
+        a.rects = rects;
+        HIPCHK(c, launch_step_near<T>(a, c->ncap, rigid, c->lds_use, nullptr, nullptr, nullptr,
+                                      PairNear(), 0, 0, c->stream));
+        const TwoForce f = {{fib(c, c->lv_next), fib(c, c->lv_spare)},
+                            {flags(c, c->lv_next), flags(c, c->lv_spare)}};
+        HIPCHK(c, single ? launch_grid_pair<T>(src, dst, grid_args(c->L.inst[0]), f, c->num_cu, c->stream)
+                         : launch_grid_pair_batch<T>(
+                               src, dst, f, inst_table(c),
+                               reinterpret_cast<const TwoTile*>(bufp(c, LBIB_BUF_CAPS) + c->L.two_off),
+                               c->L.two_tiles, c->L.two_rows, c->L.two_threads, nt, c->stream));
+        std::swap(c->buf[LBIB_BUF_POPS_A], c->buf[LBIB_BUF_POPS_B]);
+        const int done = c->lv_next, cleared = c->lv_prev;
+        c->lv_prev = c->lv_spare;
+        c->lv_next = c->lv_old;
+        c->lv_spare = cleared;
+        c->lv_old = done;
+        c->steps += 2;
+    }
+    if (nsteps & 1) {
+        const long long n = c->steps;
+        lbib_status s = step_body<T>(c, n, 0, 0, false, c->mode == LBIB_DYNAMIC);
+        if (s != LBIB_OK) return s;
+        IBArgs<T> a = ib_args<T>(c, n + 1, ahead ? (PH_B | PH_A) : PH_B);
+        a.rects = rects;
+        HIPCHK(c, launch_ib<T>(a, c->ncap, c->lds_use, c->stream, c->ncap <= c->num_cu));
+        c->steps++;
+    }
+    c->a_ready = c->a_rects = ahead;
+    c->a_stamped = false;
+    return LBIB_OK;
+}
+
 // Fused schedule of one lattice: one launch per step (k_step) after a first one
 // that spreads the forcing of the call's first step.  With the Dynamic scheme
 // the last launch also spreads the forcing of the step after it (phase A writes
@@ -1177,7 +1288,7 @@ static lbib_status step_fused_t(lbib_ctx* c, int nsteps, bool contact)
         c->lv_spare = cleared;
     }
     c->a_ready = ahead;
-    c->a_stamped = false;
+    c->a_stamped = c->a_rects = false;
     c->steps += nsteps;
     return LBIB_OK;
 }
@@ -1235,6 +1346,22 @@ static bool capturing(hipStream_t st)
     return hipStreamIsCapturing(st, &s) != hipSuccess || s != hipStreamCaptureStatusNone;
 }
 
+// Whether two steps with capsules go in one pass: from the size on where the pass
+// itself, and not the two IB launches before it, is most of the time.  us per step,
+// fused or one pass per step / pairs, 32 capsules: FP32 2048x512 20.0 / 29.8, 2048x1536
+// (111 MiB) 38.5 / 47.5, 2048^2 (148 MiB) 74.0 / 56.7, 4096^2 221 / 137; FP64 2048x512
+// 27.8 / 41.3, 2048x1024 (148 MiB) 62.4 / 58.9, 2048^2 131 / 88; batches of 128-512 x
+// 72-128 lattices: 64 of them (70 MiB) 44.9 / 46.2, 128 71.5 / 63.8, 256 129 / 100.
+template <typename T>
+static bool pair_pays(const lbib_ctx* c)
+{
+    if (c->L.pop_elems * sizeof(T) < kPairMinBytes) return false;
+    if (c->L.inst.size() == 1) return grid_two_pays<T>(grid_args(c->L.inst[0]));
+    for (const Inst& I : c->L.inst)
+        if (9.0 * I.nxp * I.grid.ny * sizeof(T) >= 4.0 * (1u << 30) - 4096.0) return false;
+    return c->L.two_tiles > 0;
+}
+
 template <typename T>
 static lbib_status step_t(lbib_ctx* c, int nsteps)
 {
@@ -1253,11 +1380,24 @@ static lbib_status step_t(lbib_ctx* c, int nsteps)
     // the far pass), so a batch splits only when asked.
     const bool want = c->overlap >= 1 || (c->overlap < 0 && c->L.inst.size() == 1 &&
                                           cells >= kOverlapMinCells);
+    // A caller's graph keeps the addresses of the buffers and force levels that it was
+    // recorded with, so from the first recorded call on a context goes without the
+    // schedules that exchange them; and the graph must hold its first step's forcing.
+    if (capturing(c->stream)) {
+        c->recorded = true;
+        if (c->a_ready && !c->a_stamped) {
+            lbib_status s = drop_pending_forcing(c);
+            if (s != LBIB_OK) return s;
+        }
+    }
+    const bool exchange = !c->recorded && c->graph != 1;
+    const bool direct = c->overlap < 0 && c->ncap > 0 && c->L.levels == kForceLevels && !c->timing &&
+                        exchange;
+    if (direct && can_overlap && nsteps >= 2 && pair_pays<T>(c)) return step_pair_t<T>(c, nsteps);
     if (can_overlap && want) return step_overlap_t<T>(c, nsteps);
     // one launch per step (the contact force of the Kinematic scheme sits between
     // the node update and the forcing, so it keeps separate launches)
-    if (c->overlap < 0 && c->ncap > 0 && c->L.inst.size() == 1 && !(contact && !dyn) &&
-        !c->timing && c->graph != 1 && !capturing(c->stream))
+    if (direct && c->L.inst.size() == 1 && !(contact && !dyn))
         return step_fused_t<T>(c, nsteps, contact);
     // replays of captured blocks for the inner steps; timed runs launch directly
     const bool graphs = c->graph == 1 && !c->timing;
@@ -1275,8 +1415,8 @@ static lbib_status step_t(lbib_ctx* c, int nsteps)
     // without capsules two steps go in one pass; the state then stands in the other
     // population buffer, which takes the first one's place (graphs, the library's and
     // the caller's, hold the buffers' addresses and keep single passes)
-    const bool two = c->ncap == 0 && c->graph != 1 && c->L.inst.size() == 1 &&
-                     grid_two_pays<T>(grid_args(c->L.inst[0])) && !capturing(c->stream);
+    const bool two = c->ncap == 0 && exchange && c->L.inst.size() == 1 &&
+                     grid_two_pays<T>(grid_args(c->L.inst[0]));
     for (int k = 0; k < nsteps;) {
         const long long n = c->steps + k;
         if (two && nsteps - k >= 2) {
@@ -1319,7 +1459,7 @@ static lbib_status step_t(lbib_ctx* c, int nsteps)
         lbib_status s = launch_timed<T>(c, 1, do_ib<T>, &q);
         if (s != LBIB_OK) return s;
     }
-    c->a_ready = c->a_stamped = false;
+    c->a_ready = c->a_stamped = c->a_rects = false;
     c->steps += nsteps;
     return LBIB_OK;
 }

@@ -10,6 +10,7 @@ namespace lbib {
 constexpr int kSegW = 64;
 constexpr double kPlainStoreMaxBytes = 384.0 * (1 << 20);  // single pass: plain stores up to here
 constexpr double kTwoMinBytes = 16.0 * (1 << 20);  // two steps in one pass: populations from here
+constexpr double kPairMinBytes = 140.0 * (1 << 20);  // the same with capsules
 constexpr int kGridRowsPerThread = 1;  // grid kernel: nodes per thread, 4 rows apart
 constexpr int kNumXcd = 8;       // MI355X: workgroups are dealt round-robin to 8 XCDs
 constexpr int kStepRows = 2;     // k_step: rows per wave of its grid blocks
@@ -95,10 +96,10 @@ struct CapsuleDev {
 };
 static_assert(sizeof(CapsuleDev) == 312, "CapsuleDev layout");
 
-// Time levels of the force field: that of the last collision, that of the
-// coming one, and a spare one for the schedules that spread the forcing of the
-// next step while the grid still reads this step's (k_step).
-constexpr int kForceLevels = 3;
+// Time levels of the force field: that of the last collision, that of the coming
+// one, and two more for the schedules that spread a step's forcing while the
+// grid still has to read the one before (step_fused_t, step_pair_t).
+constexpr int kForceLevels = 4;
 
 constexpr int kDiagStride = 16;  // doubles per capsule in BUF_DIAG
 
@@ -191,7 +192,31 @@ struct ContactArgs {
     double cutoff;
 };
 
+// F^n and F^{n+1} with their segment flags (pairs of steps).
+struct TwoForce {
+    const long long* fib[2];
+    const int* flags[2];
+};
+// Near cells and clearing in the first launch of a pair (pair_near; inst = NULL: none).
+struct PairNear {
+    const NearRect* rects;   // node boxes of the capsules
+    const CapsuleDev* caps;
+    const InstDev* inst;
+    long long* fib[2];       // force levels to clear where their flags are set
+    int* flags[2];
+    int near_blocks, per_cap, parts;  // blocks: near_blocks = capsules x per_cap, then lattices x parts
+};
+// Columns x0 .. x0 + cols - 1 of lattice `inst` from row ya on (inst < 0: none).
+struct TwoTile {
+    int inst, x0, cols, ya;
+};
+
 // ---- launchers (lbib_kernels.hip) ----
+// A force level and its flags back to zero; n ints to zero (kernels: a caller may
+// be recording them).
+hipError_t launch_clear_level(long long* fib, int* flags, const InstDev* inst, int n_inst,
+                              int max_flags, hipStream_t s);
+hipError_t launch_zero(int* p, size_t n, hipStream_t s);
 template <typename T>
 hipError_t launch_init(T* pops, const GridArgs& g, int profile, double ux0, double uy0,
                        double nu, hipStream_t s);
@@ -203,6 +228,19 @@ template <typename T>
 bool grid_two_pays(const GridArgs& g);
 template <typename T>
 hipError_t launch_grid_two(const T* src, T* dst, const GridArgs& g, int num_cu, hipStream_t s);
+// The same with IB forces, for one lattice and for a batch (tiles by pair_tiles).
+template <typename T>
+hipError_t launch_grid_pair(const T* src, T* dst, const GridArgs& g, const TwoForce& f, int num_cu,
+                            hipStream_t s);
+int pair_tiles(const GridArgs* g, int n, int real_bytes, TwoTile* out, int& threads, int& rows);
+template <typename T>
+hipError_t launch_grid_pair_batch(const T* src, T* dst, const TwoForce& f, const InstDev* inst,
+                                  const TwoTile* table, int tiles, int rows, int threads, bool nt,
+                                  hipStream_t s);
+template <typename T>
+hipError_t launch_step_near(const IBArgs<T>& a, int ncap, bool rigid, size_t lds_bytes, const T* src,
+                            T* dst, const long long* fib_now, PairNear near, int n_inst,
+                            int max_flags, hipStream_t s);
 template <typename T>
 hipError_t launch_grid_step_batch(const T* src, T* dst, const long long* fib_now,
                                   const int* flags_now, long long* fib_old, int* flags_old,

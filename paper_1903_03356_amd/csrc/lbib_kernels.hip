@@ -260,6 +260,116 @@ __global__ __launch_bounds__(kSegW * 4) void k_grid_near(
     }
 }
 
+// Clears a lattice's force level where its segment flags are set, and the flags;
+// part `part` of clear_parts: a wave looks at 256 flags and clears the segments
+// they mark.
+__device__ __forceinline__ void clear_segments(long long* F, int* fl, const InstDev& I, int part)
+{
+    const int tid = threadIdx.x, lane = tid & (kSegW - 1);
+    const int n = (I.ny * I.nseg + 3) & ~3, at = (part * kIBThreads + tid) * 4;
+    int4 v = make_int4(0, 0, 0, 0);
+    if (at < n) v = *reinterpret_cast<const int4*>(fl + at);
+    const int any[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        unsigned long long m = __ballot(any[j] != 0);
+        while (m) {
+            const int l = __ffsll(m) - 1;
+            m &= m - 1;
+            const size_t cell = (size_t)(at - 4 * lane + 4 * l + j) * kSegW + lane;
+            *reinterpret_cast<longlong2*>(F + 2 * cell) = make_longlong2(0, 0);
+        }
+    }
+    if (v.x | v.y | v.z | v.w) *reinterpret_cast<int4*>(fl + at) = make_int4(0, 0, 0, 0);
+}
+
+static int clear_parts(int max_flags) { return (max_flags + 4 * kIBThreads - 1) / (4 * kIBThreads); }
+
+__global__ __launch_bounds__(kIBThreads) void k_clear_level(long long* fib, int* flags,
+                                                            const InstDev* __restrict__ inst,
+                                                            int parts)
+{
+    const int i = blockIdx.x / parts;
+    const InstDev& I = inst[i];
+    clear_segments(fib + I.fib_off, flags + I.flag_off, I, blockIdx.x - i * parts);
+}
+
+hipError_t launch_clear_level(long long* fib, int* flags, const InstDev* inst, int n_inst,
+                              int max_flags, hipStream_t s)
+{
+    const int parts = clear_parts(max_flags);
+    hipLaunchKernelGGL(k_clear_level, dim3((unsigned)(n_inst * parts)), dim3(kIBThreads), 0, s, fib,
+                       flags, inst, parts);
+    return hipGetLastError();
+}
+
+__global__ void k_zero(int* p, size_t n)
+{
+    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) p[i] = 0;
+}
+
+hipError_t launch_zero(int* p, size_t n, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_zero, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p, n);
+    return hipGetLastError();
+}
+
+// First launch of a pair of steps, beside the capsules' blocks (k_step): f*^n on the
+// cells that the IB work of step n + 2 reads, into the buffer that will hold
+// P^{n+2}, and the clearing of the force levels of the steps before.
+// The cells: the node box of NearRect (5 cells around x^n) and 3 more, so 3 of the
+// patch, 1 that the nodes may move, 2 that the ring of the patch's own step and its
+// pulls reach, 2 spare.  One wave per row and 64 columns (whole 64-cell segments
+// were 2.5 times the cells).
+template <typename T>
+__device__ void pair_near(const T* __restrict__ src, T* __restrict__ dst,
+                          const long long* __restrict__ fib_now, const PairNear& p, int block)
+{
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & (kSegW - 1);
+    constexpr int WAVES = kIBThreads / 64;
+    if (block >= p.near_blocks) {
+        const int b = block - p.near_blocks, i = b / p.parts;
+        const InstDev& I = p.inst[i];
+        for (int k = 0; k < 2; k++)
+            clear_segments(p.fib[k] + I.fib_off, p.flags[k] + I.flag_off, I, b - i * p.parts);
+        return;
+    }
+    const int c = block / p.per_cap, kb = block - c * p.per_cap;
+    const NearRect r = p.rects[c];
+    const InstDev& I = p.inst[p.caps[c].inst];
+    const GridArgs g = lattice_args(I);
+    src += I.pop_off;
+    dst += I.pop_off;
+    fib_now += I.fib_off;
+    const int w = min(r.x1 - r.x0 + 7, g.nx), cols = (w + kSegW - 1) / kSegW;
+    int x0 = (r.x0 - 3) % g.nx, y0 = r.y0 - 3, rows = r.y1 - r.y0 + 7;
+    x0 = x0 < 0 ? x0 + g.nx : x0;
+    if (g.periodic_y) {
+        y0 %= g.ny;
+        y0 = y0 < 0 ? y0 + g.ny : y0;
+        rows = min(rows, g.ny);
+    } else {
+        const int end = min(g.ny, y0 + rows);
+        y0 = max(0, y0);
+        rows = end - y0;
+    }
+    for (int q = kb * WAVES + wave; q < rows * cols; q += p.per_cap * WAVES) {
+        const int ri = q / cols, at = (q - ri * cols) * kSegW + lane;
+        if (at >= w) continue;
+        int x = x0 + at, y = y0 + ri;
+        if (x >= g.nx) x -= g.nx;
+        if (y >= g.ny) y -= g.ny;
+        const size_t cell = (size_t)y * g.nxp + x;
+        T s[9];
+        pull_loads<T, false>(src, x, y, g, s);
+        const longlong2 f = *reinterpret_cast<const longlong2*>(fib_now + 2 * cell);
+        const T Fx = (T)g.gx + fix_to_real<T>(f.x), Fy = fix_to_real<T>(f.y);
+        pull_complete<T, false>(src, x, y, g, Fx, s);
+        collide_pulled<T, false>(s, dst, g, x, y, Fx, Fy);
+    }
+}
+
 // Block = 4 wavefronts; a block covers one 64-cell column of a band of
 // 4 * ROWS rows, each thread ROWS nodes 4 rows apart (more loads in flight per
 // thread).  Workgroups are dealt to the 8 XCDs round-robin; block b is
@@ -308,6 +418,7 @@ __device__ __forceinline__ double lane_shift(double v)
 
 constexpr int kWaveShr1 = 0x138, kWaveShl1 = 0x130;
 constexpr int kTwoMaxThreads = 576;
+constexpr int kTwoMaxRows = 1022;  // FORCED: rows of a block (its row masks in LDS)
 
 // Block barrier that orders LDS accesses only: global loads in flight stay in
 // flight across it.
@@ -333,11 +444,14 @@ __device__ __forceinline__ void lds_barrier()
 // arithmetic is that of two single steps, bit for bit.  Bound by memory: 4096 x
 // 4096 FP32 205 -> 119 us per step (10.2 TB/s counted as 72 bytes a cell and step,
 // 5.2 TB/s moved, the rate of a plain copy); VALU about 45 % busy.
-template <typename T, bool NT>
-__global__ __launch_bounds__(kTwoMaxThreads) void k_grid_two(const T* __restrict__ src,
-                                                             T* __restrict__ dst, GridArgs g,
-                                                             unsigned bytes, int rows, int cols,
-                                                             int nblkx)
+//
+// FORCED: with the IB forces F^n and F^{n+1} of the two steps.  The block first
+// notes in LDS which rows of which of its waves touch an active segment; only
+// those load the force, one row ahead.  BATCH: the tile comes from a table.
+template <typename T, bool NT, bool FORCED, bool BATCH>
+__global__ __launch_bounds__(kTwoMaxThreads) void k_grid_two(
+    const T* __restrict__ src, T* __restrict__ dst, GridArgs g, unsigned bytes, int rows, int cols,
+    int nblkx, TwoForce f, const InstDev* __restrict__ inst, const TwoTile* __restrict__ table)
 {
     constexpr int kHalo = 128 / (int)sizeof(T);
     // populations that leave a wave through its first ([0]: 3, 6, 7) and last
@@ -347,19 +461,41 @@ __global__ __launch_bounds__(kTwoMaxThreads) void k_grid_two(const T* __restrict
     // rows of tiles dealt to the XCDs in turn 124 us)
     const int per = (int)gridDim.x / kNumXcd;
     const int t = ((int)blockIdx.x % kNumXcd) * per + (int)blockIdx.x / kNumXcd;
-    const int chunk = t / nblkx, xblk = t - chunk * nblkx;
-    const int ya = chunk * rows;
+    int x0, ya;
+    if (BATCH) {
+        const TwoTile tile = table[t];
+        if (tile.inst < 0) return;
+        const InstDev& I = inst[tile.inst];
+        g = lattice_args(I);
+        x0 = tile.x0;
+        ya = tile.ya;
+        cols = tile.cols;
+        src += I.pop_off;
+        dst += I.pop_off;
+        for (int k = 0; k < 2; k++) {
+            f.fib[k] += I.fib_off;
+            f.flags[k] += I.flag_off;
+        }
+        bytes = 9u * (unsigned)g.ny * (unsigned)g.nxp * (unsigned)sizeof(T);
+    } else {
+        const int chunk = t / nblkx;
+        x0 = (t - chunk * nblkx) * cols;
+        ya = chunk * rows;
+    }
     if (ya >= g.ny) return;
     const int yb = min(ya + rows, g.ny);
     const int tid = threadIdx.x, lane = tid & 63, wave = (tid >> 6) + 1;
-    const int xo = xblk * cols - kHalo + tid;
+    // (whole waves past the columns of a narrow lattice leave)
+    const int width = kHalo + min(cols, g.nx - x0) + 1;
+    if (BATCH && (tid & ~63) >= width) return;
+    const int xo = x0 - kHalo + tid;
     int x = xo % g.nx;
     x = x < 0 ? x + g.nx : x;
     const unsigned vm = (unsigned)(x == 0 ? g.nx - 1 : x - 1) * sizeof(T);
     const unsigned v0 = (unsigned)x * sizeof(T);
     const unsigned vp = (unsigned)(x == g.nx - 1 ? 0 : x + 1) * sizeof(T);
     const unsigned vout = tid >= kHalo && tid < kHalo + cols && xo < g.nx ? v0 : kNoCell;
-    const T om = (T)g.omega, Fx = (T)g.gx, Fy = T(0);
+    const T om = (T)g.omega;
     const T uc = (T)g.uref_c, c3 = (T)((double)FirstOrderW<T>::diag * g.uref_c);
     auto offsets = [&](int y, T (&s)[9]) {  // add_pull_offsets
         const T dm = c3 * (T)(2 * y - g.ny), dp = c3 * (T)(g.ny - 2 - 2 * y);
@@ -396,6 +532,51 @@ __global__ __launch_bounds__(kTwoMaxThreads) void k_grid_two(const T* __restrict
         buf_load<0>(in, vp, op + 7 * plane, s[7]);
         buf_load<0>(in, vm, op + 8 * plane, s[8]);
     };
+    // which waves of which row touch an active segment of F^n (bits 0 ..) and of
+    // F^{n+1} (bits 16 ..); row ya - 1 first
+    __shared__ unsigned active[FORCED ? kTwoMaxRows + 2 : 1];
+    if (FORCED) {
+        const int waves = (min((int)blockDim.x, width) + 63) >> 6, lanes = min((int)blockDim.x, waves * 64);
+        const int n = yb - ya + 2;
+        for (int i = tid; i < n; i += lanes) active[i] = 0;
+        __syncthreads();
+        for (int i = tid; i < n * waves; i += lanes) {
+            const int r = i / waves, w = i - r * waves;
+            const int y = py ? wrap(ya - 1 + r) : ya - 1 + r;
+            if ((unsigned)y > (unsigned)top) continue;
+            int a = 0, b = 0;
+            int xs = (x0 - kHalo + w * 64) % g.nx;
+            xs = xs < 0 ? xs + g.nx : xs;
+            for (int left = 64; left > 0;) {
+                const int s = y * g.nseg + xs / kSegW;
+                a |= f.flags[0][s];
+                b |= f.flags[1][s];
+                const int go = min(kSegW - xs % kSegW, g.nx - xs);
+                xs = xs + go == g.nx ? 0 : xs + go;
+                left -= go;
+            }
+            if (a | b) atomicOr(&active[r], (a ? 1u << w : 0u) | (b ? 65536u << w : 0u));
+        }
+        __syncthreads();
+    }
+    // the forces of the coming row r of step n and row r - 1 of step n + 1
+    long long fx[2] = {0, 0}, fy[2] = {0, 0};
+    const unsigned v16 = (unsigned)x * 16u;
+    auto load_force = [&](int r) {
+#pragma unroll
+        for (int k = 0; k < 2; k++) {
+            fx[k] = fy[k] = 0;
+            const int q = r - k - (ya - 1);
+            if (q < 0 || r > yb) continue;
+            const unsigned bits = __builtin_amdgcn_readfirstlane((int)active[q]);
+            if (!(bits >> (k * 16 + wave - 1) & 1u)) continue;
+            const int y = py ? wrap(r - k) : r - k;
+            const __amdgpu_buffer_rsrc_t ff = buffer_of(f.fib[k], 16u * (unsigned)g.ny * (unsigned)g.nxp);
+            buf_load<0>(ff, v16, (unsigned)y * (unsigned)g.nxp * 16u, fx[k]);
+            buf_load<0>(ff, v16 + 8, (unsigned)y * (unsigned)g.nxp * 16u, fy[k]);
+        }
+    };
+    const T gx = (T)g.gx;
     // post-collision values of the rows before, moved to this column: 2, 5, 6
     // of row r - 2 (A), 0, 1, 3 and 2, 5, 6 of row r - 1 (B)
     T A2 = 0, A5 = 0, A6 = 0, B0 = 0, B1 = 0, B2 = 0, B3 = 0, B5 = 0, B6 = 0;
@@ -403,6 +584,14 @@ __global__ __launch_bounds__(kTwoMaxThreads) void k_grid_two(const T* __restrict
         T s[9], p[9];
 #pragma unroll
         for (int i = 0; i < 9; i++) s[i] = ahead[i];
+        T Fx = gx, Fy = T(0), Gx = gx, Gy = T(0);
+        if (FORCED) {
+            Fx += fix_to_real<T>(fx[0]);
+            Fy += fix_to_real<T>(fy[0]);
+            Gx += fix_to_real<T>(fx[1]);
+            Gy += fix_to_real<T>(fy[1]);
+            load_force(r + 1);
+        }
         load(r + 2, ahead);
         const int rw = py ? wrap(r) : r;
         offsets(rw, s);
@@ -433,8 +622,8 @@ __global__ __launch_bounds__(kTwoMaxThreads) void k_grid_two(const T* __restrict
         const int yo = r - 1;
         T q[9] = {B0, B1, A2, B3, p[4], A5, A6, p[7], p[8]}, o[9];
         offsets(yo, q);
-        if (!py && (yo == 0 || yo == top)) pull_complete<T, false>(src, 1, yo, g, Fx, q);
-        collide(q, uref(yo), om, Fx, Fy, o);
+        if (!py && (yo == 0 || yo == top)) pull_complete<T, false>(src, 1, yo, g, Gx, q);
+        collide(q, uref(yo), om, Gx, Gy, o);
         const __amdgpu_buffer_rsrc_t to = buffer_of(dst, yo >= ya ? bytes : 0u);
         const unsigned so = (unsigned)max(yo, 0) * row;
 #pragma unroll
@@ -453,6 +642,7 @@ __global__ __launch_bounds__(kTwoMaxThreads) void k_grid_two(const T* __restrict
     // the row is computed from clamped loads and not used
     const int r0 = (!py && ya == 0) ? 0 : ya - 1;
     T even[9], odd[9];
+    if (FORCED) load_force(r0);
     load(r0, even);
     load(r0 + 1, odd);
     for (int r = r0; r <= yb; r += 2) {
@@ -473,37 +663,112 @@ bool grid_two_pays(const GridArgs& g)
     return g.periodic_x && bytes >= kTwoMinBytes && bytes < 4.0 * (1u << 30) - 4096.0;
 }
 
-// Column blocks of at most kTwoThreads lanes, and as many rows per block as
+// Column blocks of at most `max_threads` lanes, and as many rows per block as
 // put two blocks on every compute unit in one round: all blocks then start and
 // end together (4096^2 FP32: 64 rows 119 us, 32 rows and two rounds 134, 60 rows
 // and a second round of a few blocks 157); one block where that would leave fewer
 // than six rows to set against the two extra rows of step n (1024^2: 8 rows 9.8 us,
 // 4 rows 10.0).
+struct TwoShape {
+    int nblkx, cols, threads, rows, tiles;
+};
+
+static int two_cols(int nx, int halo, int max_threads)
+{
+    const int max_cols = (max_threads - halo - 1) / halo * halo;
+    const int nblkx = (nx + max_cols - 1) / max_cols;
+    return ((nx + nblkx - 1) / nblkx + halo - 1) / halo * halo;
+}
+
+static TwoShape two_shape(const GridArgs& g, int halo, int max_threads, int max_rows, int num_cu)
+{
+    TwoShape s;
+    s.cols = two_cols(g.nx, halo, max_threads);
+    s.nblkx = (g.nx + s.cols - 1) / s.cols;
+    s.threads = (halo + s.cols + 1 + 63) / 64 * 64;
+    auto rows_for = [&](int per_cu) {
+        const int chunks = max(1, per_cu * num_cu / s.nblkx);
+        return (g.ny + chunks - 1) / chunks;
+    };
+    s.rows = rows_for(2);
+    if (s.rows < 6) s.rows = rows_for(1);
+    s.rows = min(max(s.rows, 4), max_rows);
+    s.tiles = (g.ny + s.rows - 1) / s.rows * s.nblkx;
+    return s;
+}
+
 template <typename T>
 hipError_t launch_grid_two(const T* src, T* dst, const GridArgs& g, int num_cu, hipStream_t s)
 {
-    constexpr int kHalo = 128 / (int)sizeof(T);
-    constexpr int max_threads = sizeof(T) == 4 ? 576 : 512;
-    constexpr int max_cols = (max_threads - kHalo - 1) / kHalo * kHalo;
-    const int nblkx = (g.nx + max_cols - 1) / max_cols;
-    const int cols = ((g.nx + nblkx - 1) / nblkx + kHalo - 1) / kHalo * kHalo;
-    const int threads = (kHalo + cols + 1 + 63) / 64 * 64;
-    auto rows_for = [&](int per_cu) {
-        const int chunks = max(1, per_cu * num_cu / nblkx);
-        return (g.ny + chunks - 1) / chunks;
-    };
-    int rows = rows_for(2);
-    if (rows < 6) rows = rows_for(1);
-    rows = max(rows, 4);
-    const int tiles = (g.ny + rows - 1) / rows * nblkx;
-    const dim3 grid((unsigned)((tiles + kNumXcd - 1) / kNumXcd * kNumXcd));
+    const TwoShape p = two_shape(g, 128 / (int)sizeof(T), sizeof(T) == 4 ? kTwoMaxThreads : 512,
+                                 1 << 20, num_cu);
+    const dim3 grid((unsigned)((p.tiles + kNumXcd - 1) / kNumXcd * kNumXcd));
     const unsigned bytes = (unsigned)(9ull * g.ny * g.nxp * sizeof(T));
-    if (2.0 * bytes > kPlainStoreMaxBytes)
-        hipLaunchKernelGGL((k_grid_two<T, true>), grid, dim3(threads), 0, s, src, dst, g, bytes,
-                           rows, cols, nblkx);
-    else
-        hipLaunchKernelGGL((k_grid_two<T, false>), grid, dim3(threads), 0, s, src, dst, g, bytes,
-                           rows, cols, nblkx);
+    const auto f = 2.0 * bytes > kPlainStoreMaxBytes ? &k_grid_two<T, true, false, false>
+                                                     : &k_grid_two<T, false, false, false>;
+    hipLaunchKernelGGL(f, grid, dim3(p.threads), 0, s, src, dst, g, bytes, p.rows, p.cols, p.nblkx,
+                       TwoForce(), (const InstDev*)nullptr, (const TwoTile*)nullptr);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_grid_pair(const T* src, T* dst, const GridArgs& g, const TwoForce& f, int num_cu,
+                            hipStream_t s)
+{
+    const TwoShape p = two_shape(g, 128 / (int)sizeof(T), sizeof(T) == 4 ? kTwoMaxThreads : 512,
+                                 kTwoMaxRows, num_cu);
+    const dim3 grid((unsigned)((p.tiles + kNumXcd - 1) / kNumXcd * kNumXcd));
+    const unsigned bytes = (unsigned)(9ull * g.ny * g.nxp * sizeof(T));
+    const auto k = 2.0 * bytes > kPlainStoreMaxBytes ? &k_grid_two<T, true, true, false>
+                                                     : &k_grid_two<T, false, true, false>;
+    hipLaunchKernelGGL(k, grid, dim3(p.threads), 0, s, src, dst, g, bytes, p.rows, p.cols, p.nblkx,
+                       f, (const InstDev*)nullptr, (const TwoTile*)nullptr);
+    return hipGetLastError();
+}
+
+// Tiles of the batched pass of two steps, with the same thread and row count for
+// every lattice; the waves of a block past a narrow lattice's columns leave at
+// once.  Small blocks and several rounds of them, since the lattices differ in
+// width: 256 lattices of 128-512 x 72-128, us per step with at most (threads, blocks
+// per compute unit): (512, 2) 134, (320, 3) 127, (320, 6) 112, (320, 12) 105,
+// (320, 20) 105, (192, 12) 110, (576, 12) 107; one pass per step 129.  Returns the
+// count, a multiple of kNumXcd; `out` may be NULL.
+int pair_tiles(const GridArgs* g, int n, int real_bytes, TwoTile* out, int& threads, int& rows)
+{
+    const int halo = 128 / real_bytes;
+    threads = 320;
+    const long long want = 12 * 256;
+    auto count = [&](int r) {
+        long long t = 0;
+        for (int i = 0; i < n; i++) {
+            const int c = two_cols(g[i].nx, halo, threads);
+            t += (long long)((g[i].nx + c - 1) / c) * ((g[i].ny + r - 1) / r);
+        }
+        return t;
+    };
+    rows = 4;
+    while (rows < kTwoMaxRows && count(rows) > want) rows++;
+    int t = 0;
+    for (int i = 0; i < n; i++) {
+        const int c = two_cols(g[i].nx, halo, threads);
+        for (int y = 0; y < g[i].ny; y += rows)
+            for (int x = 0; x < g[i].nx; x += c, t++)
+                if (out) out[t] = {i, x, c, y};
+    }
+    for (; t % kNumXcd; t++)
+        if (out) out[t] = {-1, 0, 0, 0};
+    return t;
+}
+
+template <typename T>
+hipError_t launch_grid_pair_batch(const T* src, T* dst, const TwoForce& f, const InstDev* inst,
+                                  const TwoTile* table, int tiles, int rows, int threads, bool nt,
+                                  hipStream_t s)
+{
+    const dim3 grid((unsigned)tiles);
+    GridArgs g = {};
+    const auto k = nt ? &k_grid_two<T, true, true, true> : &k_grid_two<T, false, true, true>;
+    hipLaunchKernelGGL(k, grid, dim3(threads), 0, s, src, dst, g, 0u, rows, 0, 1, f, inst, table);
     return hipGetLastError();
 }
 
@@ -1891,7 +2156,7 @@ __device__ __forceinline__ void ib_block(const IBArgs<T>& a0, unsigned char* sme
     // ---- near region of this step's grid update (overlapped schedule): the
     // bounding box of x^n and x^{n-1} = x^n - d^n plus 5 cells covers the
     // supports of F^n and F^{n-1} and the patch the next IB launch stages
-    if (!STEP && a.rects) {
+    if (a.rects) {
         float nmn[2] = {3e38f, 3e38f}, nmx[2] = {-3e38f, -3e38f};
         for (int v = tid; v < nv; v += nt) {
             const float x = (float)S.px[v], y = (float)S.py[v];
@@ -1910,7 +2175,7 @@ __device__ __forceinline__ void ib_block(const IBArgs<T>& a0, unsigned char* sme
         r.y1 = (int)(refy + (long long)floorf(nmx[1])) + 5;
         if (tid == 0) a.rects[c] = r;
         const RectUnits u = rect_units(r, g);
-        const int units = u.nrows * u.nsegs;
+        const int units = a.near_map ? u.nrows * u.nsegs : 0;
         for (int q = tid; q < units; q += nt) {
             const int ri = q / u.nsegs, si = q - ri * u.nsegs;
             int y = u.ry0 + ri;
@@ -2050,12 +2315,17 @@ __global__ __launch_bounds__(kIBThreads) void k_step(IBArgs<T> a0, int cap_block
                                                      const long long* __restrict__ fib_now,
                                                      const int* __restrict__ flags_now,
                                                      long long* __restrict__ fib_old,
-                                                     int* __restrict__ flags_old, GridArgs g)
+                                                     int* __restrict__ flags_old, GridArgs g,
+                                                     PairNear near)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ double red[kIBThreads / 64][8];
     if ((int)blockIdx.x < cap_blocks) {
         if ((int)blockIdx.x < ncap) ib_block<T, DYN, true, RIGID>(a0, smem, red);
+        return;
+    }
+    if (near.inst) {
+        pair_near(src, dst, fib_now, near, (int)blockIdx.x - cap_blocks);
         return;
     }
     constexpr int ROWS = kStepRows, WAVES = kIBThreads / 64;
@@ -2075,21 +2345,47 @@ __global__ __launch_bounds__(kIBThreads) void k_step(IBArgs<T> a0, int cap_block
 }
 
 template <typename T>
-hipError_t launch_step(const IBArgs<T>& a, int ncap, bool rigid, size_t lds_bytes, const T* src, T* dst,
-                       const long long* fib_now, const int* flags_now, long long* fib_old,
-                       int* flags_old, const GridArgs& g, hipStream_t s)
+static hipError_t launch_step_blocks(const IBArgs<T>& a, int ncap, bool rigid, size_t lds_bytes,
+                                     int blocks, const T* src, T* dst, const long long* fib_now,
+                                     const int* flags_now, long long* fib_old, int* flags_old,
+                                     const GridArgs& g, const PairNear& near, hipStream_t s)
 {
     const int cap_blocks = (ncap + kNumXcd - 1) / kNumXcd * kNumXcd;
-    const int segs = (g.nx + kSegW - 1) / kSegW;
-    const int rows = kIBThreads / 64 * kStepRows;
-    const int tiles = (g.ny + rows - 1) / rows * segs;
-    const dim3 grid((unsigned)(cap_blocks + (tiles + kNumXcd - 1) / kNumXcd * kNumXcd));
+    const dim3 grid((unsigned)(cap_blocks + blocks));
     const auto f = !a.dynamic ? &k_step<T, false, false>
                    : rigid    ? &k_step<T, true, true>
                               : &k_step<T, true, false>;
     hipLaunchKernelGGL(f, grid, dim3(kIBThreads), lds_bytes, s, a, cap_blocks, ncap, src, dst,
-                       fib_now, flags_now, fib_old, flags_old, g);
+                       fib_now, flags_now, fib_old, flags_old, g, near);
     return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_step(const IBArgs<T>& a, int ncap, bool rigid, size_t lds_bytes, const T* src, T* dst,
+                       const long long* fib_now, const int* flags_now, long long* fib_old,
+                       int* flags_old, const GridArgs& g, hipStream_t s)
+{
+    const int segs = (g.nx + kSegW - 1) / kSegW;
+    const int rows = kIBThreads / 64 * kStepRows;
+    const int tiles = (g.ny + rows - 1) / rows * segs;
+    return launch_step_blocks(a, ncap, rigid, lds_bytes, (tiles + kNumXcd - 1) / kNumXcd * kNumXcd,
+                              src, dst, fib_now, flags_now, fib_old, flags_old, g, PairNear(), s);
+}
+
+// The capsules' part with the near cells and the clearing of a pair of steps
+// (`near`), or by itself (near.inst = NULL).  Blocks per capsule: its near cells
+// are about 40 wave rows.
+template <typename T>
+hipError_t launch_step_near(const IBArgs<T>& a, int ncap, bool rigid, size_t lds_bytes, const T* src,
+                            T* dst, const long long* fib_now, PairNear near, int n_inst,
+                            int max_flags, hipStream_t s)
+{
+    near.per_cap = min(5, max(1, 1024 / max(1, ncap)));
+    near.near_blocks = ncap * near.per_cap;
+    near.parts = clear_parts(max_flags);
+    return launch_step_blocks<T>(a, ncap, rigid, lds_bytes,
+                                 near.inst ? near.near_blocks + n_inst * near.parts : 0, src, dst,
+                                 fib_now, nullptr, nullptr, nullptr, GridArgs(), near, s);
 }
 
 template <typename T>
@@ -2563,6 +2859,13 @@ hipError_t launch_set_nodes(T* nodes, CapsuleDev* caps, int cap, int nv, int nod
     template hipError_t launch_grid_step<T>(const T*, T*, const long long*, const int*,           \
                                             long long*, int*, const GridArgs&, hipStream_t);      \
     template bool grid_two_pays<T>(const GridArgs&);                                              \
+    template hipError_t launch_grid_pair<T>(const T*, T*, const GridArgs&, const TwoForce&, int,  \
+                                            hipStream_t);                                         \
+    template hipError_t launch_grid_pair_batch<T>(const T*, T*, const TwoForce&, const InstDev*,  \
+                                                  const TwoTile*, int, int, int, bool,            \
+                                                  hipStream_t);                                   \
+    template hipError_t launch_step_near<T>(const IBArgs<T>&, int, bool, size_t, const T*, T*,    \
+                                            const long long*, PairNear, int, int, hipStream_t);   \
     template hipError_t launch_grid_two<T>(const T*, T*, const GridArgs&, int, hipStream_t);      \
     template hipError_t launch_grid_step_batch<T>(const T*, T*, const long long*, const int*,     \
                                                   long long*, int*, const InstDev*, const int2*,  \

@@ -155,3 +155,95 @@ def test_one_launch_per_step(name, real_bytes, mode):
         s.step(4)
     same()
     assert a.check() == b.check()
+
+
+def _pair_case(name, real_bytes, mode):
+    """Lattices past the size from which two steps with capsules share a pass."""
+    u, tau = 0.02, 0.8
+
+    def lattice(nx, ny, shapes, **kw):
+        cfg = wl._base(name, nx, ny, tau, real_bytes, mode, 0, **kw)
+        cfg["capsules"] = [wl.capsule(p, 0.05, 0.0, 1.0, 1.2) for p in shapes]
+        return cfg
+
+    if name == "box":  # both axes wrap: a capsule across the corner, one across rows of blocks
+        n = 2050 if real_bytes == 4 else 1450
+        return lattice(n, n - 3, [_ellipse(2.0, n - 4.5, 6.0, 5.0, 40),
+                                  _ellipse(500.0, 66.0, 8.0, 5.0, 48, 0.5)],
+                       periodic_y=1, init_profile=wl.INIT_UNIFORM, init_u=(u, -u))
+    if name == "channel":  # capsules beside the walls and each other, over the wrap
+        return lattice(4097, 1100, [_ellipse(3.0, 9.2, 6.0, 6.0, 40),
+                                    _ellipse(64.0, 1089.0, 9.0, 6.0, 60),
+                                    _ellipse(543.0, 500.0, 7.0, 7.0, 50),
+                                    _ellipse(559.5, 501.0, 7.0, 7.0, 50)],
+                       init_profile=wl.INIT_POISEUILLE,
+                       body_force_x=wl.poiseuille_body_force(tau, 1100, u))
+    walls = dict(u_bottom=-u, u_top=u, init_profile=wl.INIT_COUETTE)
+    n = 1 if real_bytes == 4 else 2
+    return [lattice(1500 // n, 1100, [_ellipse(250.0, 30.0, 7.0, 6.0, 40)], **walls),
+            lattice(40, 33, [_ellipse(20.0, 16.0, 5.0, 5.0, 30)], **walls),
+            lattice(1457 // n, 1300, [_ellipse(300.0, 900.0, 7.0, 6.0, 40),
+                                      _ellipse(2.0, 9.5, 6.0, 6.0, 40)], **walls),
+            lattice(257, 64, [_ellipse(255.0, 30.0, 8.0, 6.0, 40)], periodic_y=1, init_profile=wl.INIT_UNIFORM,
+                    init_u=(u, u)),
+            lattice(513, 1200, [_ellipse(511.0, 600.0, 8.0, 6.0, 40)], **walls)]
+
+
+@pytest.mark.parametrize("mode", ["dynamic", "kinematic"])
+@pytest.mark.parametrize("real_bytes", [4, 8])
+@pytest.mark.parametrize("name", ["box", "channel", "batch"])
+def test_two_steps_with_capsules(name, real_bytes, mode):
+    """Two steps with capsules in one pass (the automatic schedule of large
+    lattices and batches): the same bits as a grid and an IB launch per step,
+    also for odd counts and across a change of schedule between calls."""
+    cfg = _pair_case(name, real_bytes, mode)
+    make = lbib.Batch if isinstance(cfg, list) else lbib.Sim
+    a, b = make(cfg), make(cfg)
+    b.set_overlap(False)
+
+    def same():
+        for i in range(len(cfg) if isinstance(cfg, list) else 1):
+            np.testing.assert_array_equal(a.pops(i), b.pops(i))
+            np.testing.assert_array_equal(a.force(i), b.force(i))
+        for c in range(len(a.nv)):
+            np.testing.assert_array_equal(np.stack(a.capsule(c)), np.stack(b.capsule(c)))
+
+    for n in (2, 5, 1, 4):
+        a.step(n)
+        b.step(n)
+        same()
+    a.set_overlap(False)
+    b.set_overlap(None)
+    for s in (a, b):
+        s.step(4)
+    same()
+    if not isinstance(cfg, list) and real_bytes == 4:
+        a.set_overlap(True)
+        for s in (a, b):
+            s.step(3)
+        same()
+    assert a.check() == 0 and b.check() == 0
+
+
+@pytest.mark.parametrize("mode", ["dynamic", "kinematic"])
+def test_capsules_under_capture(mode):
+    """A caller's graph of two steps, recorded after steps of the automatic
+    schedule, repeats with the caller's own steps between its replays."""
+    import torch
+    cfg = _fused_case("walls", 4, mode)
+    st = torch.cuda.Stream()
+    a, b = lbib.Sim(cfg, stream=st), lbib.Sim(cfg)
+    b.set_overlap(False)
+    a.step(3)
+    b.step(3)
+    st.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=st):
+        a.step(2)
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        a.step(4)
+        b.step(6)
+        np.testing.assert_array_equal(a.pops(), b.pops())
+        np.testing.assert_array_equal(np.stack(a.capsule(0)), np.stack(b.capsule(0)))
