@@ -903,6 +903,7 @@ static IBArgs<T> ib_args(const lbib_ctx* c, long long n, int phase)
     a.done_count = nullptr;
     a.max_edge = c->max_edge;
     a.max_dA = c->max_dA;
+    a.bounds = nullptr;
     return a;
 }
 
@@ -1014,7 +1015,7 @@ static hipError_t do_grid_two(lbib_ctx* c, void* p)
 }
 
 template <typename T>
-static lbib_status launch_contact_t(lbib_ctx* c)
+static lbib_status launch_contact_t(lbib_ctx* c, bool bounds = true)
 {
     ContactArgs<T> a;
     a.nodes = reinterpret_cast<T*>(bufp(c, LBIB_BUF_NODES));
@@ -1024,7 +1025,7 @@ static lbib_status launch_contact_t(lbib_ctx* c)
     a.ncap = c->ncap;
     a.max_nv = c->L.max_nv;
     a.cutoff = c->contact_cutoff;
-    HIPCHK(c, launch_contact<T>(a, c->stream));
+    HIPCHK(c, launch_contact<T>(a, bounds, c->stream));
     return LBIB_OK;
 }
 
@@ -1256,13 +1257,17 @@ static lbib_status step_pair_t(lbib_ctx* c, int nsteps)
 // Fused schedule of one lattice: one launch per step (k_step) after a first one
 // that spreads the forcing of the call's first step.  With the Dynamic scheme
 // the last launch also spreads the forcing of the step after it (phase A writes
-// no node state there), so that the next call goes without.
+// no node state there), so that the next call goes without.  The contact force
+// (Eq. 27) is taken before each launch with a Dynamic node update; in the
+// Kinematic scheme it comes between the update and the forcing, which then take a
+// launch each.  k_step leaves the bounding boxes that the contact kernel needs.
 template <typename T>
 static lbib_status step_fused_t(lbib_ctx* c, int nsteps, bool contact)
 {
     const GridArgs g = grid_args(c->L.inst[0]);
+    const bool split = contact && c->mode != LBIB_DYNAMIC;
     const bool ahead = c->mode == LBIB_DYNAMIC && !contact;
-    if (!c->a_ready) {
+    if (!split && !c->a_ready) {
         IBLaunch<T> q{c->steps, c->steps == 0 ? (PH_PRIME | PH_A) : PH_A, false};
         HIPCHK(c, do_ib<T>(c, &q));
     }
@@ -1270,14 +1275,20 @@ static lbib_status step_fused_t(lbib_ctx* c, int nsteps, bool contact)
         const long long n = c->steps + k;
         const bool more = k + 1 < nsteps || ahead;
         if (contact) {
-            lbib_status s = launch_contact_t<T>(c);
+            lbib_status s = launch_contact_t<T>(c, k == 0);
             if (s != LBIB_OK) return s;
         }
+        if (split) {
+            IBLaunch<T> q{n, n == 0 ? (PH_PRIME | PH_A) : PH_A, false};
+            HIPCHK(c, do_ib<T>(c, &q));
+        }
         // IB of step n + 1 from P^n and F^n, its forcing into the spare level
-        IBArgs<T> a = ib_args<T>(c, n, more ? (PH_B | PH_A) : PH_B);
+        IBArgs<T> a = ib_args<T>(c, n, more && !split ? (PH_B | PH_A) : PH_B);
         a.fib_prev = fib(c, c->lv_next);
         a.fib_next = fib(c, c->lv_spare);
         a.flags_next = flags(c, c->lv_spare);
+        if (contact && k + 1 < nsteps)
+            a.bounds = reinterpret_cast<float4*>(bufp(c, LBIB_BUF_CAPS) + c->L.bounds);
         HIPCHK(c, launch_step<T>(a, c->ncap, any_rigid(c), c->lds_use, static_cast<const T*>(pops(c, n)),
                                  static_cast<T*>(pops(c, n + 1)), fib(c, c->lv_next),
                                  flags(c, c->lv_next), fib(c, c->lv_prev), flags(c, c->lv_prev), g,
@@ -1395,9 +1406,7 @@ static lbib_status step_t(lbib_ctx* c, int nsteps)
                         exchange;
     if (direct && can_overlap && nsteps >= 2 && pair_pays<T>(c)) return step_pair_t<T>(c, nsteps);
     if (can_overlap && want) return step_overlap_t<T>(c, nsteps);
-    // one launch per step (the contact force of the Kinematic scheme sits between
-    // the node update and the forcing, so it keeps separate launches)
-    if (direct && c->L.inst.size() == 1 && !(contact && !dyn))
+    if (direct && c->L.inst.size() == 1)
         return step_fused_t<T>(c, nsteps, contact);
     // replays of captured blocks for the inner steps; timed runs launch directly
     const bool graphs = c->graph == 1 && !c->timing;

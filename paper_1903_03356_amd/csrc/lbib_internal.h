@@ -20,12 +20,15 @@ constexpr int kIBThreads = 512;  // IB kernel block (one block per capsule)
 constexpr int kNodeScratch = 22;
 constexpr int kNodeLdsArrays = 12 + kNodeScratch;
 // contact kernel: at most this many thread groups share one capsule's pairs;
-// its LDS holds eight FP64 node arrays and two FP64 partial sums per thread
+// its LDS holds six FP64 node arrays, the staged nodes of the capsules near it
+// (x, y) and two FP64 partial sums per thread
 constexpr int kContactGroups = 8;
 constexpr int kContactChunk = 128;  // capsule records staged per round in the contact kernel
+constexpr int contact_stage(int max_nv) { return max_nv > 1024 ? max_nv : 1024; }
 constexpr size_t contact_lds_bytes(int max_nv)
 {
-    return sizeof(double) * (8 * (size_t)max_nv + 2 * (size_t)kIBThreads);
+    return sizeof(double) *
+           (6 * (size_t)max_nv + 2 * (size_t)contact_stage(max_nv) + 2 * (size_t)kIBThreads);
 }
 
 // The spread force is accumulated as a signed 64-bit fixed-point number with
@@ -161,6 +164,7 @@ struct IBArgs {
     // membrane checks of the force pass, 0 = off: longest element length and
     // largest |A / A0 - 1| before ST_EDGE / ST_AREA
     float max_edge, max_dA;
+    float4* bounds;  // k_step: if not NULL, the new bounding boxes (ContactArgs)
 };
 
 // Node tape of the gradient runs: per time level, the fields NF_HX .. NF_UY
@@ -258,7 +262,7 @@ hipError_t launch_grid_near(const T* src, T* dst, const long long* fib_now, cons
                             long long* fib_old, int* flags_old, const NearRect* rects,
                             const CapsuleDev* caps, const InstDev* inst, int ncap, hipStream_t s);
 template <typename T>
-hipError_t launch_contact(const ContactArgs<T>& a, hipStream_t s);
+hipError_t launch_contact(const ContactArgs<T>& a, bool bounds, hipStream_t s);  // bounds: not yet there
 template <typename T>
 hipError_t launch_spread_tape(const SpreadTapeArgs<T>& a, int ncap, int nsteps, hipStream_t s);
 template <typename T>

@@ -331,6 +331,7 @@ __device__ void pair_near(const T* __restrict__ src, T* __restrict__ dst,
     if (block >= p.near_blocks) {
         const int b = block - p.near_blocks, i = b / p.parts;
         const InstDev& I = p.inst[i];
+#pragma unroll
         for (int k = 0; k < 2; k++)
             clear_segments(p.fib[k] + I.fib_off, p.flags[k] + I.flag_off, I, b - i * p.parts);
         return;
@@ -1818,8 +1819,9 @@ __device__ void rigid_update(const IBArgs<T>& a, const Scratch<T>& S, const Patc
 // the block takes the moments of its patch at time n from its own grid step
 // there (step_cells), not from P^n.
 // Such a launch runs phases B and A of started capsules and no diagnostics,
-// near regions or tape; without rigid particles (RIGID) their code is left out too.
-template <typename T, bool DYN, bool STEP, bool RIGID>
+// near regions or tape; without EXTRA the code of rigid particles and of the contact
+// force's boxes is left out too (0.2 us of a lone capsule's chain).
+template <typename T, bool DYN, bool STEP, bool EXTRA>
 __device__ __forceinline__ void ib_block(const IBArgs<T>& a0, unsigned char* smem,
                                          double (*red)[8])
 {
@@ -1883,7 +1885,7 @@ __device__ __forceinline__ void ib_block(const IBArgs<T>& a0, unsigned char* sme
 
     int st = 0;
     const bool prime = !STEP && (a.phase & PH_PRIME) && !cap.primed;
-    const bool rigid = RIGID && cap.rigid;
+    const bool rigid = DYN && EXTRA && cap.rigid;
     const bool doB = (a.phase & PH_B) && cap.primed;
     const bool doA = (a.phase & PH_A) != 0;
     int wx = cap.wx, wy = cap.wy;
@@ -2153,6 +2155,22 @@ __device__ __forceinline__ void ib_block(const IBArgs<T>& a0, unsigned char* sme
         __syncthreads();
     }
 
+    // ---- bounding box for the contact force's launch (k_bounds)
+    if (STEP && EXTRA && a.bounds) {
+        float bmn[2] = {3e38f, 3e38f}, bmx[2] = {-3e38f, -3e38f};
+        for (int v = tid; v < nv; v += nt) {
+            const float x = (float)S.px[v], y = (float)S.py[v];
+            bmn[0] = fminf(bmn[0], x);
+            bmn[1] = fminf(bmn[1], y);
+            bmx[0] = fmaxf(bmx[0], x);
+            bmx[1] = fmaxf(bmx[1], y);
+        }
+        block_minmax(bmn, bmx, red);
+        if (tid == 0)
+            a.bounds[c] = make_float4((float)cap.ref_x + bmn[0], (float)cap.ref_y + bmn[1],
+                                      (float)cap.ref_x + bmx[0], (float)cap.ref_y + bmx[1]);
+    }
+
     // ---- near region of this step's grid update (overlapped schedule): the
     // bounding box of x^n and x^{n-1} = x^n - d^n plus 5 cells covers the
     // supports of F^n and F^{n-1} and the patch the next IB launch stages
@@ -2283,7 +2301,7 @@ __global__ __launch_bounds__(kIBThreads) void k_ib(IBArgs<T> a0)
     if (WIDE) __builtin_amdgcn_s_setprio(0);
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ double red[kIBThreads / 64][8];
-    ib_block<T, DYN, false, DYN>(a0, smem, red);  // every exit of ib_block is block-uniform
+    ib_block<T, DYN, false, true>(a0, smem, red);  // every exit of ib_block is block-uniform
     if (a0.done_count) {
         // the block's stores (near map, force level, node state) are made
         // visible device-wide before the count announces them
@@ -2308,7 +2326,7 @@ __global__ __launch_bounds__(kIBThreads) void k_ib(IBArgs<T> a0)
 //   the step) 22.2 -> 22.4
 // Rows per wave: the node arrays and the patch in LDS leave one or two blocks on
 // a compute unit, so a wave takes ROWS rows with their loads in flight together.
-template <typename T, bool DYN, bool RIGID>
+template <typename T, bool DYN, bool EXTRA>
 __global__ __launch_bounds__(kIBThreads) void k_step(IBArgs<T> a0, int cap_blocks, int ncap,
                                                      const T* __restrict__ src,
                                                      T* __restrict__ dst,
@@ -2321,7 +2339,7 @@ __global__ __launch_bounds__(kIBThreads) void k_step(IBArgs<T> a0, int cap_block
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ double red[kIBThreads / 64][8];
     if ((int)blockIdx.x < cap_blocks) {
-        if ((int)blockIdx.x < ncap) ib_block<T, DYN, true, RIGID>(a0, smem, red);
+        if ((int)blockIdx.x < ncap) ib_block<T, DYN, true, EXTRA>(a0, smem, red);
         return;
     }
     if (near.inst) {
@@ -2352,9 +2370,9 @@ static hipError_t launch_step_blocks(const IBArgs<T>& a, int ncap, bool rigid, s
 {
     const int cap_blocks = (ncap + kNumXcd - 1) / kNumXcd * kNumXcd;
     const dim3 grid((unsigned)(cap_blocks + blocks));
-    const auto f = !a.dynamic ? &k_step<T, false, false>
-                   : rigid    ? &k_step<T, true, true>
-                              : &k_step<T, true, false>;
+    const bool extra = rigid || a.bounds;
+    const auto f = !a.dynamic ? (extra ? &k_step<T, false, true> : &k_step<T, false, false>)
+                              : (extra ? &k_step<T, true, true> : &k_step<T, true, false>);
     hipLaunchKernelGGL(f, grid, dim3(kIBThreads), lds_bytes, s, a, cap_blocks, ncap, src, dst,
                        fib_now, flags_now, fib_old, flags_old, g, near);
     return hipGetLastError();
@@ -2397,7 +2415,8 @@ size_t ib_lds_bytes(int patch_cap, int max_nv)
 template <typename T>
 hipError_t ib_set_lds_limit(size_t bytes)
 {
-    const void* fns[7] = {reinterpret_cast<const void*>(&k_step<T, true, true>),
+    const void* fns[8] = {reinterpret_cast<const void*>(&k_step<T, false, true>),
+                          reinterpret_cast<const void*>(&k_step<T, true, true>),
                           reinterpret_cast<const void*>(&k_step<T, true, false>),
                           reinterpret_cast<const void*>(&k_step<T, false, false>),
                           reinterpret_cast<const void*>(&k_ib<T, true, false>),
@@ -2526,12 +2545,15 @@ __global__ __launch_bounds__(kIBThreads) void k_bounds(ContactArgs<T> a)
 // node's two elements.  Distances take the nearest periodic image.  One
 // block per capsule; capsules whose boxes (grown by the cutoff) miss this
 // one's are skipped, the others are staged in LDS.  FP64.
-// The pairs (node of this capsule, node of the other) are dealt to
-// K = min(nt / nv, kContactGroups) groups of nv threads: thread t takes node
-// t % nv against every K-th node of the other capsule from t / nv on, and the
-// K partial sums of a node are added in group order (fixed, so runs repeat bit
-// for bit).  The other capsules' records are staged in LDS in chunks, and
-// each capsule is staged at the periodic image nearest to this one, so that a
+// The block first lists the capsules near it (one record per thread, kContactChunk
+// at a time), stages the nodes of as many of them as fit one after the other and
+// then deals the pairs (node of this capsule, staged node) to K = min(nt / nv,
+// kContactGroups) groups of nv threads: thread t takes node t % nv against every
+// K-th staged node from t / nv on, and the K partial sums of a node are added in
+// group order (fixed, so runs repeat bit for bit).  Bound by the chain of its
+// dependent loads and barriers: staged one capsule at a time, 16 capsules of 96 nodes
+// side by side took 10.7 us, now 7.4.
+// Each capsule is staged at the periodic image nearest to this one, so that a
 // pair's own image needs the division only where |dx| still exceeds half the
 // period (below it the rounded quotient is 0); the root and the force only for
 // pairs whose squared distance is below the cutoff's.
@@ -2544,21 +2566,51 @@ __global__ __launch_bounds__(kIBThreads) void k_contact(ContactArgs<T> a)
     const int nv = cap.nv, off = cap.node_offset;
     const size_t NS = a.node_stride;
     const T* N = a.nodes;
+    const int stage = contact_stage(a.max_nv);
     double* X = reinterpret_cast<double*>(smem);
     double* Y = X + a.max_nv;
     double* IX = Y + a.max_nv;  // inward normal
     double* IY = IX + a.max_nv;
     double* FX = IY + a.max_nv;
     double* FY = FX + a.max_nv;
-    double* BX = FY + a.max_nv;  // the other capsule, in this capsule's frame
-    double* BY = BX + a.max_nv;
-    double* PX = BY + a.max_nv;  // per-thread partial sums, nt each
+    double* BX = FY + a.max_nv;  // nodes of the other capsules, in this capsule's frame
+    double* BY = BX + stage;
+    double* PX = BY + stage;  // per-thread partial sums, nt each
     double* PY = PX + nt;
     for (int v = tid; v < nv; v += nt) {
         X[v] = (double)N[NF_HX * NS + off + v] + (double)N[NF_LX * NS + off + v];
         Y[v] = (double)N[NF_HY * NS + off + v] + (double)N[NF_LY * NS + off + v];
         FX[v] = FY[v] = 0.0;
     }
+    const float4 me = a.bounds[c];
+    const double Lx = cap.nx, Ly = cap.ny;
+    const double C = 1e-4 / (8.0 * sqrt(2.0));
+    const float cut = (float)a.cutoff;
+    // squared-distance screen, a little wider than the cutoff: every pair the
+    // exact test below accepts passes it
+    const double cut2 = a.cutoff * a.cutoff * (1.0 + 1e-6);
+    const int K = nv > 0 ? max(1, min(nt / nv, kContactGroups)) : 1;
+    const int vq = nv > 0 ? tid % nv : 0, kq = nv > 0 ? tid / nv : 0;
+    const bool one = nv <= nt;  // a thread takes the pairs of one node
+    double fx = 0.0, fy = 0.0;
+    // the force on node v from the staged nodes j0, j0 + step, ... below n
+    auto pair_sum = [&](int v, int j0, int step, int n, double& fx, double& fy) {
+        const double xv = X[v], yv = Y[v];
+        for (int j = j0; j < n; j += step) {
+            double dx = BX[j] - xv, dy = BY[j] - yv;
+            if (cap.periodic_x && fabs(dx) > 0.5 * Lx) dx -= Lx * rint(dx / Lx);
+            if (cap.periodic_y && fabs(dy) > 0.5 * Ly) dy -= Ly * rint(dy / Ly);
+            const double d2 = dx * dx + dy * dy;
+            if (d2 < cut2) {
+                const double d = sqrt(d2);
+                if (d < a.cutoff && d > 0.0) {
+                    const double mag = C * sqrt(1.0 / (d * d * d * d * d));
+                    fx += mag * IX[v];
+                    fy += mag * IY[v];
+                }
+            }
+        }
+    };
     __syncthreads();
     for (int v = tid; v < nv; v += nt) {
         const int vl = v == 0 ? nv - 1 : v - 1, vr = v + 1 == nv ? 0 : v + 1;
@@ -2570,38 +2622,18 @@ __global__ __launch_bounds__(kIBThreads) void k_contact(ContactArgs<T> a)
         IX[v] = -nx / nn;
         IY[v] = -ny / nn;
     }
-    const float4 me = a.bounds[c];
-    const double Lx = cap.nx, Ly = cap.ny;
-    const double C = 1e-4 / (8.0 * sqrt(2.0));
-    const float cut = (float)a.cutoff;
-    // squared-distance screen, a little wider than the cutoff: every pair the
-    // exact test below accepts passes it
-    const double cut2 = a.cutoff * a.cutoff * (1.0 + 1e-6);
-    const int K = nv > 0 ? max(1, min(nt / nv, kContactGroups)) : 1;
-    const int vq = nv > 0 ? tid % nv : 0, kq = nv > 0 ? tid / nv : 0;
-    // the other capsules' records, kContactChunk at a time, one per thread
-    // (their loads in flight together, not one dependent load per capsule)
-    __shared__ float4 s_box[kContactChunk];
+    // the capsules near this one, in order
     __shared__ double s_rx[kContactChunk], s_ry[kContactChunk];
-    __shared__ int s_nv[kContactChunk], s_off[kContactChunk], s_inst[kContactChunk];
+    __shared__ int s_nv[kContactChunk], s_off[kContactChunk], s_count[kContactChunk / 64];
     for (int o0 = 0; o0 < a.ncap; o0 += kContactChunk) {
-        const int m = min(kContactChunk, a.ncap - o0);
-        __syncthreads();  // the last chunk's records are read no more
-        if (tid < m) {
+        bool hit = false;
+        double rx = 0.0, ry = 0.0;
+        int onv = 0, ooff = 0;
+        if (tid < kContactChunk && o0 + tid < a.ncap) {
             const CapsuleDev& r = a.caps[o0 + tid];
-            s_box[tid] = a.bounds[o0 + tid];
-            s_rx[tid] = r.ref_x;
-            s_ry[tid] = r.ref_y;
-            s_nv[tid] = r.nv;
-            s_off[tid] = r.node_offset;
-            s_inst[tid] = r.inst;
-        }
-        __syncthreads();
-        for (int q = 0; q < m; q++) {
-            const int o = o0 + q;
-            if (o == c || s_inst[q] != cap.inst) continue;
-            const float4 ob = s_box[q];
-            const int onv = s_nv[q], ooff = s_off[q];
+            const float4 ob = a.bounds[o0 + tid];
+            onv = r.nv;
+            ooff = r.node_offset;
             // box test with the nearest periodic image in x (and y when periodic)
             float sx = (0.5f * (ob.x + ob.z)) - (0.5f * (me.x + me.z));
             const float ix = cap.periodic_x ? rintf(sx / (float)Lx) : 0.0f;
@@ -2611,59 +2643,52 @@ __global__ __launch_bounds__(kIBThreads) void k_contact(ContactArgs<T> a)
             sy -= (float)Ly * iy;
             const float hx = 0.5f * ((ob.z - ob.x) + (me.z - me.x)) + cut;
             const float hy = 0.5f * ((ob.w - ob.y) + (me.w - me.y)) + cut;
-            if (fabsf(sx) > hx || fabsf(sy) > hy) continue;
-            __syncthreads();
-            // staged at the periodic image nearest to this capsule (box centres),
-            // so that the pair loop rarely needs the image division
-            const double rx = s_rx[q] - cap.ref_x - (double)ix * Lx;
-            const double ry = s_ry[q] - cap.ref_y - (double)iy * Ly;
-            for (int j = tid; j < onv; j += nt) {
-                BX[j] = rx + (double)N[NF_HX * NS + ooff + j] + (double)N[NF_LX * NS + ooff + j];
-                BY[j] = ry + (double)N[NF_HY * NS + ooff + j] + (double)N[NF_LY * NS + ooff + j];
-            }
-            __syncthreads();
-            // the force on node v from nodes j0, j0 + step, ... of the other capsule
-            auto pair_sum = [&](int v, int j0, int step, double& fx, double& fy) {
-                const double xv = X[v], yv = Y[v];
-                for (int j = j0; j < onv; j += step) {
-                    double dx = BX[j] - xv, dy = BY[j] - yv;
-                    if (cap.periodic_x && fabs(dx) > 0.5 * Lx) dx -= Lx * rint(dx / Lx);
-                    if (cap.periodic_y && fabs(dy) > 0.5 * Ly) dy -= Ly * rint(dy / Ly);
-                    const double d2 = dx * dx + dy * dy;
-                    if (d2 < cut2) {
-                        const double d = sqrt(d2);
-                        if (d < a.cutoff && d > 0.0) {
-                            const double mag = C * sqrt(1.0 / (d * d * d * d * d));
-                            fx += mag * IX[v];
-                            fy += mag * IY[v];
-                        }
-                    }
-                }
-            };
-            if (K == 1) {
-                for (int v = tid; v < nv; v += nt) {
-                    double fx = 0.0, fy = 0.0;
-                    pair_sum(v, 0, 1, fx, fy);
-                    FX[v] += fx;
-                    FY[v] += fy;
-                }
-            } else {
-                double fx = 0.0, fy = 0.0;
-                if (kq < K) pair_sum(vq, kq, K, fx, fy);
-                PX[tid] = fx;
-                PY[tid] = fy;
-                __syncthreads();
-                for (int v = tid; v < nv; v += nt) {
-                    double sx = 0.0, sy = 0.0;
-                    for (int k = 0; k < K; k++) {
-                        sx += PX[v + k * nv];
-                        sy += PY[v + k * nv];
-                    }
-                    FX[v] += sx;
-                    FY[v] += sy;
-                }
-            }
+            hit = o0 + tid != c && r.inst == cap.inst && !(fabsf(sx) > hx || fabsf(sy) > hy);
+            rx = r.ref_x - cap.ref_x - (double)ix * Lx;
+            ry = r.ref_y - cap.ref_y - (double)iy * Ly;
         }
+        const unsigned long long hits = __ballot(hit);
+        if (tid < kContactChunk && (tid & 63) == 0) s_count[tid >> 6] = __popcll(hits);
+        __syncthreads();
+        if (hit) {
+            int at = __popcll(hits & ((1ull << (tid & 63)) - 1));
+            for (int w = 0; w < tid >> 6; w++) at += s_count[w];
+            s_rx[at] = rx;
+            s_ry[at] = ry;
+            s_nv[at] = onv;
+            s_off[at] = ooff;
+        }
+        int n = 0;
+        for (int w = 0; w < kContactChunk / 64; w++) n += s_count[w];
+        __syncthreads();
+        for (int h0 = 0, h1 = 0; h0 < n; h0 = h1) {
+            int total = 0;
+            while (h1 < n && total + s_nv[h1] <= stage) total += s_nv[h1++];
+            for (int j = tid; j < total; j += nt) {
+                int h = h0, r = j;
+                while (r >= s_nv[h]) r -= s_nv[h++];
+                const size_t at = (size_t)s_off[h] + r;
+                BX[j] = s_rx[h] + (double)N[NF_HX * NS + at] + (double)N[NF_LX * NS + at];
+                BY[j] = s_ry[h] + (double)N[NF_HY * NS + at] + (double)N[NF_LY * NS + at];
+            }
+            __syncthreads();
+            if (one) {
+                if (kq < K) pair_sum(vq, kq, K, total, fx, fy);
+            } else {
+                for (int v = tid; v < nv; v += nt) pair_sum(v, 0, 1, total, FX[v], FY[v]);
+            }
+            __syncthreads();
+        }
+    }
+    if (one) {
+        PX[tid] = fx;
+        PY[tid] = fy;
+        __syncthreads();
+        for (int v = tid; v < nv; v += nt)
+            for (int k = 0; k < K; k++) {
+                FX[v] += PX[v + k * nv];
+                FY[v] += PY[v + k * nv];
+            }
     }
     T* W = a.nodes;
     for (int v = tid; v < nv; v += nt) {
@@ -2681,10 +2706,10 @@ hipError_t contact_set_lds_limit(int max_nv)
 }
 
 template <typename T>
-hipError_t launch_contact(const ContactArgs<T>& a, hipStream_t s)
+hipError_t launch_contact(const ContactArgs<T>& a, bool bounds, hipStream_t s)
 {
     if (a.ncap <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_bounds<T>, dim3(a.ncap), dim3(kIBThreads), 0, s, a);
+    if (bounds) hipLaunchKernelGGL(k_bounds<T>, dim3(a.ncap), dim3(kIBThreads), 0, s, a);
     hipLaunchKernelGGL(k_contact<T>, dim3(a.ncap), dim3(kIBThreads),
                        contact_lds_bytes(a.max_nv), s, a);
     return hipGetLastError();
@@ -2878,7 +2903,7 @@ hipError_t launch_set_nodes(T* nodes, CapsuleDev* caps, int cap, int nv, int nod
     template hipError_t launch_grid_near<T>(const T*, T*, const long long*, const int*,           \
                                             long long*, int*, const NearRect*, const CapsuleDev*, \
                                             const InstDev*, int, hipStream_t);                    \
-    template hipError_t launch_contact<T>(const ContactArgs<T>&, hipStream_t);                   \
+    template hipError_t launch_contact<T>(const ContactArgs<T>&, bool, hipStream_t);                   \
     template hipError_t launch_spread_tape<T>(const SpreadTapeArgs<T>&, int, int, hipStream_t);         \
     template hipError_t contact_set_lds_limit<T>(int);                                            \
     template hipError_t launch_ib<T>(const IBArgs<T>&, int, size_t, hipStream_t, bool);                 \

@@ -105,6 +105,11 @@ def _fused_case(name, real_bytes, mode):
     elif name == "box":  # both axes wrap
         cfg = wl.periodic_box(70, 45, tau, u0=(u, -u), real_bytes=real_bytes, mode=mode)
         shapes = [_ellipse(2.0, 43.5, 6.0, 5.0, 40), _ellipse(35.0, 20.0, 8.0, 5.0, 48, 0.5)]
+    elif name == "contact":  # three in contact, one of them over the wrap
+        cfg = wl.periodic_box(70, 45, tau, u0=(u, -u), real_bytes=real_bytes, mode=mode)
+        cfg["contact_cutoff"] = 2.0
+        shapes = [_ellipse(2.0, 20.0, 6.0, 5.0, 40), _ellipse(14.6, 20.0, 5.5, 6.0, 40),
+                  _ellipse(59.2, 21.0, 5.5, 6.0, 40)]
     elif name == "bands":  # FP64: the ring of a large capsule in several bands of rows
         cfg = wl._base(name, 160, 128, tau, real_bytes, mode, 0,
                        body_force_x=wl.poiseuille_body_force(tau, 128, u), **channel)
@@ -123,7 +128,8 @@ def _fused_case(name, real_bytes, mode):
 
 @pytest.mark.parametrize("mode", ["dynamic", "kinematic"])
 @pytest.mark.parametrize("name,real_bytes", [("walls", 4), ("walls", 8), ("box", 4), ("open", 4),
-                                             ("open", 8), ("bands", 8), ("direct", 8)])
+                                             ("open", 8), ("bands", 8), ("direct", 8),
+                                             ("contact", 4), ("contact", 8)])
 def test_one_launch_per_step(name, real_bytes, mode):
     """A step as one launch (the automatic schedule of a single lattice): the
     same bits as a grid and an IB launch per step, also after the nodes were
@@ -247,3 +253,56 @@ def test_capsules_under_capture(mode):
         b.step(6)
         np.testing.assert_array_equal(a.pops(), b.pops())
         np.testing.assert_array_equal(np.stack(a.capsule(0)), np.stack(b.capsule(0)))
+
+
+def _contact_oracle(shapes, L, cutoff):
+    """Eq. 27 on every node in FP64, a periodic box of side L."""
+    normals = []
+    for x in shapes:
+        e = np.roll(x, -1, axis=0) - x
+        e /= np.linalg.norm(e, axis=1, keepdims=True)
+        n = np.stack([e[:, 1], -e[:, 0]], 1)
+        n = n + np.roll(n, 1, axis=0)
+        normals.append(-n / np.linalg.norm(n, axis=1, keepdims=True))
+    out = []
+    for c, x in enumerate(shapes):
+        other = np.concatenate([s for o, s in enumerate(shapes) if o != c])
+        d = x[:, None] - other[None]
+        d -= L * np.rint(d / L)
+        d = np.sqrt((d ** 2).sum(-1))
+        mag = np.where((d < cutoff) & (d > 0), (1e-4 / (8 * np.sqrt(2.0))) / np.maximum(d, 1e-9) ** 2.5,
+                       0.0)
+        out.append(mag.sum(1)[:, None] * normals[c])
+    return out
+
+
+@pytest.mark.parametrize("name,real_bytes,tol", [
+    ("neighbours", 8, 1e-10),  # 1440 nodes of eight neighbours: staged in two rounds
+    ("many", 8, 1e-10),        # 196 capsules: two rounds of records
+    ("large", 4, 2e-6),        # 600 nodes: more than threads in a block
+])
+def test_contact_rounds(name, real_bytes, tol):
+    """The contact force where its kernel goes in several rounds, against an FP64
+    sum over all nodes.  The membranes are at rest with a stiffness that leaves
+    at most 1e-17 beside the force; FP64: positions to 1e-14 on distances of 0.5
+    and more, FP32: the force is stored in 24 bits."""
+    L = 128
+    if name == "neighbours":
+        shapes = [_ellipse(20.0 + 18.0 * i, 20.0 + 18.0 * j, 8.6, 8.6, 180) for i in range(3)
+                  for j in range(3)]
+    elif name == "many":
+        p = L / 14.0
+        shapes = [_ellipse((i + 0.5) * p, (j + 0.5) * p, 4.0, 4.0, 16) for i in range(14)
+                  for j in range(14)]
+    else:
+        shapes = [_ellipse(40.0, 40.0, 15.0, 12.0, 600), _ellipse(70.5, 40.0, 15.0, 12.0, 600)]
+    cfg = wl._base("contact", L, L, 0.8, real_bytes, "kinematic", 0, periodic_y=1)
+    cfg["contact_cutoff"] = 2.0
+    cfg["capsules"] = [wl.capsule(p, 1e-17, 0.0, 0.0) for p in shapes]
+    s = lbib.Sim(cfg)
+    s.step(1)
+    want = _contact_oracle(shapes, L, 2.0)
+    scale = max(np.abs(f).max() for f in want)
+    err = max(np.abs(s.capsule_force(c) - want[c]).max() for c in range(len(shapes)))
+    log(f"contact {name}: force {scale:.1e}, error {err / scale:.1e}")
+    assert scale > 1e-6 and err <= tol * scale
