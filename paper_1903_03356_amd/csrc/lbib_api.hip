@@ -1113,7 +1113,10 @@ static lbib_status step_overlap_t(lbib_ctx* c, int nsteps)
     // it, batches and smaller lattices wait on the queue.
     long long cells = 0;
     for (const Inst& I : c->L.inst) cells += (long long)I.grid.nx * I.grid.ny;
-    const bool inside = c->L.inst.size() == 1 && cells >= kFarWaitInsideCells && c->overlap != 2;
+    // FP32 only: an FP64 IB block finds no registers beside resident far waves, so they
+    // would wait for a launch that cannot start until they give up.
+    const bool inside = sizeof(T) == 4 && c->L.inst.size() == 1 && cells >= kFarWaitInsideCells &&
+                        c->overlap != 2;
     for (int k = 0; k < nsteps; k++) {
         const long long n = c->steps + k;
         long long nn = n;

@@ -306,3 +306,22 @@ def test_contact_rounds(name, real_bytes, tol):
     err = max(np.abs(s.capsule_force(c) - want[c]).max() for c in range(len(shapes)))
     log(f"contact {name}: force {scale:.1e}, error {err / scale:.1e}")
     assert scale > 1e-6 and err <= tol * scale
+
+
+def test_far_pass_waits_for_fp64_capsules():
+    """The split schedule of a large FP64 lattice: its IB launch cannot run beside
+    a far pass that waits for it, so the far pass waits on its queue; same bits as
+    a single pass, no wait given up."""
+    cfg = wl._base("far", 4096, 2049, 0.8, 8, "dynamic", 0, u_bottom=-0.02, u_top=0.02,
+                   init_profile=wl.INIT_COUETTE)
+    cfg["capsules"] = [wl.capsule(_ellipse(100.0 + 480.0 * i, 200.0 + 200.0 * i, 8.0, 6.0, 60),
+                                  0.05, 0.0, 1.0, 1.2) for i in range(8)]
+    a, b = lbib.Sim(cfg), lbib.Sim(cfg)
+    a.set_overlap(True)
+    b.set_overlap(False)
+    for s in (a, b):
+        s.step(6)
+    assert a.check() == 0
+    np.testing.assert_array_equal(a.force(), b.force())
+    for c in range(8):
+        np.testing.assert_array_equal(np.stack(a.capsule(c)), np.stack(b.capsule(c)))
