@@ -1518,15 +1518,17 @@ static lbib_status get_t(lbib_ctx* c, int what, int cap, void* dst, size_t bytes
     case LBIB_F_POPS:
     case LBIB_F_POPS_DEV: {
         if (bytes < 9 * plane * sizeof(double)) return fail(c, LBIB_EINVAL, "dst too small");
-        for (int i = 0; i < 9; i++) {
-            double* o = on_dev ? static_cast<double*>(dst) + i * plane : stage;
-            HIPCHK(c, launch_get_pop_plane<T>(pops_of<const T>(c, c->steps, I), o, i,
-                                              what == LBIB_F_POPS, g, c->stream));
-            if (!on_dev)
-                HIPCHK(c, hipMemcpyAsync(static_cast<double*>(dst) + i * plane, stage,
-                                         plane * sizeof(double), d2h, c->stream));
+        const T* from = pops_of<const T>(c, c->steps, I);
+        double* o = static_cast<double*>(dst);
+        if (on_dev) {
+            HIPCHK(c, launch_get_pops<T>(from, o, 0, 9, what == LBIB_F_POPS, g, c->stream));
+            return LBIB_OK;
         }
-        if (!on_dev) HIPCHK(c, hipStreamSynchronize(c->stream));
+        for (int i = 0; i < 9; i++) {
+            HIPCHK(c, launch_get_pops<T>(from, stage, i, 1, what == LBIB_F_POPS, g, c->stream));
+            HIPCHK(c, hipMemcpyAsync(o + i * plane, stage, plane * sizeof(double), d2h, c->stream));
+        }
+        HIPCHK(c, hipStreamSynchronize(c->stream));
         return LBIB_OK;
     }
     case LBIB_F_MOMENTS: {
@@ -1626,16 +1628,18 @@ static lbib_status set_t(lbib_ctx* c, int what, int cap, const void* src, size_t
         const GridArgs g = grid_args(I);
         const size_t plane = (size_t)I.grid.nx * I.grid.ny;
         if (bytes < 9 * plane * sizeof(double)) return fail(c, LBIB_EINVAL, "src too small");
-        for (int i = 0; i < 9; i++) {
-            const double* in = static_cast<const double*>(src) + i * plane;
-            if (!on_dev) {
-                HIPCHK(c, hipMemcpyAsync(stage, in, plane * sizeof(double), hipMemcpyHostToDevice,
-                                         c->stream));
-                in = stage;
-            }
-            HIPCHK(c, launch_set_pop_plane<T>(pops_of<T>(c, c->steps, I), in, i, g, c->stream));
+        T* to = pops_of<T>(c, c->steps, I);
+        const double* in = static_cast<const double*>(src);
+        if (on_dev) {
+            HIPCHK(c, launch_set_pops<T>(to, in, 0, 9, g, c->stream));
+            return LBIB_OK;
         }
-        if (!on_dev) HIPCHK(c, hipStreamSynchronize(c->stream));
+        for (int i = 0; i < 9; i++) {
+            HIPCHK(c, hipMemcpyAsync(stage, in + i * plane, plane * sizeof(double),
+                                     hipMemcpyHostToDevice, c->stream));
+            HIPCHK(c, launch_set_pops<T>(to, stage, i, 1, g, c->stream));
+        }
+        HIPCHK(c, hipStreamSynchronize(c->stream));
         return LBIB_OK;
     }
     if (what == LBIB_C_STATE) {

@@ -291,13 +291,13 @@ size_t ib_lds_bytes(int patch_cap, int max_nv);
 template <typename T>
 hipError_t ib_set_lds_limit(size_t bytes);
 
-// get/set helpers.  plane: population index for the per-plane calls.
+// get/set helpers.  n = 1: population `first`; n = 9 (first = 0): all, plane by plane.
 template <typename T>
-hipError_t launch_get_pop_plane(const T* src, double* out, int plane, int unshift,
-                                const GridArgs& g, hipStream_t s);
+hipError_t launch_get_pops(const T* src, double* out, int first, int n, int unshift,
+                           const GridArgs& g, hipStream_t s);
 template <typename T>
-hipError_t launch_set_pop_plane(T* dst, const double* in, int plane, const GridArgs& g,
-                                hipStream_t s);
+hipError_t launch_set_pops(T* dst, const double* in, int first, int n, const GridArgs& g,
+                           hipStream_t s);
 template <typename T>
 hipError_t launch_get_moments(const T* src, const long long* fib, double* out,
                               const GridArgs& g, hipStream_t s);

@@ -325,3 +325,23 @@ def test_far_pass_waits_for_fp64_capsules():
     np.testing.assert_array_equal(a.force(), b.force())
     for c in range(8):
         np.testing.assert_array_equal(np.stack(a.capsule(c)), np.stack(b.capsule(c)))
+
+
+@pytest.mark.parametrize("real_bytes", [4, 8])
+@pytest.mark.parametrize("name", ["walls", "box", "open", "bands"])
+def test_populations_on_the_device(name, real_bytes):
+    """The nine planes set and read in one launch (device buffers) are those set
+    and read one by one (host buffers)."""
+    import torch
+    cfg = dict(_fused_case(name, real_bytes, "dynamic"), capsules=[])
+    f0 = wl.random_populations(cfg["nx"], cfg["ny"], seed=5, amp=0.01)
+    a, b = lbib.Sim(cfg), lbib.Sim(cfg)
+    a.set_state(lbib.F_POPS, f0)
+    b.set_state(lbib.F_POPS, torch.from_numpy(np.ascontiguousarray(f0)).cuda())
+    for n in (0, 1, 2):
+        a.step(n)
+        b.step(n)
+        for what in (lbib.F_POPS, lbib.F_POPS_DEV):
+            out = torch.empty(f0.shape, dtype=torch.float64, device="cuda")
+            b.get_state(what, 0, out=out)
+            np.testing.assert_array_equal(out.cpu().numpy(), a.get_state(what, 0))
