@@ -101,7 +101,7 @@ typedef struct {
 typedef enum {
     LBIB_BUF_POPS_A = 0, /* populations, ping */
     LBIB_BUF_POPS_B = 1, /* populations, pong */
-    LBIB_BUF_FORCE = 2,  /* IB force field, two time levels, fixed point */
+    LBIB_BUF_FORCE = 2,  /* IB force field, two to four time levels, fixed point */
     LBIB_BUF_FLAGS = 3,  /* active-segment flags of the force field */
     LBIB_BUF_NODES = 4,  /* per-node capsule state */
     LBIB_BUF_CAPS = 5,   /* per-capsule records */
@@ -196,10 +196,23 @@ lbib_status lbib_add_rigid_to(lbib_ctx* ctx, int32_t lattice, const double* node
                               double mass, double inertia, int32_t* capsule_id);
 
 /* Queues nsteps >= 0 time steps of the chosen scheme on the bound stream.
- * Each step is one IB kernel launch (node update of the previous step fused
- * with the forcing of this step) and one fused collide-stream kernel launch.
  * The call ends with the node update of the last step, so between calls the
- * state is the complete state at time n.
+ * state is the complete state at time n.  Schedules, all with the same bits:
+ *  - a lattice with capsules: one launch per step, which holds the collide-stream
+ *    pass and, from the capsules' own patches, the node update closing the step
+ *    and the forcing of the next one; with the contact force one or two more;
+ *  - 140 MiB of populations or more (a lattice, or a batch in total), periodic in
+ *    x, no contact force: two steps per pass over the populations, after two
+ *    launches that spread the forces of both;
+ *  - 16 MiB or more without capsules (one lattice, periodic in x): two steps per
+ *    pass;
+ *  - else (batches, kernel timing, more than 2^28 cells, or lbib_set_overlap or
+ *    lbib_set_graph given): one IB launch (node update of the previous step fused
+ *    with the forcing of this one) and one collide-stream launch per step, or the
+ *    overlapped schedule below.
+ * The first two exchange population buffers and force levels, whose addresses a
+ * caller's own graph of lbib_step would keep: from the first call that is being
+ * recorded on, a context takes the last schedule.
  * Overlapped schedule (lbib_set_overlap): lattices periodic in x (one, or
  * every lattice of a batch) with 1..4096 capsules and no contact force can
  * split the collide-stream pass.  A
@@ -208,11 +221,11 @@ lbib_status lbib_add_rigid_to(lbib_ctx* ctx, int32_t lattice, const double* node
  * follows it there; a far kernel covers the rest on a second stream of the
  * library's own, so the IB work runs beside it.  The results are
  * bit-identical to the single pass, and the call still returns with all work
- * ordered on the bound stream.  By default the split is used for a single
- * lattice of 2^22 cells or more, where it pays; a batch takes it only when
- * asked (many small lattices: the far launch slows the IB launch beside it
- * more than the split saves).
- * Captured steps (lbib_set_graph(ctx, 1)): otherwise, unless kernel timing is
+ * ordered on the bound stream.  By default the split is used where the schedules
+ * above do not apply, for a single lattice of 2^22 cells or more; a batch takes
+ * it only when asked (many small lattices: the far launch slows the IB launch
+ * beside it more than the split saves).
+ * Captured steps (lbib_set_graph(ctx, 1)): unless kernel timing is
  * on, the inner steps of a call go in blocks of 16 steps captured once into a
  * HIP graph (one for blocks that start on an even step, one for odd) and
  * replayed with one launch per block; the first step of a call and the
@@ -260,16 +273,17 @@ lbib_status lbib_set_timing(lbib_ctx* ctx, int32_t enable);
  * gives no cutoff; 2 is the reading the workloads use.  cutoff = 0 (the
  * default) switches it off.  The force joins the total nodal force of the
  * Dynamic update (step 7) and the internal force of the Kinematic forcing
- * (step i), at the positions those use.  Contacts cost one bounds and one
- * contact kernel per force evaluation; the Kinematic scheme then takes
- * separate launches for the node update and the forcing.
+ * (step i), at the positions those use.  Contacts cost one contact kernel per
+ * force evaluation (and one for the bounding boxes where the launch before did
+ * not leave them); the Kinematic scheme then takes separate launches for the
+ * node update and the forcing.
  * Errors: EINVAL (cutoff not in [0, 16]), EDEVICE. */
 lbib_status lbib_set_contact(lbib_ctx* ctx, double cutoff);
 
 /* Schedule of lbib_step: enable = 1 always uses the overlapped near / far
- * schedule where it applies (see lbib_step), 0 never, -1 (the default) for
- * one lattice of 2^22 cells or more.  In the overlapped schedule of one
- * lattice of 2^23 cells or more, the far kernel of every step after a call's
+ * schedule where it applies, 0 one IB and one grid launch per step, -1 (the
+ * default) the schedule that lbib_step says.  In the overlapped schedule of one
+ * FP32 lattice of 2^23 cells or more, the far kernel of every step after a call's
  * first waits for that step's IB launch on the device (a counter the IB blocks
  * raise), not on the queue; this needs the two streams' kernels to run
  * concurrently.  enable = 2 is the overlapped schedule with queue-level waits
