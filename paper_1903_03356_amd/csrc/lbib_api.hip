@@ -136,7 +136,7 @@ struct lbib_ctx {
     bool a_rects = false;  // and the capsules' node boxes are written (step_pair_t only)
     // force levels by what they hold at time `steps` (as the step calls go on):
     // F^{n-1}, F^n (zero until spread), and a spare one (zero).  A serial step
-    // swaps the first two, a fused one rotates all three.
+    // swaps the first two, a fused one rotates all three, a pair all four.
     int lv_prev = 1, lv_next = 0, lv_spare = 2;
     int lv_old = 3;  // may still hold F^{n-2}: step_pair_t clears it before use
     // membrane checks (lbib_set_limits), 0 = off
@@ -1386,8 +1386,9 @@ static lbib_status step_t(lbib_ctx* c, int nsteps)
                              c->ncap <= kMaxOverlapCapsules;
     long long cells = 0;
     for (const Inst& I : c->L.inst) cells += (long long)I.grid.nx * I.grid.ny;
-    // automatic: the split pays once the grid step clearly outlasts the IB
-    // launch, the near pass and the stream hand-offs (32 capsules, measured:
+    // Without those, automatic: the split against the single pass pays once the grid
+    // step clearly outlasts the IB launch, the near pass and the stream hand-offs
+    // (32 capsules, measured:
     // +7 % at 16.8 M cells, +12 % at 8.4 M, +5.5 % at 4.2 M, -10 % at 2.1 M,
     // -19 % at 1.0 M).  A batch of small lattices loses (256 lattices,
     // 8.0 M cells, 388 capsules: -17 %, the IB launch runs 2.4x longer beside

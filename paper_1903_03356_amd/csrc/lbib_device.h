@@ -350,7 +350,7 @@ struct AxisFit {
 };
 
 // exp(-x), 0 <= x <= 8: FP32 by the hardware's 2^t (1 ulp) with the rounding of
-// t = -x log2(e) put back to first order.  
+// t = -x log2(e) put back to first order.
 __device__ __forceinline__ float gauss(float x)
 {
     const float c = -1.44269504088896341f;                          // -log2(e), rounded
