@@ -2116,12 +2116,14 @@ extern "C" lbib_status lbib_set_tile(lbib_ctx* c, int32_t rows, int32_t linear, 
 // Times every tile-shape candidate of the batched grid pass on the context's
 // own lattices and keeps the fastest.  The pass runs on the current state
 // with the force level of the coming step as both its force input and the
-// level it clears: between calls that level is zero (the last grid pass
-// cleared it), so the trial passes read no force, clear nothing, and write
-// only the other population buffer, which the next step rewrites in full.
+// level it clears: that level is zero (a forcing spread ahead is undone first),
+// so the trial passes read no force, clear nothing, and write only the other
+// population buffer, which the next step rewrites in full.
 template <typename T>
 static lbib_status autotune_t(lbib_ctx* c, int launches, double* us)
 {
+    const lbib_status dropped = drop_pending_forcing(c);
+    if (dropped != LBIB_OK) return dropped;
     const long long n = c->steps;
     const T* src = static_cast<const T*>(pops(c, n));
     T* dst = static_cast<T*>(pops(c, n + 1));

@@ -345,3 +345,17 @@ def test_populations_on_the_device(name, real_bytes):
             out = torch.empty(f0.shape, dtype=torch.float64, device="cuda")
             b.get_state(what, 0, out=out)
             np.testing.assert_array_equal(out.cpu().numpy(), a.get_state(what, 0))
+
+
+def test_autotune_between_steps():
+    """Trial passes between two Dynamic calls, the first of which spread the
+    forcing of the second ahead: the same bits as without them."""
+    cfg = _fused_case("walls", 4, "dynamic")
+    a, b = lbib.Sim(cfg), lbib.Sim(cfg)
+    for s in (a, b):
+        s.step(3)
+    a.autotune(1)
+    for s in (a, b):
+        s.step(3)
+    np.testing.assert_array_equal(a.pops(), b.pops())
+    np.testing.assert_array_equal(np.stack(a.capsule(0)), np.stack(b.capsule(0)))
