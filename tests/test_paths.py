@@ -348,14 +348,16 @@ def test_populations_on_the_device(name, real_bytes):
 
 
 def test_autotune_between_steps():
-    """Trial passes between two Dynamic calls, the first of which spread the
-    forcing of the second ahead: the same bits as without them."""
-    cfg = _fused_case("walls", 4, "dynamic")
-    a, b = lbib.Sim(cfg), lbib.Sim(cfg)
+    """Trial passes between two Dynamic calls of a batch, the first of which spread
+    the forcing of the second ahead: the same bits as without them."""
+    cfg = _pair_case("batch", 4, "dynamic")
+    a, b = lbib.Batch(cfg), lbib.Batch(cfg)
     for s in (a, b):
-        s.step(3)
+        s.step(2)
     a.autotune(1)
     for s in (a, b):
-        s.step(3)
-    np.testing.assert_array_equal(a.pops(), b.pops())
+        s.step(2)
+    for i in range(len(cfg)):
+        np.testing.assert_array_equal(a.pops(i), b.pops(i))
+        np.testing.assert_array_equal(a.force(i), b.force(i))
     np.testing.assert_array_equal(np.stack(a.capsule(0)), np.stack(b.capsule(0)))
