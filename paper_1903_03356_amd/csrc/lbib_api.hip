@@ -1535,7 +1535,8 @@ static lbib_status get_t(lbib_ctx* c, int what, int cap, void* dst, size_t bytes
     case LBIB_F_MOMENTS: {
         if (bytes < 3 * plane * sizeof(double)) return fail(c, LBIB_EINVAL, "dst too small");
         double* o = on_dev ? static_cast<double*>(dst) : stage;
-        HIPCHK(c, launch_get_moments<T>(pops_of<const T>(c, c->steps, I), fib_last, o, g,
+        HIPCHK(c, launch_get_moments<T>(pops_of<const T>(c, c->steps, I), fib_last,
+                                        flags(c, c->lv_prev) + I.flag_off, o, g,
                                         c->stream));
         return finish(o, 3 * plane);
     }

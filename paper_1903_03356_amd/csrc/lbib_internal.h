@@ -299,7 +299,7 @@ template <typename T>
 hipError_t launch_set_pops(T* dst, const double* in, int first, int n, const GridArgs& g,
                            hipStream_t s);
 template <typename T>
-hipError_t launch_get_moments(const T* src, const long long* fib, double* out,
+hipError_t launch_get_moments(const T* src, const long long* fib, const int* flags, double* out,
                               const GridArgs& g, hipStream_t s);
 hipError_t launch_get_force(const long long* fib, double* out, const GridArgs& g, hipStream_t s);
 template <typename T>

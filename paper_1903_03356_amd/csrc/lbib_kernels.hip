@@ -2790,16 +2790,30 @@ hipError_t launch_set_pops(T* dst, const double* in, int first, int n, const Gri
     return hipGetLastError();
 }
 
-template <typename T>
-__global__ void k_get_moments(const T* src, const long long* fib, double* out, GridArgs g)
+// FLAGS: reads the force of active segments only, which alone hold one.  16 of 76 bytes
+// a cell (4096^2 FP32 207 -> 158 us), but one more round trip: lattices of 2^20 cells
+// and more (256 x 100: 3.4 us without, 3.8 with).
+template <typename T, bool FLAGS>
+__global__ void k_get_moments(const T* src, const long long* fib, const int* flags, double* out,
+                              GridArgs g)
 {
     const int x = blockIdx.x * blockDim.x + threadIdx.x, y = blockIdx.y;
     if (x >= g.nx) return;
     const size_t cell = (size_t)y * g.nxp + x;
-    const double Fx = g.gx + (double)fib[2 * cell] * kFixInv;
-    const double Fy = (double)fib[2 * cell + 1] * kFixInv;
+    double Fx = g.gx, Fy = 0.0;
     T s[9];
-    pull(src, x, y, g, (T)Fx, s);
+    if (FLAGS) {
+        pull_loads(src, x, y, g, s);
+        if (flags[y * g.nseg + x / kSegW]) {
+            Fx += (double)fib[2 * cell] * kFixInv;
+            Fy = (double)fib[2 * cell + 1] * kFixInv;
+        }
+        pull_complete(src, x, y, g, (T)Fx, s);
+    } else {
+        Fx += (double)fib[2 * cell] * kFixInv;
+        Fy = (double)fib[2 * cell + 1] * kFixInv;
+        pull(src, x, y, g, (T)Fx, s);
+    }
     double drho = 0, jx = 0, jy = 0;
 #pragma unroll
     for (int i = 0; i < 9; i++) {
@@ -2815,11 +2829,12 @@ __global__ void k_get_moments(const T* src, const long long* fib, double* out, G
 }
 
 template <typename T>
-hipError_t launch_get_moments(const T* src, const long long* fib, double* out, const GridArgs& g,
-                              hipStream_t s)
+hipError_t launch_get_moments(const T* src, const long long* fib, const int* flags, double* out,
+                              const GridArgs& g, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_get_moments<T>, dim3((g.nx + 255) / 256, g.ny), dim3(256), 0, s, src, fib,
-                       out, g);
+    const auto f = (long long)g.nx * g.ny >= 1 << 20 ? &k_get_moments<T, true>
+                                                     : &k_get_moments<T, false>;
+    hipLaunchKernelGGL(f, dim3((g.nx + 255) / 256, g.ny), dim3(256), 0, s, src, fib, flags, out, g);
     return hipGetLastError();
 }
 
@@ -2939,7 +2954,7 @@ hipError_t launch_set_nodes(T* nodes, CapsuleDev* caps, int cap, int nv, int nod
                                            hipStream_t);                                          \
     template hipError_t launch_set_pops<T>(T*, const double*, int, int, const GridArgs&,          \
                                            hipStream_t);                                          \
-    template hipError_t launch_get_moments<T>(const T*, const long long*, double*,                \
+    template hipError_t launch_get_moments<T>(const T*, const long long*, const int*, double*,                \
                                               const GridArgs&, hipStream_t);                      \
     template hipError_t launch_get_nodes<T>(const T*, const CapsuleDev*, int, int, int, int,      \
                                             double*, hipStream_t);                                \

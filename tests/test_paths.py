@@ -361,3 +361,22 @@ def test_autotune_between_steps():
         np.testing.assert_array_equal(a.pops(i), b.pops(i))
         np.testing.assert_array_equal(a.force(i), b.force(i))
     np.testing.assert_array_equal(np.stack(a.capsule(0)), np.stack(b.capsule(0)))
+
+
+def test_moments_of_a_large_lattice():
+    """From 2^20 cells the moments take the force of active segments only: on a
+    lattice with capsules, the velocity that the populations and the whole force
+    field give (FP64; sums of a dozen terms of at most 1: 1e-14)."""
+    cfg = _pair_case("channel", 8, "dynamic")
+    s = lbib.Sim(cfg)
+    s.step(3)
+    rho, ux, uy = s.moments()
+    f, F = s.pops(), s.force()
+    ex = np.array([0, 1, 0, -1, 0, 1, -1, -1, 1.0])
+    ey = np.array([0, 0, 1, 0, -1, 1, 1, -1, -1.0])
+    assert np.abs(F[1]).max() > 0
+    np.testing.assert_allclose(rho, f.sum(0), rtol=0, atol=1e-14)
+    inner = slice(1, -1)
+    for u, e, k in ((ux, ex, 0), (uy, ey, 1)):
+        want = (np.tensordot(e, f, 1) + 0.5 * F[k]) / f.sum(0)
+        np.testing.assert_allclose(u[inner], want[inner], rtol=0, atol=1e-14)
