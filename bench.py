@@ -638,11 +638,15 @@ def main() -> int:
             "traffic": traffic,
             "bytes_per_cell": BYTES_PER_CELL,
             "cells_per_launch": far_cells,
+            # the instrumented run splits each step; the timed steps of a large
+            # lattice go two per pass (k_grid_two: half these bytes per step)
+            "schedule": "instrumented run: one step per pass; timed steps: two per pass",
             "kernel_mean_us": round(grid_ms * 1e3, 2),
             "near_kernel_mean_us": round(near_ms * 1e3, 2),
             "ib_kernel_mean_us": round(ib_ms * 1e3, 2),
         },
         **side,
+        # of single-pass bytes: above 1 where two steps share a pass
         "hbm_fraction_step": round(BYTES_PER_CELL * cells * args.steps / r["seconds"] / 1e9
                                    / PEAK_HBM_GBS, 4),
     }
