@@ -428,20 +428,27 @@ __device__ __forceinline__ void stage_moments(const Patch<T>& P, int i, const T 
 
 // Lattice coordinate ref + off on a periodic axis of n nodes.  The reference
 // point (64-bit, unwrapped) is reduced once per call site with wrap_ref; each
-// coordinate then takes an add and at most one correction while |off| < n, and
-// the remainder only beyond that.
-__device__ __forceinline__ int wrap_ref(long long ref, int n)
+// coordinate then takes an add and at most one correction while |off| < n.  Beyond
+// that the correction is the largest n 2^k that cannot overshoot, so that any int (a
+// diverged capsule's offset) is reduced in under 80 rounds, n at a time would be
+// 2^31 / n.  (A remainder there took 30 registers of k_step.)
+__host__ __device__ __forceinline__ int wrap_ref(long long ref, int n)
 {
     // the quotient in FP64 (off by one at most for |ref| < 2^50), the remainder exact
     const long long r = ref - (long long)floor((double)ref * (1.0 / n)) * n;
     return (int)(r < 0 ? r + n : (r >= n ? r - n : r));
 }
 
-__device__ __forceinline__ int wrap_add(int base, int off, int n)
+__host__ __device__ __forceinline__ int wrap_add(int base, int off, int n)
 {
-    int v = base + off;
+    int v = (int)((unsigned)base + (unsigned)off);
 #pragma unroll 1
-    while ((unsigned)v >= (unsigned)n) v += v < 0 ? n : -n;
+    while ((unsigned)v >= (unsigned)n) {
+        const unsigned a = v < 0 ? 0u - (unsigned)v : (unsigned)v;
+        const int k = __builtin_clz((unsigned)n) - __builtin_clz(a) - 1;
+        const int d = n << (k > 0 ? k : 0);
+        v += v < 0 ? d : -d;
+    }
     return v;
 }
 
@@ -522,8 +529,8 @@ __device__ __forceinline__ void set_geo(PatchGeo<T>& Q, const Patch<T>& P, const
     Q.c3 = (T)((double)FirstOrderW<T>::diag * g.uref_c);
     Q.far_offsets = (unsigned long long)g.ny * (unsigned)g.nxp >= 0xfffff000u / (9 * sizeof(T)) ||
                     (unsigned long long)g.ny * (unsigned)g.nxp >= 0xfffff000u / 16;
-    Q.plain = !Q.far_offsets && Q.bx >= 2 && Q.bx + P.W <= g.nx - 2 && Q.by >= 2 &&
-              Q.by + P.H <= g.ny - 2;
+    Q.plain = !Q.far_offsets && Q.bx >= 2 && Q.bx <= g.nx - 2 - P.W && Q.by >= 2 &&
+              Q.by <= g.ny - 2 - P.H;
 }
 
 // Row i / width of item i (width = 1 / inv): exact, as (i + 1/2) / width is at

@@ -1128,7 +1128,7 @@ template <typename T>
 __device__ __forceinline__ int support_index(const Patch<T>& P, int cx, int cy)
 {
     const int lx = cx - 1 - P.ox, ly = cy - 1 - P.oy;
-    return lx >= 0 && lx + 2 < P.W && ly >= 0 && ly + 2 < P.H ? ly * P.W + lx : -1;
+    return lx >= 0 && lx < P.W - 2 && ly >= 0 && ly < P.H - 2 ? ly * P.W + lx : -1;
 }
 
 // Eq. 8 sum of the velocity over the support with the weights phi.  A support
@@ -1565,7 +1565,7 @@ __device__ __forceinline__ void spread_patch(const IBArgs<T>& a, const GridArgs&
         const T* phi = base + 3 * row * stride + v;
         const T p[3] = {phi[0], phi[stride], row == 2 ? base[12 * stride + v] : phi[2 * stride]};
         const int lx = cx - 1 - P.ox, ly = cy + row - 1 - P.oy;
-        const bool inside = lx >= 0 && lx + 2 < P.W && ly >= 0 && ly < P.H;
+        const bool inside = lx >= 0 && lx < P.W - 2 && ly >= 0 && ly < P.H;
         if (!inside) {
             for (int i = 0; i < 3; i++)
                 spread_one(a, g, r, cx, cy, 3 * row + i, p[i] * fx, p[i] * fy, st);
