@@ -452,6 +452,78 @@ __host__ __device__ __forceinline__ int wrap_add(int base, int off, int n)
     return v;
 }
 
+// ---- near regions (NearRect; any ints: a diverged capsule's box can hold whatever
+// the conversion of its coordinates gives)
+// Rows and 64-cell segments of a capsule's near region (rect in world cells,
+// x unwrapped).  The IB kernel stamps exactly these (row, segment) units into
+// the near map and the near kernel computes exactly these, so near and far
+// cover the lattice once.
+struct RectUnits {
+    int ry0, nrows;  // first row (wrapped) and row count
+    int sa, nA, nsegs;  // segments: sa .. sa + nA - 1, then 0 .. (nsegs - nA) - 1
+};
+
+// The cells of the rect grown by `more` on every side: rows y0 .. y0 + rows - 1 and
+// columns x0 .. x0 + w - 1, those past the lattice's end from 0 on again.
+struct NearCells {
+    int x0, y0, w, rows;
+};
+
+__host__ __device__ __forceinline__ int wrapped(int x, int n)
+{
+    const int r = x % n;
+    return r < 0 ? r + n : r;
+}
+
+// Numbers a .. b, at most `most` of them.
+__host__ __device__ __forceinline__ int count_of(long long a, long long b, int most)
+{
+    const long long n = b - a + 1;
+    return n < 0 ? 0 : (n > most ? most : (int)n);
+}
+
+__host__ __device__ __forceinline__ NearCells near_cells(const NearRect& r, const GridArgs& g,
+                                                         int more)
+{
+    NearCells c;
+    c.w = count_of((long long)r.x0 - more, (long long)r.x1 + more, g.nx);
+    c.x0 = wrap_add(wrapped(r.x0, g.nx), -more, g.nx);
+    if (g.periodic_y) {
+        c.rows = count_of((long long)r.y0 - more, (long long)r.y1 + more, g.ny);
+        c.y0 = wrap_add(wrapped(r.y0, g.ny), -more, g.ny);
+    } else {
+        const long long a = (long long)r.y0 - more, b = (long long)r.y1 + more;
+        c.y0 = a < 0 ? 0 : (a > g.ny ? g.ny : (int)a);
+        c.rows = count_of(c.y0, b < g.ny ? b : g.ny - 1, g.ny);
+    }
+    return c;
+}
+
+__host__ __device__ __forceinline__ RectUnits rect_units(const NearRect& r, const GridArgs& g)
+{
+    const NearCells c = near_cells(r, g, 0);
+    RectUnits u;
+    u.ry0 = c.y0;
+    u.nrows = c.rows;
+    if (c.w >= g.nx) {
+        u.sa = 0;
+        u.nA = g.nseg;
+        u.nsegs = g.nseg;
+    } else {
+        const int b = c.x0 + c.w - 1;
+        u.sa = c.x0 / kSegW;
+        if (b < g.nx) {
+            u.nA = b / kSegW - u.sa + 1;
+            u.nsegs = u.nA;
+        } else {
+            u.nA = g.nseg - u.sa;
+            u.nsegs = u.nA + (b - g.nx) / kSegW + 1;
+        }
+        if (c.w == 0) u.nA = u.nsegs = 0;
+    }
+    return u;
+}
+
 // Raw buffer access: a scalar base and offset per row and plane, one 32-bit
 // offset per lane; an offset past the end reads 0 and stores nothing, so a lane
 // without a cell needs no branch (kNoCell).  Streaming loads and stores as

@@ -116,45 +116,6 @@ __device__ __forceinline__ void grid_cell(const T* __restrict__ src, T* __restri
 }
 
 // ---- near / far split of a grid step (IB launch hidden behind the far part)
-// Rows and 64-cell segments of a capsule's near region (rect in world cells,
-// x unwrapped).  The IB kernel stamps exactly these (row, segment) units into
-// the near map and the near kernel computes exactly these, so near and far
-// cover the lattice once.
-struct RectUnits {
-    int ry0, nrows;  // first row (wrapped) and row count
-    int sa, nA, nsegs;  // segments: sa .. sa + nA - 1, then 0 .. (nsegs - nA) - 1
-};
-
-__device__ __forceinline__ RectUnits rect_units(const NearRect& r, const GridArgs& g)
-{
-    RectUnits u;
-    if (g.periodic_y) {
-        u.nrows = min(r.y1 - r.y0 + 1, g.ny);
-        u.ry0 = ((r.y0 % g.ny) + g.ny) % g.ny;
-    } else {
-        u.ry0 = max(0, r.y0);
-        u.nrows = max(0, min(g.ny - 1, r.y1) - u.ry0 + 1);
-    }
-    const int w = r.x1 - r.x0 + 1;
-    if (w >= g.nx) {
-        u.sa = 0;
-        u.nA = g.nseg;
-        u.nsegs = g.nseg;
-    } else {
-        const int a = ((r.x0 % g.nx) + g.nx) % g.nx;
-        const int b = a + w - 1;
-        u.sa = a / kSegW;
-        if (b < g.nx) {
-            u.nA = b / kSegW - u.sa + 1;
-            u.nsegs = u.nA;
-        } else {
-            u.nA = g.nseg - u.sa;
-            u.nsegs = u.nA + (b - g.nx) / kSegW + 1;
-        }
-    }
-    return u;
-}
-
 // Grid arguments of one lattice of the lattice table.
 __device__ __forceinline__ GridArgs lattice_args(const InstDev& I)
 {
@@ -343,22 +304,12 @@ __device__ void pair_near(const T* __restrict__ src, T* __restrict__ dst,
     src += I.pop_off;
     dst += I.pop_off;
     fib_now += I.fib_off;
-    const int w = min(r.x1 - r.x0 + 7, g.nx), cols = (w + kSegW - 1) / kSegW;
-    int x0 = (r.x0 - 3) % g.nx, y0 = r.y0 - 3, rows = r.y1 - r.y0 + 7;
-    x0 = x0 < 0 ? x0 + g.nx : x0;
-    if (g.periodic_y) {
-        y0 %= g.ny;
-        y0 = y0 < 0 ? y0 + g.ny : y0;
-        rows = min(rows, g.ny);
-    } else {
-        const int end = min(g.ny, y0 + rows);
-        y0 = max(0, y0);
-        rows = end - y0;
-    }
-    for (int q = kb * WAVES + wave; q < rows * cols; q += p.per_cap * WAVES) {
+    const NearCells n = near_cells(r, g, 3);
+    const int cols = (n.w + kSegW - 1) / kSegW;
+    for (int q = kb * WAVES + wave; q < n.rows * cols; q += p.per_cap * WAVES) {
         const int ri = q / cols, at = (q - ri * cols) * kSegW + lane;
-        if (at >= w) continue;
-        int x = x0 + at, y = y0 + ri;
+        if (at >= n.w) continue;
+        int x = n.x0 + at, y = n.y0 + ri;
         if (x >= g.nx) x -= g.nx;
         if (y >= g.ny) y -= g.ny;
         const size_t cell = (size_t)y * g.nxp + x;
