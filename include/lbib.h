@@ -210,9 +210,11 @@ lbib_status lbib_add_rigid_to(lbib_ctx* ctx, int32_t lattice, const double* node
  *    lbib_set_graph given): one IB launch (node update of the previous step fused
  *    with the forcing of this one) and one collide-stream launch per step, or the
  *    overlapped schedule below.
- * The first two exchange population buffers and force levels, whose addresses a
- * caller's own graph of lbib_step would keep: from the first call that is being
- * recorded on, a context takes the last schedule.
+ * The first three exchange population buffers or force levels, whose addresses a
+ * caller's own graph would keep, and the Dynamic ones spread the coming call's
+ * forcing ahead: from the first call of any kind that is being recorded on
+ * (lbib_step, or lbib_get_state / lbib_set_state with device memory), a context
+ * takes the last schedule.
  * Overlapped schedule (lbib_set_overlap): lattices periodic in x (one, or
  * every lattice of a batch) with 1..4096 capsules and no contact force can
  * split the collide-stream pass.  A

@@ -132,7 +132,8 @@ struct lbib_ctx {
     // of a forcing spread ahead: the step's near map is stamped too (overlapped
     // schedule only)
     bool a_stamped = false;
-    bool recorded = false;  // a caller has recorded a step call into a graph
+    // a caller has recorded a call into a graph (note_recording)
+    bool recorded = false;
     bool a_rects = false;  // and the capsules' node boxes are written (step_pair_t only)
     // force levels by what they hold at time `steps` (as the step calls go on):
     // F^{n-1}, F^n (zero until spread), and a spare one (zero).  A serial step
@@ -427,6 +428,25 @@ static int step_stamp(long long n) { return (int)((n + 1) & 0x7fffffff); }
 static unsigned long long* ib_done_counter(const lbib_ctx* c)
 {
     return reinterpret_cast<unsigned long long*>(bufp(c, LBIB_BUF_DIAG) + status_offset(c->L) + 32);
+}
+
+// Whether the caller is recording the stream into a graph of its own.
+static bool capturing(hipStream_t st)
+{
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(st, &s) != hipSuccess || s != hipStreamCaptureStatusNone;
+}
+
+// At the start of every call that queues work: a caller's graph keeps the addresses
+// of the buffers and force levels that it was recorded with, and its replays are not
+// seen here, so from the first recorded call on (of any kind: a read-out, a restart,
+// steps) a context goes without the schedules that exchange them and without a forcing
+// spread ahead of the call that reads it.
+static bool note_recording(lbib_ctx* c)
+{
+    const bool rec = capturing(c->stream);
+    c->recorded = c->recorded || rec;
+    return rec;
 }
 
 // Undoes a forcing spread ahead (lbib_ctx::a_ready): clears the step's force
@@ -1102,7 +1122,7 @@ static lbib_status step_overlap_t(lbib_ctx* c, int nsteps)
     // Dynamic, one lattice: the last launch also spreads the next step's
     // forcing (phase A writes no node state there), so the next call needs
     // no opening IB launch in front of its first far pass
-    const bool ahead = c->mode == LBIB_DYNAMIC && c->L.inst.size() == 1;
+    const bool ahead = c->mode == LBIB_DYNAMIC && c->L.inst.size() == 1 && !c->recorded;
     // Far pass n waits for IB(n).  From the second step of a call on, on one
     // large lattice, the far kernel waits inside, on the count of finished IB
     // blocks: that spares the queue-level hand-off between the two streams
@@ -1353,13 +1373,6 @@ static lbib_status capture_steps(lbib_ctx* c, long long n0, bool contact, bool d
     return LBIB_OK;
 }
 
-// Whether the caller is recording the stream into a graph of its own.
-static bool capturing(hipStream_t st)
-{
-    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(st, &s) != hipSuccess || s != hipStreamCaptureStatusNone;
-}
-
 // Whether two steps with capsules go in one pass: from the size on where the pass
 // itself, and not the two IB launches before it, is most of the time.  us per step,
 // fused or one pass per step / pairs, 32 capsules: FP32 2048x512 20.0 / 29.8, 2048x1536
@@ -1395,15 +1408,10 @@ static lbib_status step_t(lbib_ctx* c, int nsteps)
     // the far pass), so a batch splits only when asked.
     const bool want = c->overlap >= 1 || (c->overlap < 0 && c->L.inst.size() == 1 &&
                                           cells >= kOverlapMinCells);
-    // A caller's graph keeps the addresses of the buffers and force levels that it was
-    // recorded with, so from the first recorded call on a context goes without the
-    // schedules that exchange them; and the graph must hold its first step's forcing.
-    if (capturing(c->stream)) {
-        c->recorded = true;
-        if (c->a_ready && !c->a_stamped) {
-            lbib_status s = drop_pending_forcing(c);
-            if (s != LBIB_OK) return s;
-        }
+    // a graph must hold its first step's forcing
+    if (note_recording(c) && !c->a_stamped) {
+        lbib_status s = drop_pending_forcing(c);
+        if (s != LBIB_OK) return s;
     }
     const bool exchange = !c->recorded && c->graph != 1;
     const bool direct = c->overlap < 0 && c->ncap > 0 && c->L.levels == kForceLevels && !c->timing &&
@@ -1497,6 +1505,7 @@ extern "C" lbib_status lbib_step(lbib_ctx* c, int32_t nsteps, lbib_mode mode)
 template <typename T>
 static lbib_status get_t(lbib_ctx* c, int what, int cap, void* dst, size_t bytes, int on_dev)
 {
+    note_recording(c);
     // field states: cap names the lattice
     const bool field = what == LBIB_F_POPS || what == LBIB_F_POPS_DEV ||
                        what == LBIB_F_MOMENTS || what == LBIB_F_FORCE;
@@ -1619,6 +1628,7 @@ template <typename T>
 static lbib_status set_t(lbib_ctx* c, int what, int cap, const void* src, size_t bytes, int on_dev)
 {
     double* stage = reinterpret_cast<double*>(bufp(c, LBIB_BUF_STAGE));
+    note_recording(c);
     if (what == LBIB_F_POPS || what == LBIB_C_STATE) {
         lbib_status d = drop_pending_forcing(c);
         if (d != LBIB_OK) return d;

@@ -380,3 +380,94 @@ def test_moments_of_a_large_lattice():
     for u, e, k in ((ux, ex, 0), (uy, ey, 1)):
         want = (np.tensordot(e, f, 1) + 0.5 * F[k]) / f.sum(0)
         np.testing.assert_allclose(u[inner], want[inner], rtol=0, atol=1e-14)
+
+
+def _recorded_case(name, mode="dynamic"):
+    """Lattices of the schedules that exchange buffers or force levels."""
+    if name == "fused":
+        return _fused_case("walls", 4, mode)
+    if name == "contact":
+        return _fused_case("contact", 8, mode)
+    if name == "pair":
+        return _pair_case("channel", 4, mode)
+    return wl._base("two", 1024, 512, 0.7, 4, "kinematic", 0, u_top=0.02,
+                    init_profile=wl.INIT_COUETTE)
+
+
+def _device_like(sim, what, cap=0):
+    import torch
+    nx, ny = sim.dims[0]
+    shape = {lbib.F_POPS: (9, ny, nx), lbib.F_MOMENTS: (3, ny, nx), lbib.F_FORCE: (2, ny, nx),
+             lbib.C_STATE: (3, sim.nv[cap] if sim.nv else 1, 2)}[what]
+    return torch.zeros(shape, dtype=torch.float64, device="cuda")
+
+
+@pytest.mark.parametrize("name,mode", [("fused", "dynamic"), ("fused", "kinematic"),
+                                       ("contact", "kinematic"), ("pair", "dynamic"), ("two", "kinematic")])
+def test_recorded_read_out(name, mode):
+    """A caller's graph of read-outs, recorded after steps of the automatic schedule,
+    reads the state after every even number of the caller's own steps."""
+    import torch
+    cfg = _recorded_case(name, mode)
+    st = torch.cuda.Stream()
+    a, b = lbib.Sim(cfg, stream=st), lbib.Sim(cfg)
+    b.set_overlap(False)
+    whats = [lbib.F_POPS, lbib.F_MOMENTS, lbib.F_FORCE] + ([lbib.C_STATE] if a.nv else [])
+    out = [_device_like(a, w) for w in whats]
+    torch.cuda.synchronize()
+    a.step(4)
+    b.step(4)
+    st.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=st):
+        for w, o in zip(whats, out):
+            a.get_state(w, 0, out=o)
+    for n in (0, 2, 4, 6):
+        a.step(n)
+        b.step(n)
+        graph.replay()
+        torch.cuda.synchronize()
+        for w, o in zip(whats, out):
+            np.testing.assert_array_equal(o.cpu().numpy(), b.get_state(w, 0))
+
+
+@pytest.mark.parametrize("name,mode", [("fused", "dynamic"), ("fused", "kinematic"), ("pair", "dynamic"),
+                                       ("two", "kinematic")])
+def test_recorded_restart(name, mode):
+    """A caller's graph that restores a saved state, recorded before the first step,
+    with the caller's own steps between its replays."""
+    import torch
+    cfg = _recorded_case(name, mode)
+    st = torch.cuda.Stream()
+    a, b = lbib.Sim(cfg, stream=st), lbib.Sim(cfg)
+    b.set_overlap(False)
+    whats = [lbib.F_POPS] + ([lbib.C_STATE] if a.nv else [])
+    saved = [_device_like(a, w) for w in whats]
+    src = lbib.Sim(cfg)
+    src.step(2)
+    for w, x in zip(whats, saved):
+        src.get_state(w, 0, out=x)
+    torch.cuda.synchronize()
+    st.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=st):
+        for w, x in zip(whats, saved):
+            a.set_state(w, x, 0)
+
+    def same():
+        np.testing.assert_array_equal(a.pops(), b.pops())
+        np.testing.assert_array_equal(a.force(), b.force())
+        if a.nv:
+            np.testing.assert_array_equal(np.stack(a.capsule(0)), np.stack(b.capsule(0)))
+
+    a.step(2)
+    b.step(2)
+    same()
+    for _ in range(3):
+        graph.replay()
+        for w, x in zip(whats, saved):
+            b.set_state(w, x, 0)
+        for s in (a, b):
+            s.step(4)
+        torch.cuda.synchronize()
+        same()
