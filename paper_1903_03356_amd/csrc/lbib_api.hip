@@ -132,8 +132,10 @@ struct lbib_ctx {
     // of a forcing spread ahead: the step's near map is stamped too (overlapped
     // schedule only)
     bool a_stamped = false;
-    // a caller has recorded a call into a graph (note_recording)
-    bool recorded = false;
+    // a caller has recorded a call into a graph (note_recording).  `uncleared`: of
+    // such a call, the forcing spread ahead was dropped in the graph only, so the
+    // step's level may still hold it (drop_pending_forcing)
+    bool recorded = false, uncleared = false;
     bool a_rects = false;  // and the capsules' node boxes are written (step_pair_t only)
     // force levels by what they hold at time `steps` (as the step calls go on):
     // F^{n-1}, F^n (zero until spread), and a spare one (zero).  A serial step
@@ -451,14 +453,18 @@ static bool note_recording(lbib_ctx* c)
 
 // Undoes a forcing spread ahead (lbib_ctx::a_ready): clears the step's force
 // level, its segment flags and its near map, so that the next call spreads the
-// forcing again from the state as it then stands.
+// forcing again from the state as it then stands.  In a recorded call that happens
+// when the graph is replayed; whatever comes before that clears them again (a level
+// without a forcing is zero, clearing it twice is harmless).
 static lbib_status drop_pending_forcing(lbib_ctx* c)
 {
-    if (!c->a_ready) return LBIB_OK;
+    if (!c->a_ready && !c->uncleared) return LBIB_OK;
     HIPCHK(c, launch_clear_level(fib(c, c->lv_next), flags(c, c->lv_next), inst_table(c),
                                  (int)c->L.inst.size(), c->L.max_flags, c->stream));
-    if (c->a_stamped) HIPCHK(c, launch_zero(near_map(c, c->steps), c->L.flag_level, c->stream));
+    if (c->a_stamped || c->uncleared)
+        HIPCHK(c, launch_zero(near_map(c, c->steps), c->L.flag_level, c->stream));
     c->a_ready = c->a_stamped = c->a_rects = false;
+    c->uncleared = capturing(c->stream);
     return LBIB_OK;
 }
 
@@ -1409,7 +1415,8 @@ static lbib_status step_t(lbib_ctx* c, int nsteps)
     const bool want = c->overlap >= 1 || (c->overlap < 0 && c->L.inst.size() == 1 &&
                                           cells >= kOverlapMinCells);
     // a graph must hold its first step's forcing
-    if (note_recording(c) && !c->a_stamped) {
+    const bool rec = note_recording(c);
+    if (rec || c->uncleared) {
         lbib_status s = drop_pending_forcing(c);
         if (s != LBIB_OK) return s;
     }

@@ -433,9 +433,11 @@ def test_recorded_read_out(name, mode):
 
 @pytest.mark.parametrize("name,mode", [("fused", "dynamic"), ("fused", "kinematic"), ("pair", "dynamic"),
                                        ("two", "kinematic")])
-def test_recorded_restart(name, mode):
-    """A caller's graph that restores a saved state, recorded before the first step,
-    with the caller's own steps between its replays."""
+@pytest.mark.parametrize("before", [0, 4])
+def test_recorded_restart(name, mode, before):
+    """A caller's graph that restores a saved state, recorded before the first step or
+    after steps of the automatic schedule (the Dynamic one spreads the forcing of the
+    coming call ahead), with steps between the recording and its first replay."""
     import torch
     cfg = _recorded_case(name, mode)
     st = torch.cuda.Stream()
@@ -448,6 +450,8 @@ def test_recorded_restart(name, mode):
     for w, x in zip(whats, saved):
         src.get_state(w, 0, out=x)
     torch.cuda.synchronize()
+    a.step(before)
+    b.step(before)
     st.synchronize()
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph, stream=st):
@@ -471,3 +475,30 @@ def test_recorded_restart(name, mode):
             s.step(4)
         torch.cuda.synchronize()
         same()
+
+
+def test_steps_after_a_recording_not_replayed():
+    """Steps recorded while a forcing is spread ahead drop it in the graph; the
+    caller's next step, before any replay, starts from a clean level all the same."""
+    import torch
+    cfg = _fused_case("walls", 4, "dynamic")
+    st = torch.cuda.Stream()
+    a, b = lbib.Sim(cfg, stream=st), lbib.Sim(cfg)
+    b.set_overlap(False)
+    a.step(4)
+    b.step(4)
+    st.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=st):
+        a.step(2)
+    for n in (2, 4):
+        a.step(n)
+        b.step(n)
+        np.testing.assert_array_equal(a.pops(), b.pops())
+        np.testing.assert_array_equal(np.stack(a.capsule(0)), np.stack(b.capsule(0)))
+    for _ in range(3):
+        graph.replay()
+        b.step(2)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(a.pops(), b.pops())
+        np.testing.assert_array_equal(np.stack(a.capsule(0)), np.stack(b.capsule(0)))
