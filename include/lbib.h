@@ -214,7 +214,8 @@ lbib_status lbib_add_rigid_to(lbib_ctx* ctx, int32_t lattice, const double* node
  * caller's own graph would keep, and the Dynamic ones spread the coming call's
  * forcing ahead: from the first call of any kind that is being recorded on
  * (lbib_step, or lbib_get_state / lbib_set_state with device memory), a context
- * takes the last schedule.
+ * takes the last schedule, in the recorded calls themselves with one IB and one
+ * grid launch per step, also where lbib_set_overlap asks for more.
  * Overlapped schedule (lbib_set_overlap): lattices periodic in x (one, or
  * every lattice of a batch) with 1..4096 capsules and no contact force can
  * split the collide-stream pass.  A

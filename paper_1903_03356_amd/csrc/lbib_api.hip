@@ -1424,7 +1424,9 @@ static lbib_status step_t(lbib_ctx* c, int nsteps)
     const bool direct = c->overlap < 0 && c->ncap > 0 && c->L.levels == kForceLevels && !c->timing &&
                         exchange;
     if (direct && can_overlap && nsteps >= 2 && pair_pays<T>(c)) return step_pair_t<T>(c, nsteps);
-    if (can_overlap && want) return step_overlap_t<T>(c, nsteps);
+    // (not recorded: its launches hold the step's stamp and the count that the far pass
+    // waits for, and a second replay would find both already there)
+    if (can_overlap && want && !rec) return step_overlap_t<T>(c, nsteps);
     if (direct && c->L.inst.size() == 1)
         return step_fused_t<T>(c, nsteps, contact);
     // replays of captured blocks for the inner steps; timed runs launch directly

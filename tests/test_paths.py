@@ -502,3 +502,45 @@ def test_steps_after_a_recording_not_replayed():
         torch.cuda.synchronize()
         np.testing.assert_array_equal(a.pops(), b.pops())
         np.testing.assert_array_equal(np.stack(a.capsule(0)), np.stack(b.capsule(0)))
+
+
+@pytest.mark.parametrize("overlap", [None, True, "ahead"])
+def test_large_lattice_under_capture(overlap):
+    """A caller's graph of steps of a lattice past the size of the overlapped schedule
+    (its far pass waits inside from 2^23 cells), asked for or not, or asked for until
+    just before ("ahead": it left the forcing of the next step spread): every replay
+    computes its own near regions, also after the capsules were moved."""
+    import torch
+    cfg = wl._base("cap", 4096, 2049, 0.8, 4, "dynamic", 0, u_bottom=-0.02, u_top=0.02,
+                   init_profile=wl.INIT_COUETTE)
+    cfg["capsules"] = [wl.capsule(_ellipse(100.0 + 480.0 * i, 200.0 + 200.0 * i, 8.0, 6.0, 60),
+                                  0.05, 0.0, 1.0, 1.2) for i in range(8)]
+    st = torch.cuda.Stream()
+    a, b = lbib.Sim(cfg, stream=st), lbib.Sim(cfg)
+    a.set_overlap(True if overlap == "ahead" else overlap)
+    b.set_overlap(False)
+    a.step(2)
+    b.step(2)
+    if overlap == "ahead":
+        a.set_overlap(False)
+    st.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=st):
+        a.step(2)
+    for k in range(4):
+        graph.replay()
+        b.step(2)
+        torch.cuda.synchronize()
+        if k == 1:  # far enough for other rows and segments, past what a stale map holds
+            for c in range(8):
+                x, xp, uv = b.capsule(c)
+                for s in (a, b):
+                    s.set_capsule(c, x + [70.0, 20.0], xp + [70.0, 20.0], uv)
+        if k == 2:  # the caller's own steps between
+            a.step(2)
+            b.step(2)
+    np.testing.assert_array_equal(a.pops(), b.pops())
+    np.testing.assert_array_equal(a.force(), b.force())
+    for c in range(8):
+        np.testing.assert_array_equal(np.stack(a.capsule(c)), np.stack(b.capsule(c)))
+    assert a.check() == b.check() == 0
