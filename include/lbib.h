@@ -212,8 +212,8 @@ lbib_status lbib_add_rigid_to(lbib_ctx* ctx, int32_t lattice, const double* node
  *    overlapped schedule below.
  * The first three exchange population buffers or force levels, whose addresses a
  * caller's own graph would keep, and the Dynamic ones spread the coming call's
- * forcing ahead: from the first call of any kind that is being recorded on
- * (lbib_step, or lbib_get_state / lbib_set_state with device memory), a context
+ * forcing ahead: from the first call that is being recorded on (lbib_step, or with
+ * device memory lbib_set_state or the field states of lbib_get_state), a context
  * takes the last schedule, in the recorded calls themselves with one IB and one
  * grid launch per step, also where lbib_set_overlap asks for more.
  * Overlapped schedule (lbib_set_overlap): lattices periodic in x (one, or

@@ -441,8 +441,8 @@ static bool capturing(hipStream_t st)
 
 // At the start of every call that queues work: a caller's graph keeps the addresses
 // of the buffers and force levels that it was recorded with, and its replays are not
-// seen here, so from the first recorded call on (of any kind: a read-out, a restart,
-// steps) a context goes without the schedules that exchange them and without a forcing
+// seen here, so from the first recorded call on (steps, a restart, a read-out of a
+// field) a context goes without the schedules that exchange them and without a forcing
 // spread ahead of the call that reads it.
 static bool note_recording(lbib_ctx* c)
 {
@@ -1514,10 +1514,10 @@ extern "C" lbib_status lbib_step(lbib_ctx* c, int32_t nsteps, lbib_mode mode)
 template <typename T>
 static lbib_status get_t(lbib_ctx* c, int what, int cap, void* dst, size_t bytes, int on_dev)
 {
-    note_recording(c);
     // field states: cap names the lattice
     const bool field = what == LBIB_F_POPS || what == LBIB_F_POPS_DEV ||
                        what == LBIB_F_MOMENTS || what == LBIB_F_FORCE;
+    if (field) note_recording(c);  // (the node arrays stay in place)
     if (field && (cap < 0 || cap >= (int)c->L.inst.size()))
         return fail(c, LBIB_EINVAL, "bad lattice index");
     const Inst& I = c->L.inst[field ? cap : 0];
