@@ -286,13 +286,14 @@ lbib_status lbib_set_contact(lbib_ctx* ctx, double cutoff);
 /* Schedule of lbib_step: enable = 1 always uses the overlapped near / far
  * schedule where it applies, 0 one IB and one grid launch per step, -1 (the
  * default) the schedule that lbib_step says.  In the overlapped schedule of one
- * FP32 lattice of 2^23 cells or more, the far kernel of every step after a call's
- * first waits for that step's IB launch on the device (a counter the IB blocks
- * raise), not on the queue; this needs the two streams' kernels to run
- * concurrently.  enable = 2 is the overlapped schedule with queue-level waits
- * only, for tools that run kernels one at a time (counter collection, kernel
- * serialisation): under such a tool the device-side wait gives up after about
- * 0.05 s per block and raises LBIB_FLAG_SYNC.  Results are the same bits in
+ * FP32 lattice of 2^23 cells or more, with at most one capsule for every four
+ * compute units, the far kernel of every step after a call's first waits for that
+ * step's IB launch on the device (a counter the IB blocks raise), not on the
+ * queue; this needs the two streams' kernels to run concurrently.  enable = 2 is
+ * the overlapped schedule with queue-level waits only, for tools that run kernels
+ * one at a time (counter collection, kernel serialisation): under such a tool the
+ * device-side wait gives up after about 0.05 s per block and raises
+ * LBIB_FLAG_SYNC.  Results are the same bits in
  * every schedule.  Errors: EINVAL (other values). */
 lbib_status lbib_set_overlap(lbib_ctx* ctx, int32_t enable);
 

@@ -1141,8 +1141,11 @@ static lbib_status step_overlap_t(lbib_ctx* c, int nsteps)
     for (const Inst& I : c->L.inst) cells += (long long)I.grid.nx * I.grid.ny;
     // FP32 only: an FP64 IB block finds no registers beside resident far waves, so they
     // would wait for a launch that cannot start until they give up.
+    // And a launch whose blocks are all resident before far(n) fills the device: those
+    // that are not wait for slots that its waiting waves take (4096^2 with 512 capsules
+    // gave up, at 2048 in every step, 8.4 ms; 32 run as fast as they can).
     const bool inside = sizeof(T) == 4 && c->L.inst.size() == 1 && cells >= kFarWaitInsideCells &&
-                        c->overlap != 2;
+                        c->overlap != 2 && c->ncap <= c->num_cu / 4;
     for (int k = 0; k < nsteps; k++) {
         const long long n = c->steps + k;
         long long nn = n;

@@ -544,3 +544,26 @@ def test_large_lattice_under_capture(overlap):
     for c in range(8):
         np.testing.assert_array_equal(np.stack(a.capsule(c)), np.stack(b.capsule(c)))
     assert a.check() == b.check() == 0
+
+
+def _grid_of_capsules(nx, ny, cols, rows, a=8.0, b=6.0):
+    return [wl.capsule(_ellipse((i + 0.5) * nx / cols, 8 + (j + 0.5) * (ny - 16) / rows, a, b, 60),
+                       0.05, 0.0, 1.0, 1.2) for j in range(rows) for i in range(cols)]
+
+
+@pytest.mark.parametrize("ny,cols,rows", [(2049, 8, 8), (2049, 13, 5), (4096, 32, 16)])
+def test_overlap_of_many_capsules(ny, cols, rows):
+    """The split schedule of a large FP32 lattice at and past the number of capsules
+    up to which its far pass waits inside: no wait given up, the bits of a single pass."""
+    cfg = wl._base("far", 4096, ny, 0.8, 4, "dynamic", 0, u_bottom=-0.02, u_top=0.02,
+                   init_profile=wl.INIT_COUETTE)
+    cfg["capsules"] = _grid_of_capsules(4096, ny, cols, rows)
+    a, b = lbib.Sim(cfg), lbib.Sim(cfg)
+    a.set_overlap(True)
+    b.set_overlap(False)
+    for s in (a, b):
+        s.step(5)
+    assert a.check() == b.check() == 0
+    np.testing.assert_array_equal(a.force(), b.force())
+    for c in range(0, cols * rows, 7):
+        np.testing.assert_array_equal(np.stack(a.capsule(c)), np.stack(b.capsule(c)))
