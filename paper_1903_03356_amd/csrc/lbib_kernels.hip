@@ -698,8 +698,15 @@ int pair_tiles(const GridArgs* g, int n, int real_bytes, TwoTile* out, int& thre
         }
         return t;
     };
+    // the fewest rows that leave at most `want` tiles (more rows, fewer tiles); by
+    // bisection, since every sizing call of a batch comes here
+    int hi = kTwoMaxRows;
     rows = 4;
-    while (rows < kTwoMaxRows && count(rows) > want) rows++;
+    while (rows < hi) {
+        const int mid = (rows + hi) / 2;
+        if (count(mid) > want) rows = mid + 1;
+        else hi = mid;
+    }
     int t = 0;
     for (int i = 0; i < n; i++) {
         const int c = two_cols(g[i].nx, halo, threads);

@@ -174,3 +174,56 @@ def test_noalloc_gradient_declared_with_its_scratch_size(L):
 def test_membrane_limits_arguments(L):
     """lbib_set_limits rejects a NULL context before touching a device."""
     assert L.lbib_set_limits(None, 1.0, 0.05) == lbib.EINVAL
+
+
+def _pair_tiles(grids):
+    """Tiles of a batch's pass of two steps: 320 threads a block, the fewest rows (4 or
+    more) that leave at most 3072 tiles, a multiple of 8."""
+    halo = 128 // grids[0].real_bytes
+    max_cols = (320 - halo - 1) // halo * halo
+
+    def tiles(rows):
+        t = 0
+        for g in grids:
+            blocks = -(-g.nx // max_cols)
+            cols = -(-(-(-g.nx // blocks)) // halo) * halo
+            t += -(-g.nx // cols) * -(-g.ny // rows)
+        return t
+    rows = 4
+    while rows < 1022 and tiles(rows) > 3072:
+        rows += 1
+    return -(-tiles(rows) // 8) * 8
+
+
+def _caps_bytes(grids, tiles):
+    """Size of the capsule buffer: tables of capsules, lattices, tile rounds, near
+    regions, boxes and the tiles of the pass of two steps."""
+    up = lambda b: -(-b // 256) * 256  # noqa: E731
+    rounds, flags, caps = [0] * 9, 0, sum(g.max_capsules for g in grids)
+    for g in grids:
+        nxp = -(-g.nx // 64) * 64
+        nseg = (nxp + 64 if nxp % 512 == 0 else nxp) // 64
+        flags += -(-g.ny * nseg // 64) * 64
+        for k in range(9):
+            bands = -(-g.ny // (4 * (1, 2, 4)[k % 3]))
+            rounds[k] += -(-bands // 8) * nseg if k < 3 else -(-bands * nseg // 8)
+    return (up(312 * caps) + up(112 * len(grids)) + sum(up(8 * r) for r in rounds) + up(32 * caps)
+            + up(8 * flags) + 2 * up(16 * caps) + up(16 * tiles))
+
+
+@pytest.mark.parametrize("n,nx,ny,real_bytes", [(64, 500, 130, 8), (128, 511, 129, 4), (700, 130, 65, 4),
+                                                (2100, 64, 64, 4), (3, 1500, 2000, 4), (2, 41, 60000, 8)])
+def test_tiles_of_a_batch(L, n, nx, ny, real_bytes):
+    grids = [lbib.make_grid(nx - 7 * (i % 5), ny - i % 9, real_bytes, 1, 30, 30) for i in range(n)]
+    assert 9 * real_bytes * sum(-(-g.nx // 64) * 64 * g.ny for g in grids) >= 140 << 20
+    assert lbib.required_bytes_batch(grids, 5) == _caps_bytes(grids, _pair_tiles(grids))
+
+
+def test_sizing_a_large_batch_is_quick(L):
+    """Eight sizing calls of 65,536 lattices: 0.1 s of work; the search of the tile rows
+    one by one took 6 s."""
+    import time
+    grids = (lbib.lbib_grid * 65536)(*[lbib.make_grid(64 + i % 60, 32 + i % 7, 4) for i in range(65536)])
+    t = time.perf_counter()
+    assert all(L.lbib_required_bytes_batch(grids, 65536, i) > 0 for i in range(8))
+    assert time.perf_counter() - t < 2.0
