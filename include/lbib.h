@@ -204,8 +204,8 @@ lbib_status lbib_add_rigid_to(lbib_ctx* ctx, int32_t lattice, const double* node
  *  - 140 MiB of populations or more (a lattice, or a batch in total), periodic in
  *    x, no contact force: two steps per pass over the populations, after two
  *    launches that spread the forces of both;
- *  - 16 MiB or more without capsules (one lattice, periodic in x): two steps per
- *    pass;
+ *  - 16 MiB or more without capsules (one lattice, periodic in x; not with
+ *    lbib_set_overlap(ctx, 0)): two steps per pass;
  *  - else (batches, kernel timing, more than 2^28 cells, or lbib_set_overlap or
  *    lbib_set_graph given): one IB launch (node update of the previous step fused
  *    with the forcing of this one) and one collide-stream launch per step, or the
@@ -265,7 +265,8 @@ lbib_status lbib_check(lbib_ctx* ctx, int32_t* flags_out);
  * enable = 0 stops.  lbib_get_timing waits for the stream and returns
  * out[6] = {grid (or far) kernel total ms, its launches, IB kernel total ms,
  * IB launches, near kernel total ms, near launches}.  It then resets the
- * counters. */
+ * counters.  Timed steps take the schedules that have launches of one kernel and
+ * one step each (the last one of lbib_step), and are slower for it. */
 lbib_status lbib_set_timing(lbib_ctx* ctx, int32_t enable);
 
 /* Contact force between capsules (Sec. 3.4, Eq. 27).  cutoff > 0 switches it

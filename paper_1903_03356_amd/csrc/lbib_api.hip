@@ -1447,15 +1447,15 @@ static lbib_status step_t(lbib_ctx* c, int nsteps)
     }
     // without capsules two steps go in one pass; the state then stands in the other
     // population buffer, which takes the first one's place (graphs, the library's and
-    // the caller's, hold the buffers' addresses and keep single passes)
-    const bool two = c->ncap == 0 && exchange && c->L.inst.size() == 1 &&
-                     grid_two_pays<T>(grid_args(c->L.inst[0]));
+    // the caller's, hold the buffers' addresses and keep single passes; so do timed
+    // steps, one launch each, and lbib_set_overlap(0))
+    const bool two = c->ncap == 0 && exchange && !c->timing && c->overlap != 0 &&
+                     c->L.inst.size() == 1 && grid_two_pays<T>(grid_args(c->L.inst[0]));
     for (int k = 0; k < nsteps;) {
         const long long n = c->steps + k;
         if (two && nsteps - k >= 2) {
             long long nn = n;
-            lbib_status s = launch_timed<T>(c, 0, do_grid_two<T>, &nn);
-            if (s != LBIB_OK) return s;
+            HIPCHK(c, do_grid_two<T>(c, &nn));
             std::swap(c->buf[LBIB_BUF_POPS_A], c->buf[LBIB_BUF_POPS_B]);
             k += 2;
             continue;

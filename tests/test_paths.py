@@ -567,3 +567,26 @@ def test_overlap_of_many_capsules(ny, cols, rows):
     np.testing.assert_array_equal(a.force(), b.force())
     for c in range(0, cols * rows, 7):
         np.testing.assert_array_equal(np.stack(a.capsule(c)), np.stack(b.capsule(c)))
+
+
+@pytest.mark.parametrize("real_bytes", [4, 8])
+def test_timed_steps_take_a_launch_each(real_bytes):
+    """Kernel timing of a capsule-free lattice that takes two steps per pass when it is
+    off: one timed grid launch per step, also for odd counts; the same bits either way,
+    and with the schedule of one launch per step asked for."""
+    cfg = wl._base("two", 1024, 512, 0.7, real_bytes, "kinematic", 0, u_top=0.02,
+                   init_profile=wl.INIT_COUETTE)
+    a, b, c = lbib.Sim(cfg), lbib.Sim(cfg), lbib.Sim(cfg)
+    a.set_timing(True)
+    c.set_overlap(False)
+    for n in (4, 3):
+        for s in (a, b, c):
+            s.step(n)
+    t = a.get_timing()
+    assert t["grid_launches"] == 7 and t["ib_launches"] == 0
+    a.set_timing(False)
+    for s in (a, b, c):
+        s.step(2)
+    assert a.get_timing()["grid_launches"] == 0
+    np.testing.assert_array_equal(a.pops(), b.pops())
+    np.testing.assert_array_equal(a.pops(), c.pops())
