@@ -1393,9 +1393,14 @@ static bool pair_pays(const lbib_ctx* c)
 {
     if (c->L.pop_elems * sizeof(T) < kPairMinBytes) return false;
     if (c->L.inst.size() == 1) return grid_two_pays<T>(grid_args(c->L.inst[0]));
-    for (const Inst& I : c->L.inst)
+    double cells = 0, narrow = 0;
+    for (const Inst& I : c->L.inst) {
         if (9.0 * I.nxp * I.grid.ny * sizeof(T) >= 4.0 * (1u << 30) - 4096.0) return false;
-    return c->L.two_tiles > 0;
+        cells += (double)I.nxp * I.grid.ny;
+        if (I.grid.nx <= kSegW) narrow += (double)I.nxp * I.grid.ny;
+    }
+    // (2000 lattices of 64 x 48 86 / 91, FP64 1000 of them 89 / 96; of 100 x 64 104 / 86)
+    return c->L.two_tiles > 0 && 2.0 * narrow <= cells;
 }
 
 template <typename T>

@@ -607,12 +607,16 @@ __global__ __launch_bounds__(kTwoMaxThreads) void k_grid_two(
 // the size where a single pass is bound by its launch (us per step in single /
 // double passes, FP32: 512^2, 9 MiB, 4.8 / 5.0-6.2; 768^2, 20 MiB, 7.7 / 6.5; 1024^2
 // 12.7 / 9.6; 2048^2 52.9 / 32.4; 8192^2 839 / 501; FP64: 550^2 8.8 / 7.5, 1777 x 1003
-// 40.1 / 27.2, 4096^2 408 / 249) and within the 32-bit buffer offsets.
+// 40.1 / 27.2, 4096^2 408 / 249) and within the 32-bit buffer offsets; and its rows
+// longer than a segment, since a block's halo is as long as a short row (60 MiB, FP32:
+// 16 columns 13.2 / 25.3, 64 columns 20.3 / 25.4, 70 columns 17.0 / 15.5; FP64: 16
+// columns 10.9 / 13.5, 40 columns 16.9 / 19.6, 64 columns even, 70 columns 16.6 / 12.2).
 template <typename T>
 bool grid_two_pays(const GridArgs& g)
 {
     const double bytes = 9.0 * g.ny * g.nxp * sizeof(T);
-    return g.periodic_x && bytes >= kTwoMinBytes && bytes < 4.0 * (1u << 30) - 4096.0;
+    return g.periodic_x && g.nx > kSegW && bytes >= kTwoMinBytes &&
+           bytes < 4.0 * (1u << 30) - 4096.0;
 }
 
 // Column blocks of at most `max_threads` lanes, and as many rows per block as

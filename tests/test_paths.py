@@ -590,3 +590,46 @@ def test_timed_steps_take_a_launch_each(real_bytes):
     assert a.get_timing()["grid_launches"] == 0
     np.testing.assert_array_equal(a.pops(), b.pops())
     np.testing.assert_array_equal(a.pops(), c.pops())
+
+
+def _step_us(sim, steps, calls=1):
+    """Microseconds a step, the least of seven timings."""
+    import torch
+    best = 1e30
+    for i in range(8):
+        e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        e0.record()
+        for _ in range(calls):
+            sim.step(steps)
+        e1.record()
+        torch.cuda.synchronize()
+        if i:
+            best = min(best, 1e3 * e0.elapsed_time(e1) / (steps * calls))
+    return best
+
+
+def _default_against_serial(cfg, steps, bar):
+    """The automatic schedule takes at most `bar` times as long as one IB and one grid
+    launch per step."""
+    make = lbib.Batch if isinstance(cfg, list) else lbib.Sim
+    a, b = make(cfg), make(cfg)
+    b.set_overlap(False)
+    ta, tb = _step_us(a, steps), _step_us(b, steps)
+    log(f"{ta:.1f} us a step, serial {tb:.1f}")
+    assert ta <= bar * tb
+
+
+@pytest.mark.parametrize("name,real_bytes", [("grid", 4), ("capsules", 4), ("batch", 4)])
+def test_narrow_lattices_take_single_passes(name, real_bytes):
+    """Rows of a segment or less: two steps in one pass would take 1.2 (batch) to 1.9
+    times as long as single ones (the bar: one route timed twice, to 6 %)."""
+    def lattice(nx, ny, caps):
+        cfg = wl._base("narrow", nx, ny, 0.8, real_bytes, "kinematic", 0,
+                       init_profile=wl.INIT_POISEUILLE,
+                       body_force_x=wl.poiseuille_body_force(0.8, ny, 0.02))
+        cfg["capsules"] = [wl.capsule(_ellipse(0.5 * nx, ny * (i + 1.0) / (caps + 1), 6.0, 6.0, 50),
+                                      0.01, 0.0, 1.0, 1.0) for i in range(caps)]
+        return cfg
+    cfg = {"grid": lambda: lattice(16, 27306, 0), "capsules": lambda: lattice(48, 70000, 4),
+           "batch": lambda: [lattice(40, 47, i % 200 == 0) for i in range(2500)]}[name]()
+    _default_against_serial(cfg, 20, 1.06)
