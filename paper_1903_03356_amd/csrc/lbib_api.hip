@@ -72,6 +72,13 @@ struct Layout {
     size_t two_off = 0;
 };
 
+// What a patch's own grid step (k_step) costs a capsule's block: cells of the ring, the
+// bands of rows it takes them in, and an estimate in us.  The largest of all capsules.
+struct OwnStep {
+    int ring = 0, bands = 0;
+    double us = 0;
+};
+
 struct lbib_ctx {
     Layout L;
     double nu0 = 0;
@@ -92,6 +99,8 @@ struct lbib_ctx {
     std::vector<hipEvent_t> pool;
     std::vector<int> cap_off, cap_nv, cap_inst;  // host copy of the capsule table layout
     std::vector<double> cap_kb, cap_P0;
+    std::vector<int> cap_w, cap_h;  // patch box of the stress-free shape
+    OwnStep own;  // of the capsules, for the schedules with the patch's own grid step
     std::vector<int> cap_rigid;
     // overlapped schedule: far part of the grid step on a second stream
     // (-1 automatic: large lattices only; 0 off; 1 on; 2 on, queue-level waits only)
@@ -798,6 +807,8 @@ static lbib_status add_capsule_t(lbib_ctx* c, int inst, const double* xy, int n,
     c->cap_inst.push_back(inst);
     c->cap_kb.push_back(kb);
     c->cap_P0.push_back(P);
+    c->cap_w.push_back((int)W);
+    c->cap_h.push_back((int)H);
     c->cap_rigid.push_back(rigid ? 1 : 0);
     c->ncap++;
     c->nodes_used += n;
@@ -899,6 +910,45 @@ static void size_patches(lbib_ctx* c)
     c->patch_use = need < (double)c->patch_cap ? (int)need : c->patch_cap;
     c->lds_use = ib_lds_bytes<T>(c->patch_use, c->L.max_nv);
     c->lds_ncap = c->ncap;
+    // The patch with its two spare cells and a sixteenth for its deformation; nine
+    // values a ring cell behind three moments a patch cell (ib_block).  Another band
+    // costs two barriers and a round of loads that nothing hides.
+    OwnStep o;
+    for (size_t i = 0; i < c->cap_w.size(); i++) {
+        const long long w = c->cap_w[i] + 2 + c->cap_w[i] / 16, h = c->cap_h[i] + 2 + c->cap_h[i] / 16;
+        const long long left = 3LL * c->patch_use - 3 * w * h;
+        const long long rows = left > 0 ? left / (9 * (w + 2)) - 2 : 0;
+        const int bands = rows > 0 ? (int)((h + rows - 1) / rows) : 1000;
+        const int ring = (int)((w + 2) * (h + 2));
+        const double k = 1e-3 * ring;
+        o.ring = std::max(o.ring, ring);
+        o.bands = std::max(o.bands, bands);
+        o.us = std::max(o.us, sizeof(T) == 4 ? 2.0 * k + (bands - 1) * (2.0 + 1.5 * k)
+                                             : 4.5 * k + (bands - 1) * (2.0 + 3.0 * k));
+    }
+    c->own = o;
+}
+
+// Whether the schedules pay in which a capsule's block steps its own patch (one
+// launch per step, two steps per pass), by the capsules' size.  What they spare is
+// a grid launch, a few us, and on larger lattices the time that the grid pass runs
+// beside the capsules; what they cost is OwnStep.  us per step with one launch / two
+// launches per step, circles of radius r, FP64 (bands from 13 on), 512x200 with one
+// Kinematic capsule: r 10 20.5 / 20.0, 14 27.5 / 22.5, 20 31.4 / 22.9, 26 202 / 26.9, 28 107 /
+// 27.7; 1024x512 (37 MiB) with eight Dynamic ones: 8 26.5 / 31.9, 14 39.5 / 34.8, 20 53.9 /
+// 40.8; two steps per pass, 2048^2 (297 MiB): 14 98.8 / 127, 20 116 / 134, 24 160 / 139.  FP32
+// (bands from 22), 512x200: 14 20.2 / 19.6, 22 23.0 / 18.9, 40 76.3 / 29.9; 1024x512: 20 32.2 /
+// 32.1, 24 40.8 / 37.3, 40 95 / 45; 2048^2: 20 69.6 / 79.3, 24 79.5 / 83.7, 40 186 / 103.
+// On small lattices a patch across the wrap or beside a wall costs another round: 256x120
+// with four there, FP64 r 8 18.5 / 18.9, 11 21.8 / 19.9, 12 24.6 / 19.1, FP32 14 17.4 / 16.4, 16 22.3 /
+// 19.9, 21 27.3 / 25.0 (and 12 without a patch there 15.8 / 16.4).
+template <typename T>
+static bool own_step_pays(const lbib_ctx* c)
+{
+    const double mib = c->L.pop_elems * sizeof(T) / (double)(1 << 20);
+    if (mib < (sizeof(T) == 4 ? 24.0 : 12.0))
+        return c->own.bands == 1 && c->own.ring <= (sizeof(T) == 4 ? 1700 : 1024);
+    return c->own.us <= 4.0 + 0.2 * mib;
 }
 
 template <typename T>
@@ -1391,7 +1441,7 @@ static lbib_status capture_steps(lbib_ctx* c, long long n0, bool contact, bool d
 template <typename T>
 static bool pair_pays(const lbib_ctx* c)
 {
-    if (c->L.pop_elems * sizeof(T) < kPairMinBytes) return false;
+    if (c->L.pop_elems * sizeof(T) < kPairMinBytes || !own_step_pays<T>(c)) return false;
     if (c->L.inst.size() == 1) return grid_two_pays<T>(grid_args(c->L.inst[0]));
     double cells = 0, narrow = 0;
     for (const Inst& I : c->L.inst) {
@@ -1435,7 +1485,7 @@ static lbib_status step_t(lbib_ctx* c, int nsteps)
     // (not recorded: its launches hold the step's stamp and the count that the far pass
     // waits for, and a second replay would find both already there)
     if (can_overlap && want && !rec) return step_overlap_t<T>(c, nsteps);
-    if (direct && c->L.inst.size() == 1)
+    if (direct && c->L.inst.size() == 1 && own_step_pays<T>(c))
         return step_fused_t<T>(c, nsteps, contact);
     // replays of captured blocks for the inner steps; timed runs launch directly
     const bool graphs = c->graph == 1 && !c->timing;

@@ -633,3 +633,64 @@ def test_narrow_lattices_take_single_passes(name, real_bytes):
     cfg = {"grid": lambda: lattice(16, 27306, 0), "capsules": lambda: lattice(48, 70000, 4),
            "batch": lambda: [lattice(40, 47, i % 200 == 0) for i in range(2500)]}[name]()
     _default_against_serial(cfg, 20, 1.06)
+
+
+@pytest.mark.parametrize("mode", ["dynamic", "kinematic"])
+@pytest.mark.parametrize("name,real_bytes,mid,large", [("bands", 8, 13.0, 22.0), ("direct", 8, 0.0, 140.0),
+                                                       ("bands", 4, 21.0, 38.0)])
+def test_patch_that_outgrew_its_launch(name, real_bytes, mid, large, mode):
+    """The patch's own grid step in bands of rows, and of a patch so wide that no row of
+    its ring fits: shapes that the schedule of one launch per step is not chosen for
+    are reached by deforming a capsule that it is chosen for.  The same bits as a grid
+    and an IB launch per step."""
+    u, tau = 0.02, 0.8
+    nx, ny = (400, 48) if name == "direct" else (160, 128)
+    cfg = wl._base(name, nx, ny, tau, real_bytes, mode, 0, init_profile=wl.INIT_POISEUILLE,
+                   body_force_x=wl.poiseuille_body_force(tau, ny, u))
+    c = (200.0, 22.0) if name == "direct" else (80.3, 60.2)
+    # a star: a small patch, and a perimeter that sizes the LDS for a large one
+    n = 120
+    t = 2.0 * np.pi * (np.arange(n) + 0.5) / n
+    r = 6.0 * (1.0 + 0.5 * np.cos(12 * t))
+    star = np.stack([c[0] + r * np.cos(t), c[1] + r * np.sin(t)], 1)
+    cfg["capsules"] = [wl.capsule(star, 1e-6, 0.0, 0.0, 1.2)]
+    a, b = lbib.Sim(cfg), lbib.Sim(cfg)
+    b.set_overlap(False)
+
+    def same():
+        np.testing.assert_array_equal(a.pops(), b.pops())
+        np.testing.assert_array_equal(a.force(), b.force())
+        np.testing.assert_array_equal(np.stack(a.capsule(0)), np.stack(b.capsule(0)))
+
+    for s in (a, b):
+        s.step(2)
+    same()
+    for size in (mid, large):
+        if not size:
+            continue
+        x = _ellipse(*c, size, 3.0 if name == "direct" else size - 1.0, n)
+        for s in (a, b):
+            s.set_capsule(0, x, x, np.zeros_like(x))
+            s.step(3)
+        same()
+    assert a.check() == b.check()
+
+
+@pytest.mark.parametrize("nx,ny,real_bytes,radius,caps,mode", [
+    (512, 200, 8, 26.0, 1, "kinematic"),    # dozens of bands of rows: 3.9 times as long
+    (512, 200, 8, 20.0, 1, "kinematic"),    # 4 bands: 1.4
+    (512, 200, 8, 2.3, 1, "kinematic"),     # a ring that the LDS of a tiny patch does not hold: 1.3
+    (512, 200, 4, 40.0, 1, "kinematic"),    # 2.5
+    (1024, 512, 4, 40.0, 6, "dynamic"),     # 2.1
+    (1500, 1400, 8, 28.0, 6, "dynamic"),    # two steps per pass: 1.8
+])
+def test_large_capsules_take_two_launches(nx, ny, real_bytes, radius, caps, mode):
+    """Capsules whose patch does not step well by itself (the factors: the schedules of
+    one launch per step and of two steps per pass, where they do not suit); the bar:
+    one route timed twice, to 6 %."""
+    n = int(2 * np.pi * radius / 0.75) + 1
+    cfg = wl._base("large", nx, ny, 0.8, real_bytes, mode, 0, init_profile=wl.INIT_POISEUILLE,
+                   body_force_x=wl.poiseuille_body_force(0.8, ny, 0.02))
+    cfg["capsules"] = [wl.capsule(_ellipse(nx * (i + 0.5) / caps, 0.5 * ny, radius, radius, n),
+                                  wl.ks_from_ca(0.8, 0.02, 5e-2), 0.0, 1.0, 1.2) for i in range(caps)]
+    _default_against_serial(cfg, 15, 1.06)
