@@ -1432,6 +1432,22 @@ static lbib_status capture_steps(lbib_ctx* c, long long n0, bool contact, bool d
     return LBIB_OK;
 }
 
+// Whether one launch per step pays on a lattice of this size (with the contact force,
+// an open channel, or one step per call; else two steps per pass take over).  Its grid
+// blocks run at the capsule blocks' registers and LDS, one or two on a compute unit, which
+// hides less of the memory's latency once the populations leave the cache.  us per step
+// with one / two launches, 16 capsules: FP32 open 1792^2 (110 MiB) 40.4 / 51.0, 2048^2 (149
+// MiB) 68.3 / 71.6, 2200^2 (169 MiB) 87.6 / 72.7, 2896^2 135 / 123, 4096^2 258 / 222; with contacts
+// 2048^2 74.7 / 79.3, 2200^2 88.1 / 81.8, 4096^2 264 / 233; FP64 open 1600^2 (176 MiB) 71.9 /
+// 76.1, 2048^2 (297 MiB) 121 / 123, 2200^2 147 / 140, 2600^2 197 / 188; with contacts 1448^2 (144
+// MiB) 68.5 / 77.6, 1600^2 88.3 / 87.5, 1800^2 115 / 111, 2600^2 215 / 197.
+template <typename T>
+static bool fused_pays(const lbib_ctx* c, bool contact)
+{
+    const double limit = (sizeof(T) == 4 || contact ? 160.0 : 300.0) * (1 << 20);
+    return c->L.inst.size() == 1 && c->L.pop_elems * sizeof(T) <= limit && own_step_pays<T>(c);
+}
+
 // Whether two steps with capsules go in one pass: from the size on where the pass
 // itself, and not the two IB launches before it, is most of the time.  us per step,
 // fused or one pass per step / pairs, 32 capsules: FP32 2048x512 20.0 / 29.8, 2048x1536
@@ -1485,8 +1501,7 @@ static lbib_status step_t(lbib_ctx* c, int nsteps)
     // (not recorded: its launches hold the step's stamp and the count that the far pass
     // waits for, and a second replay would find both already there)
     if (can_overlap && want && !rec) return step_overlap_t<T>(c, nsteps);
-    if (direct && c->L.inst.size() == 1 && own_step_pays<T>(c))
-        return step_fused_t<T>(c, nsteps, contact);
+    if (direct && fused_pays<T>(c, contact)) return step_fused_t<T>(c, nsteps, contact);
     // replays of captured blocks for the inner steps; timed runs launch directly
     const bool graphs = c->graph == 1 && !c->timing;
     const int tile = c->tile_shape * 256 + c->tile_resident;
