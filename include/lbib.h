@@ -205,11 +205,12 @@ lbib_status lbib_add_rigid_to(lbib_ctx* ctx, int32_t lattice, const double* node
  *    x, no contact force: two steps per pass over the populations, after two
  *    launches that spread the forces of both;
  *    both where the patches are small enough to be stepped beside the node work (on
- *    a small lattice a half-length of about 10 in FP64 and 17 in FP32);
+ *    a small lattice a half-length of about 10 in FP64 and 17 in FP32), and the
+ *    capsules few enough for the lattice;
  *  - 16 MiB or more without capsules (one lattice, periodic in x; not with
  *    lbib_set_overlap(ctx, 0)): two steps per pass;
- *  - else (batches, kernel timing, more than 2^28 cells, or lbib_set_overlap or
- *    lbib_set_graph given): one IB launch (node update of the previous step fused
+ *  - else (also with kernel timing, for more than 2^28 cells, and with
+ *    lbib_set_overlap or lbib_set_graph given): one IB launch (node update of the previous step fused
  *    with the forcing of this one) and one collide-stream launch per step, or the
  *    overlapped schedule below.
  * The first three exchange population buffers or force levels, whose addresses a
@@ -227,8 +228,8 @@ lbib_status lbib_add_rigid_to(lbib_ctx* ctx, int32_t lattice, const double* node
  * library's own, so the IB work runs beside it.  The results are
  * bit-identical to the single pass, and the call still returns with all work
  * ordered on the bound stream.  By default the split is used where the schedules
- * above do not apply, for a single lattice of 2^22 cells or more; a batch takes
- * it only when asked (many small lattices: the far launch slows the IB launch
+ * above do not apply, for a single lattice of 2^22 cells or more with at most one
+ * capsule for every two compute units; a batch takes it only when asked (many small lattices: the far launch slows the IB launch
  * beside it more than the split saves).
  * Captured steps (lbib_set_graph(ctx, 1)): unless kernel timing is
  * on, the inner steps of a call go in blocks of 16 steps captured once into a

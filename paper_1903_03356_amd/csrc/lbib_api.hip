@@ -910,21 +910,22 @@ static void size_patches(lbib_ctx* c)
     c->patch_use = need < (double)c->patch_cap ? (int)need : c->patch_cap;
     c->lds_use = ib_lds_bytes<T>(c->patch_use, c->L.max_nv);
     c->lds_ncap = c->ncap;
-    // The patch with its two spare cells and a sixteenth for its deformation; nine
-    // values a ring cell behind three moments a patch cell (ib_block).  Another band
-    // costs two barriers and a round of loads that nothing hides.
+    // The patch with its two spare cells; its bands with a little more for its
+    // deformation.  Nine values a ring cell lie behind three moments a patch cell
+    // (ib_block).  Another band costs two barriers and a round of loads that nothing
+    // hides.
     OwnStep o;
     for (size_t i = 0; i < c->cap_w.size(); i++) {
-        const long long w = c->cap_w[i] + 2 + c->cap_w[i] / 16, h = c->cap_h[i] + 2 + c->cap_h[i] / 16;
+        const int ring = (c->cap_w[i] + 4) * (c->cap_h[i] + 4);
+        const long long w = c->cap_w[i] + 2 + c->cap_w[i] / 24, h = c->cap_h[i] + 2 + c->cap_h[i] / 24;
         const long long left = 3LL * c->patch_use - 3 * w * h;
         const long long rows = left > 0 ? left / (9 * (w + 2)) - 2 : 0;
         const int bands = rows > 0 ? (int)((h + rows - 1) / rows) : 1000;
-        const int ring = (int)((w + 2) * (h + 2));
         const double k = 1e-3 * ring;
         o.ring = std::max(o.ring, ring);
         o.bands = std::max(o.bands, bands);
         o.us = std::max(o.us, sizeof(T) == 4 ? 2.0 * k + (bands - 1) * (2.0 + 1.5 * k)
-                                             : 4.5 * k + (bands - 1) * (2.0 + 3.0 * k));
+                                             : 4.0 * k + (bands - 1) * (2.0 + 2.5 * k));
     }
     c->own = o;
 }
@@ -947,7 +948,7 @@ static bool own_step_pays(const lbib_ctx* c)
 {
     const double mib = c->L.pop_elems * sizeof(T) / (double)(1 << 20);
     if (mib < (sizeof(T) == 4 ? 24.0 : 12.0))
-        return c->own.bands == 1 && c->own.ring <= (sizeof(T) == 4 ? 1700 : 1024);
+        return c->own.bands == 1 && c->own.ring <= (sizeof(T) == 4 ? 1800 : 1100);
     return c->own.us <= 4.0 + 0.2 * mib;
 }
 
@@ -1440,12 +1441,26 @@ static lbib_status capture_steps(lbib_ctx* c, long long n0, bool contact, bool d
 // MiB) 68.3 / 71.6, 2200^2 (169 MiB) 87.6 / 72.7, 2896^2 135 / 123, 4096^2 258 / 222; with contacts
 // 2048^2 74.7 / 79.3, 2200^2 88.1 / 81.8, 4096^2 264 / 233; FP64 open 1600^2 (176 MiB) 71.9 /
 // 76.1, 2048^2 (297 MiB) 121 / 123, 2200^2 147 / 140, 2600^2 197 / 188; with contacts 1448^2 (144
-// MiB) 68.5 / 77.6, 1600^2 88.3 / 87.5, 1800^2 115 / 111, 2600^2 215 / 197.
+// MiB) 68.5 / 77.6, 1600^2 88.3 / 87.5, 1800^2 115 / 111, 2600^2 215 / 197; one step per call FP64
+// 2000^2 (290 MiB) Dynamic 121 / 133, Kinematic 131 / 126.
+// And while the capsules' blocks are resident in one round, so that the grid's have
+// somewhere to run beside them: by the registers two of the Kinematic FP32 instance on a
+// compute unit, one of the others, and five eighths of that where the grid pass is the
+// longer part.  Radius 7 to 8, Dynamic FP32 1024^2 (37 MiB) with 192 capsules 28.6 / 29.9, 256
+// 31.3 / 31.4, 400 39.8 / 35.4, 1000 79.7 / 56.0; 1280^2 with 256 40.5 / 38.4; 1800^2 with 130 51.1
+// / 53.7, 256 64.2 / 55.9; Kinematic FP32 1024^2 with 400 29.1 / 32.9, 1448^2 with 512 43.4 / 46.1,
+// 1800^2 with 256 50.0 / 53.1, 400 59.2 / 57.8, 512 66.3 / 59.1; FP64 1024^2 (75 MiB) with 192 39.5 /
+// 42.9, 256 43.9 / 44.2; 1280^2 with 200 53.5 / 56.5, 256 59.8 / 57.0; 1400^2 with 130 64.5 / 65.7.
 template <typename T>
 static bool fused_pays(const lbib_ctx* c, bool contact)
 {
-    const double limit = (sizeof(T) == 4 || contact ? 160.0 : 300.0) * (1 << 20);
-    return c->L.inst.size() == 1 && c->L.pop_elems * sizeof(T) <= limit && own_step_pays<T>(c);
+    const double mib = c->L.pop_elems * sizeof(T) / (double)(1 << 20);
+    const bool light = sizeof(T) == 4 && c->mode == LBIB_KINEMATIC;
+    const int round = c->num_cu * (light ? 2 : 1);
+    const bool crowded = mib > (sizeof(T) == 4 && !light ? 40.0 : 80.0);
+    const bool early = sizeof(T) == 4 || contact || c->mode == LBIB_KINEMATIC;
+    return c->L.inst.size() == 1 && mib <= (early ? 160.0 : 300.0) &&
+           c->ncap <= (crowded ? round * 5 / 8 : round) && own_step_pays<T>(c);
 }
 
 // Whether two steps with capsules go in one pass: from the size on where the pass
@@ -1453,12 +1468,25 @@ static bool fused_pays(const lbib_ctx* c, bool contact)
 // fused or one pass per step / pairs, 32 capsules: FP32 2048x512 20.0 / 29.8, 2048x1536
 // (111 MiB) 38.5 / 47.5, 2048^2 (148 MiB) 74.0 / 56.7, 4096^2 221 / 137; FP64 2048x512
 // 27.8 / 41.3, 2048x1024 (148 MiB) 62.4 / 58.9, 2048^2 131 / 88; batches of 128-512 x
-// 72-128 lattices: 64 of them (70 MiB) 44.9 / 46.2, 128 71.5 / 63.8, 256 129 / 100.
+// 72-128 lattices with one or two capsules, one pass per step / pairs: 64 of them (70 MiB)
+// 44.9 / 46.2, 128 71.5 / 63.8, 256 129 / 100; FP64 64 (156 MiB) 71.9 / 76.3, 72 (185 MiB) 83.0 /
+// 88.2, 80 with three each (195 MiB) 90.3 / 94.5, 96 with three (241 MiB) 117 / 108.
+// And while the populations outweigh the capsules, which pay two IB launches with the
+// near cells and their own steps: one pass per step / pairs at KiB of populations per
+// capsule, Dynamic FP32: 2048^2 594 75.4 / 69.4, 505 76.9 / 74.2, 379 78.5 / 79.7, 149 102 / 138;
+// batches 620 77.5 / 76.4, 400 83.6 / 95.4, 309 166 / 182; FP64: 2048^2 594 140 / 130, 297 176 / 186;
+// batches 847 137 / 127, 618 304 / 261, 206 218 / 240; Kinematic FP32: 2048^2 379 75.1 / 66.5, 303
+// 75.3 / 71.7, 297 76.3 / 77.6; batches 402 81.9 / 80.4, 309 147 / 142, 103 105 / 135; FP64: 594 136 / 126,
+// 297 165 / 178.
 template <typename T>
 static bool pair_pays(const lbib_ctx* c)
 {
-    if (c->L.pop_elems * sizeof(T) < kPairMinBytes || !own_step_pays<T>(c)) return false;
+    const double bytes = (double)c->L.pop_elems * sizeof(T);
+    if (bytes < kPairMinBytes || !own_step_pays<T>(c)) return false;
+    if (bytes < c->ncap * (sizeof(T) == 4 && c->mode == LBIB_KINEMATIC ? 300.0 : 480.0) * 1024.0)
+        return false;
     if (c->L.inst.size() == 1) return grid_two_pays<T>(grid_args(c->L.inst[0]));
+    if (sizeof(T) == 8 && bytes < 210.0 * (1 << 20)) return false;
     double cells = 0, narrow = 0;
     for (const Inst& I : c->L.inst) {
         if (9.0 * I.nxp * I.grid.ny * sizeof(T) >= 4.0 * (1u << 30) - 4096.0) return false;
@@ -1486,8 +1514,10 @@ static lbib_status step_t(lbib_ctx* c, int nsteps)
     // -19 % at 1.0 M).  A batch of small lattices loses (256 lattices,
     // 8.0 M cells, 388 capsules: -17 %, the IB launch runs 2.4x longer beside
     // the far pass), so a batch splits only when asked.
+    // With many capsules it loses as well (one pass per step / split, FP32: 2048^2 with 256
+    // capsules 75 / 90, 4096^2 with 32 222 / 212, with 512 234 / 333).
     const bool want = c->overlap >= 1 || (c->overlap < 0 && c->L.inst.size() == 1 &&
-                                          cells >= kOverlapMinCells);
+                                          cells >= kOverlapMinCells && c->ncap <= c->num_cu / 2);
     // a graph must hold its first step's forcing
     const bool rec = note_recording(c);
     if (rec || c->uncleared) {

@@ -713,3 +713,18 @@ def test_large_lattices_take_two_launches(kind, n, real_bytes):
         cfg["contact_cutoff"] = 2.0
     cfg["capsules"] = _grid_of_capsules(n, n, 4, 4)
     _default_against_serial(cfg, 15, 1.05)
+
+
+@pytest.mark.parametrize("name", ["lattice", "small", "batch"])
+def test_many_capsules_take_two_launches(name):
+    """Lattices full of capsules, whose own steps and near cells cost more than the
+    passes they spare: 1.3 to 1.6 times as long as one IB and one grid launch per step;
+    the bar: one route timed twice, to 6 %."""
+    def lattice(nx, ny, cols, rows):
+        cfg = wl._base("many", nx, ny, 0.8, 4, "dynamic", 0, init_profile=wl.INIT_POISEUILLE,
+                       body_force_x=wl.poiseuille_body_force(0.8, ny, 0.02))
+        cfg["capsules"] = _grid_of_capsules(nx, ny, cols, rows)
+        return cfg
+    cfg = {"lattice": lambda: lattice(2048, 2048, 32, 32), "small": lambda: lattice(1024, 1024, 32, 25),
+           "batch": lambda: [lattice(400, 100, 6, 2) for _ in range(128)]}[name]()
+    _default_against_serial(cfg, 10, 1.06)
