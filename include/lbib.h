@@ -205,7 +205,7 @@ lbib_status lbib_add_rigid_to(lbib_ctx* ctx, int32_t lattice, const double* node
  *    x, no contact force: two steps per pass over the populations, after two
  *    launches that spread the forces of both;
  *    both where the patches are small enough to be stepped beside the node work (on
- *    a small lattice a half-length of about 10 in FP64 and 17 in FP32), and the
+ *    a small lattice a half-length of about 13 in FP64 and 18 in FP32), and the
  *    capsules few enough for the lattice;
  *  - 16 MiB or more without capsules (one lattice, periodic in x; not with
  *    lbib_set_overlap(ctx, 0)): two steps per pass;

@@ -940,15 +940,15 @@ static void size_patches(lbib_ctx* c)
 // 40.8; two steps per pass, 2048^2 (297 MiB): 14 98.8 / 127, 20 116 / 134, 24 160 / 139.  FP32
 // (bands from 22), 512x200: 14 20.2 / 19.6, 22 23.0 / 18.9, 40 76.3 / 29.9; 1024x512: 20 32.2 /
 // 32.1, 24 40.8 / 37.3, 40 95 / 45; 2048^2: 20 69.6 / 79.3, 24 79.5 / 83.7, 40 186 / 103.
-// On small lattices a patch across the wrap or beside a wall costs another round: 256x120
-// with four there, FP64 r 8 18.5 / 18.9, 11 21.8 / 19.9, 12 24.6 / 19.1, FP32 14 17.4 / 16.4, 16 22.3 /
-// 19.9, 21 27.3 / 25.0 (and 12 without a patch there 15.8 / 16.4).
+// Small lattices with the ring in one piece: 200x130 FP64 Kinematic r 8 15.0 / 16.6, 13 17.8 / 18.1;
+// FP32 14 15.3 / 15.8, 18 17.3 / 17.8, 21 19.3 / 18.7; 256x120 with four, two of them across the wrap, FP64 8
+// 16.9 / 18.1, 13 19.7 / 19.8, FP32 18 18.8 / 18.8, 20 20.2 / 19.3.
 template <typename T>
 static bool own_step_pays(const lbib_ctx* c)
 {
     const double mib = c->L.pop_elems * sizeof(T) / (double)(1 << 20);
     if (mib < (sizeof(T) == 4 ? 24.0 : 12.0))
-        return c->own.bands == 1 && c->own.ring <= (sizeof(T) == 4 ? 1800 : 1100);
+        return c->own.bands == 1 && c->own.ring <= 2310;
     return c->own.us <= 4.0 + 0.2 * mib;
 }
 

@@ -607,7 +607,7 @@ __device__ __forceinline__ void set_geo(PatchGeo<T>& Q, const Patch<T>& P, const
 
 // Row i / width of item i (width = 1 / inv): exact, as (i + 1/2) / width is at
 // least 1 / (2 width) from the next integer and a patch has under 2^14 cells.
-__device__ __forceinline__ int row_of(int i, float inv)
+__host__ __device__ __forceinline__ int row_of(int i, float inv)
 {
     return (int)(((float)i + 0.5f) * inv);
 }
@@ -673,8 +673,62 @@ __device__ __forceinline__ void collide_ring_cell(const PatchGeo<T>& Q, const Gr
     }
 }
 
+// Positions 0 .. count - 1 of an axis from lattice coordinate o on whose coordinate is
+// on an end of it (0, size - 1) or off the lattice: s0 .. s0 + n0 - 1 and s1 .. s1 + n1 - 1.
+// A periodic axis wraps, with 0 <= o < size and count <= size.
+struct AxisEnds {
+    int n0, s1, n1;  // s0 = 0
+    __host__ __device__ __forceinline__ int count() const { return n0 + n1; }
+};
+
+__host__ __device__ __forceinline__ AxisEnds axis_ends(int o, int count, int size, int periodic)
+{
+    AxisEnds e;
+    const int a = 1 - o, b = size - 1 - o, c = size + 1 - o;
+    e.n0 = periodic ? (o == 0 ? 1 : 0) : (a < 0 ? 0 : (a > count ? count : a));
+    e.s1 = b < e.n0 ? e.n0 : (b > count ? count : b);
+    e.n1 = (periodic && c < count ? c : count) - e.s1;
+    return e;
+}
+
+// The cells of a box (w columns from lattice coordinate x on, h rows from y on) that
+// need another rule than the nine plain loads, one after the other (those at a corner
+// twice): its rows and then its columns at the lattice's ends, so that a block takes
+// them in one round (the whole box, a row of it at a time, took a memory latency in
+// every round).  A box that wraps onto itself, or one without plain loads: all cells.
+struct OtherCells {
+    AxisEnds cols, rows;
+    int w, h, n, in_rows;
+    float inv_w, inv_h;
+    __host__ __device__ __forceinline__ OtherCells(const GridArgs& g, bool all, int x, int y, int w_, int h_)
+    {
+        w = w_;
+        h = h_;
+        inv_w = 1.0f / (float)w;
+        inv_h = 1.0f / (float)h;
+        all = all || (g.periodic_x && w > g.nx) || (g.periodic_y && h > g.ny);
+        cols = axis_ends(g.periodic_x ? wrap_add(x, 0, g.nx) : x, w, g.nx, g.periodic_x);
+        rows = axis_ends(g.periodic_y ? wrap_add(y, 0, g.ny) : y, h, g.ny, g.periodic_y);
+        if (all) {
+            rows.n0 = h;
+            rows.n1 = cols.n0 = cols.n1 = 0;
+        }
+        in_rows = rows.count() * w;
+        n = in_rows + cols.count() * h;
+    }
+    __host__ __device__ __forceinline__ void cell(int i, int& lx, int& ly) const
+    {
+        const bool r = i < in_rows;  // (selects: both halves stay in registers)
+        const int q = r ? i : i - in_rows, k = row_of(q, r ? inv_w : inv_h);
+        const int n0 = r ? rows.n0 : cols.n0, s1 = r ? rows.s1 : cols.s1;
+        const int line = k < n0 ? k : s1 + k - n0, along = q - k * (r ? w : h);
+        lx = r ? along : line;
+        ly = r ? line : along;
+    }
+};
+
 // Whether the nine sources of a cell are its plain neighbours.
-__device__ __forceinline__ bool plain_cell(const GridArgs& g, int x, int y)
+__host__ __device__ __forceinline__ bool plain_cell(const GridArgs& g, int x, int y)
 {
     return (unsigned)(x - 1) < (unsigned)(g.nx - 2) && (unsigned)(y - 1) < (unsigned)(g.ny - 2);
 }
@@ -765,9 +819,11 @@ template <typename T>
 __device__ void stage_other_cells(const PatchGeo<T>& Q, const GridArgs& g, const Patch<T>& P)
 {
     if (Q.plain) return;
-    for (int i = threadIdx.x; i < Q.W * Q.H; i += blockDim.x) {
-        const int ly = row_of(i, Q.inv_w), lx = i - ly * Q.W;
-        int x, y;
+    const OtherCells others(g, Q.far_offsets, Q.bx, Q.by, Q.W, Q.H);
+    for (int j = threadIdx.x; j < others.n; j += blockDim.x) {
+        int lx, ly, x, y;
+        others.cell(j, lx, ly);
+        const int i = ly * Q.W + lx;
         if (!patch_cell(Q, g, lx, ly, x, y) || !has_moments(g, x, y)) {
             P.drho[i] = P.ux[i] = P.uy[i] = T(NAN);
             continue;
@@ -825,9 +881,11 @@ template <typename T>
 __device__ void step_other_cells(const PatchGeo<T>& Q, const GridArgs& g, const Patch<T>& P)
 {
     if (Q.plain) return;
-    for (int i = threadIdx.x; i < Q.RW * (Q.rows + 2); i += blockDim.x) {
-        const int ly = row_of(i, Q.inv_rw), lx = i - ly * Q.RW;
-        int x, y;
+    const OtherCells others(g, false, Q.bx - 1, Q.by + Q.by0 - 1, Q.RW, Q.rows + 2);
+    for (int j = threadIdx.x; j < others.n; j += blockDim.x) {
+        int lx, ly, x, y;
+        others.cell(j, lx, ly);
+        const int i = ly * Q.RW + lx;
         if (!patch_cell(Q, g, lx - 1, Q.by0 + ly - 1, x, y) || plain_cell(g, x, y)) continue;
         const longlong2 f = *reinterpret_cast<const longlong2*>(Q.fib + 2 * ((size_t)y * g.nxp + x));
         T s[9], Fx, Fy;

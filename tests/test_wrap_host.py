@@ -138,3 +138,60 @@ def test_near_regions_of_any_box(tmp_path):
     exe = compiled(tmp_path, RECTS)
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout
+
+
+OTHERS = r"""
+#include "lbib_device.h"
+#include <stdio.h>
+#include <vector>
+using namespace lbib;
+
+int main()
+{
+    int bad = 0;
+    for (int nx : {8, 11, 30})
+        for (int ny : {9, 25})
+            for (int px = 0; px < 2; px++)
+                for (int py = 0; py < 2; py++)
+                    for (int w = 3; w <= 12; w += 3)
+                        for (int h = 3; h <= 12; h += 2)
+                            for (int x0 = px ? -1 : -w - 2; x0 <= nx + 2; x0++)
+                                for (int y0 = py ? -1 : -h - 2; y0 <= ny + 2; y0++) {
+                                    GridArgs g = {};
+                                    g.nx = nx;
+                                    g.ny = ny;
+                                    g.periodic_x = px;
+                                    g.periodic_y = py;
+                                    const OtherCells o(g, false, x0, y0, w, h);
+                                    std::vector<int> got(w * h);
+                                    bool ok = true;
+                                    for (int j = 0; j < o.n; j++) {
+                                        int lx, ly;
+                                        o.cell(j, lx, ly);
+                                        ok = ok && lx >= 0 && lx < w && ly >= 0 && ly < h;
+                                        if (ok) got[ly * w + lx] = 1;
+                                    }
+                                    const bool all = (px && w > nx) || (py && h > ny);
+                                    for (int ly = 0; ly < h; ly++)
+                                        for (int lx = 0; lx < w; lx++) {
+                                            const int x = px ? ((x0 + lx) % nx + nx) % nx : x0 + lx;
+                                            const int y = py ? ((y0 + ly) % ny + ny) % ny : y0 + ly;
+                                            const int want = all || !plain_cell(g, x, y);
+                                            ok = ok && got[ly * w + lx] == want;
+                                        }
+                                    if (!ok && bad++ < 5)
+                                        printf("box %d x %d at (%d, %d) on %d x %d, periodic %d %d\n", w,
+                                               h, x0, y0, nx, ny, px, py);
+                                }
+    return bad != 0;
+}
+"""
+
+
+def test_cells_of_a_patch_at_the_ends(tmp_path):
+    """The cells of a patch that do not take the nine plain loads: exactly those on the
+    lattice's end rows and columns and off it, for every place of a box on walls, open
+    ends and wraps; all cells of a box that wraps onto itself."""
+    exe = compiled(tmp_path, OTHERS)
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, r.stdout
