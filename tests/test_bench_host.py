@@ -28,3 +28,13 @@ def test_traffic_needs_the_current_kernel_source(tmp_path, monkeypatch):
     summary.write_text(f"kernel_source_sha256: {sha}\nhbm_bytes_per_launch: 1206524918\n")
     assert bench.traffic_from_profile(sha) == 1206524918.0
     assert bench.traffic_from_profile("0" * 64) is None  # taken on other source
+
+
+def test_bytes_are_those_of_the_schedule():
+    """Fractions of the HBM peak count two steps per pass where the timed steps take
+    them."""
+    from paper_1903_03356_amd import workloads as wl
+    fused = [bench.steps_per_pass(wl.fused_bench(n=n, steps=1)) for n in (1024, 2048, 4096)]
+    grid = [bench.steps_per_pass(wl.grid_bench(n=n)) for n in (512, 1024, 4096)]
+    assert fused == [1, 2, 2] and grid == [1, 2, 2]
+    assert bench.steps_per_pass(wl.fused_bench(n=4096, steps=1), queue_waits=True) == 1
