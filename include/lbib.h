@@ -101,7 +101,9 @@ typedef struct {
 typedef enum {
     LBIB_BUF_POPS_A = 0, /* populations, ping */
     LBIB_BUF_POPS_B = 1, /* populations, pong */
-    LBIB_BUF_FORCE = 2,  /* IB force field, two to four time levels, fixed point */
+    LBIB_BUF_FORCE = 2,  /* IB force field, fixed point: 16 bytes a cell (rows padded to 64) and
+                            time level; four levels up to 2^28 cells in all (4096^2: 1.1 GB,
+                            read and written only beside the capsules), two beyond */
     LBIB_BUF_FLAGS = 3,  /* active-segment flags of the force field */
     LBIB_BUF_NODES = 4,  /* per-node capsule state */
     LBIB_BUF_CAPS = 5,   /* per-capsule records */

@@ -1269,7 +1269,7 @@ static lbib_status step_body(lbib_ctx* c, long long n, int pb, int pa, bool cont
 //   IB     step n + 1 from P^n (ib_block, STEP): spreads F^{n+1}; beside it f*^n near
 //          the capsules into the buffer of P^{n+2}, and the clearing of two levels
 //   IB     step n + 2 in the same way from there: spreads F^{n+2}
-//   grid   P^n -> P^{n+2}, over the cells the first launch left
+//   grid   P^n -> P^{n+2}, every cell (the near cells' f*^n are written over)
 template <typename T>
 static lbib_status step_pair_t(lbib_ctx* c, int nsteps)
 {

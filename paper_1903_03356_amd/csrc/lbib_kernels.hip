@@ -1025,8 +1025,8 @@ __device__ __forceinline__ void comp_add(T& hi, T& lo, T d)
 // of the fit splits into one straight-line fit per axis (AxisFit); the rows
 // are products of the axes' values:
 //   phi = b_x a_y + a_x (b_y - a_y),  dphi/dx = s_x a_y,  dphi/dy = a_x s_y.
-// Six exponentials and two divisions where the inverse of the 3x3 system took
-// nine and one, and about a third of its FP64 operations; the IB launch is
+// Six exponentials and two reciprocals (recip) where the inverse of the 3x3 system
+// took nine and a division, and about a third of its FP64 operations; the IB launch is
 // bound by this chain (one or two waves per SIMD), so it shortens with it.
 // Outputs: centre (cx, cy), phi (value) and, if G, the slope rows of the local
 // fit.
@@ -1780,8 +1780,9 @@ __device__ void rigid_update(const IBArgs<T>& a, const Scratch<T>& S, const Patc
 // STEP: the launch also holds grid step n - 1 (k_step): a.pops is P^{n-1}, and
 // the block takes the moments of its patch at time n from its own grid step
 // there (step_cells), not from P^n.
-// Such a launch runs phases B and A of started capsules and no diagnostics,
-// near regions or tape; without EXTRA the code of rigid particles and of the contact
+// Such a launch runs phases B and A of started capsules and no diagnostics, near
+// map or tape (the second launch of a pair writes its node boxes, `rects`); without
+// EXTRA the code of rigid particles and of the contact
 // force's boxes is left out too (0.2 us of a lone capsule's chain).
 template <typename T, bool DYN, bool STEP, bool EXTRA>
 __device__ __forceinline__ void ib_block(const IBArgs<T>& a0, unsigned char* smem,
