@@ -730,3 +730,30 @@ def test_many_capsules_take_two_launches(name):
     cfg = {"lattice": lambda: lattice(2048, 2048, 32, 32), "small": lambda: lattice(1024, 1024, 32, 25),
            "batch": lambda: [lattice(400, 100, 6, 2) for _ in range(128)]}[name]()
     _default_against_serial(cfg, 10, 1.06)
+
+
+@pytest.mark.parametrize("mode", ["dynamic", "kinematic"])
+@pytest.mark.parametrize("name", ["batch", "bands"])
+def test_two_steps_with_capsules_fp64(name, mode):
+    """Two steps in one pass in FP64: a batch past the size from which it takes them, and
+    capsules whose rings go in three bands of rows on a lattice large enough for that;
+    the same bits as a grid and an IB launch per step."""
+    if name == "batch":
+        cfg = [dict(c, real_bytes=8) for c in _pair_case("batch", 4, mode)]
+    else:
+        cfg = wl._base(name, 1450, 1447, 0.8, 8, mode, 0, periodic_y=1, init_profile=wl.INIT_UNIFORM,
+                       init_u=(0.02, -0.02))
+        cfg["capsules"] = [wl.capsule(_ellipse(5.0, 1440.0, 18.0, 17.0, 150), 0.05, 0.0, 1.0, 1.2),
+                           wl.capsule(_ellipse(700.0, 300.0, 18.0, 16.0, 150), 0.05, 0.0, 1.0, 1.2)]
+    make = lbib.Batch if isinstance(cfg, list) else lbib.Sim
+    a, b = make(cfg), make(cfg)
+    b.set_overlap(False)
+    for n in (3, 4):
+        a.step(n)
+        b.step(n)
+        for i in range(len(cfg) if isinstance(cfg, list) else 1):
+            np.testing.assert_array_equal(a.pops(i), b.pops(i))
+            np.testing.assert_array_equal(a.force(i), b.force(i))
+        for c in range(len(a.nv)):
+            np.testing.assert_array_equal(np.stack(a.capsule(c)), np.stack(b.capsule(c)))
+    assert a.check() == b.check() == 0
