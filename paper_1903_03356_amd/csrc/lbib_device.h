@@ -116,8 +116,10 @@ __device__ __forceinline__ double recip(double x)
 // own: one step is bound by memory either way, two steps in one pass
 // (k_grid_two) would not be.  The rest population takes C less the other eight
 // shares, so that mass is conserved whatever 1/9 rounds to.
-template <typename T>
-__device__ __forceinline__ void collide(const T (&s)[9], Uref<T> ur, T om, T Fx, T Fy, T (&o)[9])
+// put(i, v) takes population i: EACH, as soon as it is known (collide_pulled), or
+// else all of them last.
+template <bool EACH, typename T, typename Put>
+__device__ __forceinline__ void collide(const T (&s)[9], Uref<T> ur, T om, T Fx, T Fy, Put put)
 {
     const T d13 = s[1] - s[3], d24 = s[2] - s[4], d57 = s[5] - s[7], d68 = s[6] - s[8];
     const T p13 = s[1] + s[3], p24 = s[2] + s[4], p57 = s[5] + s[7], p68 = s[6] + s[8];
@@ -136,21 +138,44 @@ __device__ __forceinline__ void collide(const T (&s)[9], Uref<T> ur, T om, T Fx,
     const T c9 = C * T(1.0 / 9.0);
     const T q = c9 + S;
     const T w3a = FirstOrderW<T>::axis, w3d = FirstOrderW<T>::diag;
-    const T Ex = fma(-hom, p13, tx + c9), Ey = fma(-hom, p24, ty + c9);
-    const T Ep = fma(-hom, p57, T(0.25) * (q + X)), Em = fma(-hom, p68, T(0.25) * (q - X));
-    const T Ox = fma(om, fma(w3a, mx, T(-0.5) * d13), w3a * pFx);
-    const T Oy = fma(om, fma(w3a, my, T(-0.5) * d24), w3a * pFy);
-    const T Op = fma(om, fma(w3d, mx + my, T(-0.5) * d57), w3d * (pFx + pFy));
-    const T Om = fma(om, fma(w3d, my - mx, T(-0.5) * d68), w3d * (pFy - pFx));
-    o[0] = s[0] + fma(-om, s[0], fma(T(-5), c9, C));
-    o[1] = s[1] + (Ex + Ox);
-    o[2] = s[2] + (Ey + Oy);
-    o[3] = s[3] + (Ex - Ox);
-    o[4] = s[4] + (Ey - Oy);
-    o[5] = s[5] + (Ep + Op);
-    o[6] = s[6] + (Em + Om);
-    o[7] = s[7] + (Ep - Op);
-    o[8] = s[8] + (Em - Om);
+    const auto Ex = [&] { return fma(-hom, p13, tx + c9); };
+    const auto Ey = [&] { return fma(-hom, p24, ty + c9); };
+    const auto Ep = [&] { return fma(-hom, p57, T(0.25) * (q + X)); };
+    const auto Em = [&] { return fma(-hom, p68, T(0.25) * (q - X)); };
+    const auto Ox = [&] { return fma(om, fma(w3a, mx, T(-0.5) * d13), w3a * pFx); };
+    const auto Oy = [&] { return fma(om, fma(w3a, my, T(-0.5) * d24), w3a * pFy); };
+    const auto Op = [&] { return fma(om, fma(w3d, mx + my, T(-0.5) * d57), w3d * (pFx + pFy)); };
+    const auto Om = [&] { return fma(om, fma(w3d, my - mx, T(-0.5) * d68), w3d * (pFy - pFx)); };
+    const auto rest = [&] { put(0, s[0] + fma(-om, s[0], fma(T(-5), c9, C))); };
+    const auto pair = [&](int i, T E, T O) {
+        put(i, s[i] + (E + O));
+        put(i + 2, s[i + 2] + (E - O));
+    };
+    if (EACH) {
+        rest();
+        pair(1, Ex(), Ox());
+        pair(2, Ey(), Oy());
+        pair(5, Ep(), Op());
+        pair(6, Em(), Om());
+    } else {
+        const T ex = Ex(), ey = Ey(), ep = Ep(), em = Em();
+        const T ox = Ox(), oy = Oy(), op = Op(), on = Om();
+        rest();
+        put(1, s[1] + (ex + ox));
+        put(2, s[2] + (ey + oy));
+        put(3, s[3] + (ex - ox));
+        put(4, s[4] + (ey - oy));
+        put(5, s[5] + (ep + op));
+        put(6, s[6] + (em + on));
+        put(7, s[7] + (ep - op));
+        put(8, s[8] + (em - on));
+    }
+}
+
+template <typename T>
+__device__ __forceinline__ void collide(const T (&s)[9], Uref<T> ur, T om, T Fx, T Fy, T (&o)[9])
+{
+    collide<false>(s, ur, om, Fx, Fy, [&o](int i, T v) { o[i] = v; });
 }
 
 // Population loads of the pull.  The lines of the three directions with

@@ -44,16 +44,31 @@ __device__ __forceinline__ void put_pop(T* p, T v)
 
 // One lattice node with total force (Fx, Fy), from its pulled and completed
 // populations s: force-corrected moments, BGK + forcing, store.
-template <typename T, bool NT = true>
+// EACH: a value is stored as soon as it is known (the scheduling barrier keeps it
+// so).  All nine stores of a wave in one burst behind the arithmetic lengthen the
+// smallest lattices' step, and cost one that just outgrows the L2 up to a tenth of
+// it (single pass, us per step, burst -> now: FP32 4000 x 100 6.24 -> 5.56,
+// 3041 x 134 6.48 -> 6.24, FP64 64^2 3.15 -> 3.06; equal from 800^2 on).  Beside
+// the IB chain (k_step) the burst is the better one by 0.8 % (2048 x 512 with 32
+// capsules).
+template <typename T, bool NT = true, bool EACH = true>
 __device__ __forceinline__ void collide_pulled(const T (&s)[9], T* __restrict__ dst,
                                                const GridArgs& g, int x, int y, T Fx, T Fy)
 {
-    T o[9];
-    collide(s, uref_at<T>(g, y), (T)g.omega, Fx, Fy, o);
     const size_t plane = (size_t)g.ny * g.nxp;
-    T* out = dst + (size_t)y * g.nxp + x;
+    if (EACH) {
+        T* out = dst + (size_t)y * g.nxp + x;
+        collide<true>(s, uref_at<T>(g, y), (T)g.omega, Fx, Fy, [=](int i, T v) {
+            put_pop<T, NT>(&out[i * plane], v);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    } else {
+        T o[9];
+        collide(s, uref_at<T>(g, y), (T)g.omega, Fx, Fy, o);
+        T* out = dst + (size_t)y * g.nxp + x;
 #pragma unroll
-    for (int i = 0; i < 9; i++) put_pop<T, NT>(&out[i * plane], o[i]);
+        for (int i = 0; i < 9; i++) put_pop<T, NT>(&out[i * plane], o[i]);
+    }
 }
 
 // One lattice node with the IB force of this step.  A wave holds one 64-cell
@@ -70,7 +85,7 @@ __device__ __forceinline__ void collide_pulled(const T (&s)[9], T* __restrict__ 
 // The far part skips a segment whose near-map entry carries this step's stamp
 // (the near pass computes it) and raises ST_NEAR where it finds an active
 // force flag: the near regions were too small.
-template <bool OPEN, bool NT = true, bool FAR = false, typename T>
+template <bool OPEN, bool NT = true, bool FAR = false, bool EACH = true, typename T>
 __device__ __forceinline__ void grid_cell(const T* __restrict__ src, T* __restrict__ dst,
                                           const long long* __restrict__ fib_now,
                                           const int* __restrict__ flags_now,
@@ -107,7 +122,7 @@ __device__ __forceinline__ void grid_cell(const T* __restrict__ src, T* __restri
             Fy += fix_to_real<T>(f.y);
         }
         pull_complete<T, OPEN>(src, x, y, g, Fx, s);
-        collide_pulled<T, NT>(s, dst, g, x, y, Fx, Fy);
+        collide_pulled<T, NT, EACH>(s, dst, g, x, y, Fx, Fy);
     }
     if (old) {
         *reinterpret_cast<longlong2*>(fib_old + 2 * cell) = make_longlong2(0, 0);
@@ -318,7 +333,7 @@ __device__ void pair_near(const T* __restrict__ src, T* __restrict__ dst,
         const longlong2 f = *reinterpret_cast<const longlong2*>(fib_now + 2 * cell);
         const T Fx = (T)g.gx + fix_to_real<T>(f.x), Fy = fix_to_real<T>(f.y);
         pull_complete<T, false>(src, x, y, g, Fx, s);
-        collide_pulled<T, false>(s, dst, g, x, y, Fx, Fy);
+        collide_pulled<T, false, false>(s, dst, g, x, y, Fx, Fy);
     }
 }
 
@@ -2320,8 +2335,8 @@ __global__ __launch_bounds__(kIBThreads) void k_step(IBArgs<T> a0, int cap_block
     for (int r = 0; r < ROWS; r++) {
         const int y = y0 + WAVES * r;
         if (y < g.ny)
-            grid_cell<true, false>(src, dst, fib_now, flags_now, fib_old, flags_old, g, y, seg,
-                                   lane);
+            grid_cell<true, false, false, false>(src, dst, fib_now, flags_now, fib_old, flags_old,
+                                                 g, y, seg, lane);
     }
 }
 
