@@ -184,6 +184,12 @@ __device__ __forceinline__ void collide(const T (&s)[9], Uref<T> ur, T om, T Fx,
 // x-shifted directions, which the neighbouring segment's wave reads too.
 // Measured on a 4096 x 4096 pass: streaming the three e_x = 0 loads 2 % faster
 // than plain loads, streaming all nine 0.5 % slower.
+// Without STREAM they are plain loads: a small lattice's lines still lie in the
+// L2 from the step that wrote them, and the buffer is written again in the step
+// after this one (single pass, us per step, streaming -> plain: FP64 4039 x 51
+// 7.55 -> 6.50, 900^2 20.1 -> 19.1, 1200^2 31.7 -> 31.5, but 4000 x 500 43.7 ->
+// 51.2, 1448^2 49.4 -> 53.3; FP32 3041 x 134 6.24 -> 5.71, 1448^2 24.8 -> 23.6,
+// 2048^2 50.5 -> 51.0: kPlainLoadMaxBytes lies between them).
 template <typename T>
 __device__ __forceinline__ T ld_stream(const T* p)
 {

@@ -9,6 +9,7 @@ namespace lbib {
 // Force field: one 64-cell row segment per wavefront of the grid kernel.
 constexpr int kSegW = 64;
 constexpr double kPlainStoreMaxBytes = 384.0 * (1 << 20);  // single pass: plain stores up to here
+constexpr double kPlainLoadMaxBytes = 192.0 * (1 << 20);  // and plain loads up to here
 constexpr double kTwoMinBytes = 16.0 * (1 << 20);  // two steps in one pass: populations from here
 constexpr double kPairMinBytes = 140.0 * (1 << 20);  // the same with capsules
 constexpr int kGridRowsPerThread = 1;  // grid kernel: nodes per thread, 4 rows apart

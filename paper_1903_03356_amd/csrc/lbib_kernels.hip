@@ -85,7 +85,7 @@ __device__ __forceinline__ void collide_pulled(const T (&s)[9], T* __restrict__ 
 // The far part skips a segment whose near-map entry carries this step's stamp
 // (the near pass computes it) and raises ST_NEAR where it finds an active
 // force flag: the near regions were too small.
-template <bool OPEN, bool NT = true, bool FAR = false, bool EACH = true, typename T>
+template <bool OPEN, bool NT = true, bool FAR = false, bool EACH = true, bool STREAM = true, typename T>
 __device__ __forceinline__ void grid_cell(const T* __restrict__ src, T* __restrict__ dst,
                                           const long long* __restrict__ fib_now,
                                           const int* __restrict__ flags_now,
@@ -101,7 +101,7 @@ __device__ __forceinline__ void grid_cell(const T* __restrict__ src, T* __restri
     // lanes past the row's end (x < nxp) load the last node's values and
     // store nothing
     T s[9];
-    pull_loads<T, OPEN>(src, in ? x : g.nx - 1, y, g, s);
+    pull_loads<T, OPEN, STREAM>(src, in ? x : g.nx - 1, y, g, s);
     const int act = flags_now[fidx];
     const int old = flags_old[fidx];
     const int mark = FAR ? near_map[fidx] : 0;
@@ -345,7 +345,7 @@ __device__ void pair_near(const T* __restrict__ src, T* __restrict__ dst,
 // (accesses spread over all HBM channels), and the cache lines that the
 // x-shifted pulls share between neighbouring segments of a band stay in the L2
 // of the XCD that owns the band.
-template <typename T, int ROWS, bool OPEN, bool NT>
+template <typename T, int ROWS, bool OPEN, bool NT, bool STREAM>
 __global__ __launch_bounds__(kSegW * 4) void k_grid_step(
     const T* __restrict__ src, T* __restrict__ dst, const long long* __restrict__ fib_now,
     const int* __restrict__ flags_now, long long* __restrict__ fib_old,
@@ -365,7 +365,8 @@ __global__ __launch_bounds__(kSegW * 4) void k_grid_step(
     for (int r = 0; r < ROWS; r++) {
         const int y = y0 + 4 * r;
         if (y < g.ny)
-            grid_cell<OPEN, NT>(src, dst, fib_now, flags_now, fib_old, flags_old, g, y, seg, lane);
+            grid_cell<OPEN, NT, false, true, STREAM>(src, dst, fib_now, flags_now, fib_old,
+                                                     flags_old, g, y, seg, lane);
     }
 }
 
@@ -764,21 +765,19 @@ hipError_t launch_grid_step(const T* src, T* dst, const long long* fib_now, cons
 {
     constexpr int R = kGridRowsPerThread;
     const int blocks = grid_blocks(g.ny, g.nseg);
-    // streaming stores once the two population buffers outgrow the cache
-    const bool nt = 2.0 * 9.0 * g.ny * g.nxp * sizeof(T) > kPlainStoreMaxBytes;
-    const dim3 grid((unsigned)blocks), block(kSegW * 4);
-    if (g.periodic_x && nt)
-        hipLaunchKernelGGL((k_grid_step<T, R, false, true>), grid, block, 0, s, src, dst, fib_now,
-                           flags_now, fib_old, flags_old, g);
-    else if (g.periodic_x)
-        hipLaunchKernelGGL((k_grid_step<T, R, false, false>), grid, block, 0, s, src, dst, fib_now,
-                           flags_now, fib_old, flags_old, g);
-    else if (nt)
-        hipLaunchKernelGGL((k_grid_step<T, R, true, true>), grid, block, 0, s, src, dst, fib_now,
-                           flags_now, fib_old, flags_old, g);
-    else
-        hipLaunchKernelGGL((k_grid_step<T, R, true, false>), grid, block, 0, s, src, dst, fib_now,
-                           flags_now, fib_old, flags_old, g);
+    // streaming stores once the two population buffers outgrow the cache, and
+    // streaming loads (pull_loads) where they outgrow the L2 by far
+    const double bytes = 2.0 * 9.0 * g.ny * g.nxp * sizeof(T);
+    const bool nt = bytes > kPlainStoreMaxBytes, stream = bytes > kPlainLoadMaxBytes;
+    auto k = &k_grid_step<T, R, true, false, false>;
+    if (g.periodic_x)
+        k = nt       ? &k_grid_step<T, R, false, true, true>
+            : stream ? &k_grid_step<T, R, false, false, true>
+                     : &k_grid_step<T, R, false, false, false>;
+    else if (stream)
+        k = nt ? &k_grid_step<T, R, true, true, true> : &k_grid_step<T, R, true, false, true>;
+    hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(kSegW * 4), 0, s, src, dst, fib_now,
+                       flags_now, fib_old, flags_old, g);
     return hipGetLastError();
 }
 

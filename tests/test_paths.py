@@ -592,6 +592,32 @@ def test_timed_steps_take_a_launch_each(real_bytes):
     np.testing.assert_array_equal(a.pops(), c.pops())
 
 
+@pytest.mark.parametrize("nx,ny,real_bytes,ends", [
+    (1601, 1680, 4, "walls"), (1601, 1681, 4, "walls"),   # both buffers just within and just
+    (1024, 1285, 8, "walls"), (1024, 1286, 8, "walls"),   # past 192 MiB
+    (1024, 1285, 8, "open"), (1024, 1286, 8, "open"),
+])
+def test_single_passes_around_the_load_rule(nx, ny, real_bytes, ends):
+    """A launch per grid step where the kernel turns from plain to streaming loads: the
+    same bits as two steps per pass, and (open ends, a capsule) as one launch per step."""
+    if ends == "open":
+        cfg = wl.open_channel(nx, ny, 0.8, 0.02, real_bytes=real_bytes, mode="dynamic",
+                              init_profile=wl.INIT_INLET)
+        cfg["capsules"] = [wl.capsule(wl.circle_nodes(80.3, 70.6, 8.0, 60), 0.05, 0.0, 1.0, 1.2)]
+    else:
+        cfg = wl._base("one", nx, ny, 0.7, real_bytes, "kinematic", 0, u_top=0.02)
+    f0 = wl.random_populations(nx, ny, seed=6, amp=0.01)
+    a, b = lbib.Sim(cfg), lbib.Sim(cfg)
+    b.set_overlap(False)
+    for s in (a, b):
+        s.set_pops(f0)
+    for n in (4, 1):
+        a.step(n)
+        b.step(n)
+        np.testing.assert_array_equal(a.pops(), b.pops())
+    assert a.check() == b.check()
+
+
 def _step_us(sim, steps, calls=1):
     """Microseconds a step, the least of seven timings."""
     import torch
